@@ -729,7 +729,10 @@ DavResult davidson(DeviceMolecule& m, const DavOptions& opt, DenseSolver& ds, Da
         hipLaunchKernelGGL(scale_cols_kernel, dim3(K), dim3(256), 0, st, uco, Smax, S, K, om, 1.5);
       } else {
         copy(st, w.Hs.p, w.Mp.p, static_cast<long>(S) * Smax);
-        ds.eigh_lowest(S, w.Hs.p, Smax, std::min(2 * K, S), w.w2.p);  // K Ritz pairs, 2K for a collapse
+        // K Ritz pairs; 2K where this iteration may end in a collapse (the
+        // basis would overflow, or the low-precision phase may step up)
+        const bool may_collapse = S + K > Smax || prec != kPrecFP64;
+        ds.eigh_lowest(S, w.Hs.p, Smax, may_collapse ? std::min(2 * K, S) : std::min(K, S), w.w2.p);
         hipLaunchKernelGGL(omega_kernel, dim3(ceil_div(K, 64)), dim3(64), 0, st, K, w.w2.p, om, 0);
         copy(st, tco, w.Hs.p, static_cast<long>(K) * Smax);
       }

@@ -147,10 +147,6 @@ __global__ void __launch_bounds__(256) reduce_partials_wide_kernel(int nchunks, 
   if (threadIdx.x == 0) out[static_cast<long>(idx / nt) * ldo + idx % nt] = red[0];
 }
 
-// split-K chunk of the inner products: short enough that a basis of a few
-// hundred vectors still spreads over thousands of workgroups
-constexpr long kDotChunk = 1024;
-
 }  // namespace
 
 template <class TB, class TC>
@@ -221,8 +217,18 @@ __device__ __forceinline__ void load4(const float* p, double* o) {
   o[3] = a[3];
 }
 
-// X and Y rows of FP64 or FP32 elements (FP32 ones widened on load); FP64 products
-template <int NX, class TX, class TY>
+// 4 contiguous values whose address is only a multiple of the element size
+template <class T>
+__device__ __forceinline__ void load4_any(const T* p, double* o) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) o[q] = static_cast<double>(p[q]);
+}
+
+// X and Y rows of FP64 or FP32 elements (FP32 ones widened on load); FP64
+// products.  ALIGNED: row starts are 16-byte aligned.  Otherwise (an odd row
+// length, as in C40H42 with nov = 101 * 101) the same four values per lane
+// come as four element loads, which hit the same cache lines.
+template <int NX, class TX, class TY, bool ALIGNED>
 __global__ void __launch_bounds__(256) skinny_dots_kernel(int ns, int nt, const TX* __restrict__ X, long ldx,
                                                           const TY* __restrict__ Y, long ldy, long len,
                                                           long chunk, double* __restrict__ part) {
@@ -250,9 +256,15 @@ __global__ void __launch_bounds__(256) skinny_dots_kernel(int ns, int nt, const 
   auto load = [&](long blk, double (*xv)[4], double (*yv)[4]) {
     const long kk = k0 + 16 * blk + 4 * g;
 #pragma unroll
-    for (int a = 0; a < NX; ++a) load4(xr[a] + kk, xv[a]);
+    for (int a = 0; a < NX; ++a) {
+      if constexpr (ALIGNED) load4(xr[a] + kk, xv[a]);
+      else load4_any(xr[a] + kk, xv[a]);
+    }
 #pragma unroll
-    for (int b = 0; b < 2; ++b) load4(yr[b] + kk, yv[b]);
+    for (int b = 0; b < 2; ++b) {
+      if constexpr (ALIGNED) load4(yr[b] + kk, yv[b]);
+      else load4_any(yr[b] + kk, yv[b]);
+    }
   };
   auto mma = [&](double (*xv)[4], double (*yv)[4]) {
 #pragma unroll
@@ -303,81 +315,56 @@ __global__ void __launch_bounds__(256) skinny_dots_kernel(int ns, int nt, const 
 
 }  // namespace
 
-// chunk length of the tall-skinny path: about 1024 workgroups, at least 256
+// Chunk length: about 1024 workgroups for long vectors, at least 256 values.
+// Vectors below 4096 values take chunks of 64 (4 MFMA blocks a wavefront): one
+// molecule of 30-90 AOs gives only a handful of 128-row groups, and the short
+// chunks keep the serial part near a microsecond.
+constexpr long kShortDot = 4096;
 long skinny_chunk(int nt, long len) {
   const long groups = (nt + 127) / 128;
   const long want = std::max<long>(1, 1024 / groups);
   long chunk = (len + want - 1) / want;
   chunk = (chunk + 15) / 16 * 16;
-  return std::max<long>(chunk, 256);
+  return std::max<long>(chunk, len < kShortDot ? 64 : 256);
 }
 
 // Rows of X per pass of the inner products: the tall-skinny kernels hold at
 // most 48 rows; more rows take several passes, each reading Y once.
 constexpr int kDotRows = 48;
 
-// split-K chunk of the general path: kDotChunk, or longer for very long
-// vectors so that there are at most 256 chunks
-long dot_chunk(long len) { return std::max<long>(kDotChunk, (len + 255) / 256); }
-
-// Partial sums of either path for one pass of at most kDotRows rows.  The
-// tall-skinny path makes at most min(1024, len / 256) chunks whatever nt is,
-// so the count is monotone in ns and nt: a workspace sized for the largest
-// shape serves every smaller one.
+// Partial sums of one pass of at most kDotRows rows: whatever nt is, at most
+// 64 chunks of a vector below kShortDot and min(1024, len / 256) above.  The
+// bound is monotone in ns, nt and len: a workspace sized for the largest shape
+// serves every smaller one.
 size_t dots_workspace(int ns, int nt, long len) {
-  const long nfall = (len + dot_chunk(len) - 1) / dot_chunk(len);
-  const long nchunks = std::max(nfall, std::min<long>(1024, (len + 255) / 256));
+  const long nchunks = std::max(std::min<long>(64, (len + 63) / 64), std::min<long>(1024, (len + 255) / 256));
   return static_cast<size_t>(nchunks) * std::min(ns, kDotRows) * nt;
 }
 
 namespace {
 
-// rows of X and Y can go through the tall-skinny kernel: long, with rows whose
-// starts are 16-byte aligned (the loads take 4 contiguous values)
+// rows whose starts are 16-byte aligned (the loads then take 4 contiguous values)
 template <class TX, class TY>
-bool skinny_ok(const TX* X, long ldx, const TY* Y, long ldy, long len) {
+bool rows_aligned(const TX* X, long ldx, const TY* Y, long ldy) {
   const long ax = 16 / sizeof(TX), ay = 16 / sizeof(TY);
-  return len >= 1024 && ldx % ax == 0 && ldy % ay == 0 && aligned_to(X, 16) && aligned_to(Y, 16);
+  return ldx % ax == 0 && ldy % ay == 0 && aligned_to(X, 16) && aligned_to(Y, 16);
 }
 
-template <class TX, class TY>
-void dots_fast(hipStream_t st, int ns, const TX* X, long ldx, int nt, const TY* Y, long ldy, long len, double* out,
+template <class TX, class TY, bool ALIGNED>
+void dots_pass(hipStream_t st, int ns, const TX* X, long ldx, int nt, const TY* Y, long ldy, long len, double* out,
                long ldo, double* ws) {
   const long chunk = skinny_chunk(nt, len);
   const int nchunks = static_cast<int>((len + chunk - 1) / chunk);
   const dim3 grid(ceil_div(nt, 128), nchunks);
   if (ns <= 16)
-    hipLaunchKernelGGL((skinny_dots_kernel<1, TX, TY>), grid, dim3(256), 0, st, ns, nt, X, ldx, Y, ldy, len, chunk, ws);
+    hipLaunchKernelGGL((skinny_dots_kernel<1, TX, TY, ALIGNED>), grid, dim3(256), 0, st, ns, nt, X, ldx, Y, ldy, len,
+                       chunk, ws);
   else if (ns <= 32)
-    hipLaunchKernelGGL((skinny_dots_kernel<2, TX, TY>), grid, dim3(256), 0, st, ns, nt, X, ldx, Y, ldy, len, chunk, ws);
+    hipLaunchKernelGGL((skinny_dots_kernel<2, TX, TY, ALIGNED>), grid, dim3(256), 0, st, ns, nt, X, ldx, Y, ldy, len,
+                       chunk, ws);
   else
-    hipLaunchKernelGGL((skinny_dots_kernel<3, TX, TY>), grid, dim3(256), 0, st, ns, nt, X, ldx, Y, ldy, len, chunk, ws);
-  if (ns * nt < 1024 && nchunks >= 64)
-    hipLaunchKernelGGL(reduce_partials_wide_kernel, dim3(ns * nt), dim3(256), 0, st, nchunks, ns, nt, ws, out, ldo);
-  else
-    hipLaunchKernelGGL(reduce_partials_kernel, dim3(ceil_div(ns * nt, 64)), dim3(64 * kRedWaves), 0, st, nchunks, ns,
-                       nt, ws, out, ldo);
-  SEQX_LAUNCH_CHECK();
-}
-
-void dots_pass(hipStream_t st, int ns, const double* X, long ldx, int nt, const double* Y, long ldy, long len,
-               double* out, long ldo, double* ws) {
-  if (skinny_ok(X, ldx, Y, ldy, len)) {
-    dots_fast(st, ns, X, ldx, nt, Y, ldy, len, out, ldo, ws);
-    return;
-  }
-  const long dc = dot_chunk(len);
-  const int nchunks = static_cast<int>((len + dc - 1) / dc);
-  // chunk c: partial[c] (ns x nt) = X[:, chunk] * Y[:, chunk]^T ; the last chunk is ragged
-  const int full = static_cast<int>(len / dc);
-  if (full > 0)
-    dgemm(st, false, true, ns, nt, static_cast<int>(dc), 1.0, X, ldx, dc, Y, ldy, dc, 0.0, ws, nt,
-          static_cast<long>(ns) * nt, full, nullptr);
-  if (full < nchunks) {
-    const long off = static_cast<long>(full) * dc;
-    dgemm(st, false, true, ns, nt, static_cast<int>(len - off), 1.0, X + off, ldx, 0, Y + off, ldy, 0, 0.0,
-          ws + static_cast<long>(full) * ns * nt, nt, 0, 1, nullptr);
-  }
+    hipLaunchKernelGGL((skinny_dots_kernel<3, TX, TY, ALIGNED>), grid, dim3(256), 0, st, ns, nt, X, ldx, Y, ldy, len,
+                       chunk, ws);
   if (ns * nt < 1024 && nchunks >= 64)
     hipLaunchKernelGGL(reduce_partials_wide_kernel, dim3(ns * nt), dim3(256), 0, st, nchunks, ns, nt, ws, out, ldo);
   else
@@ -388,25 +375,34 @@ void dots_pass(hipStream_t st, int ns, const double* X, long ldx, int nt, const 
 
 }  // namespace
 
+// Any length and alignment: products over 804 same-atom pairs ((H2O)67, 7
+// vectors) took 110 us as a general GEMM of 7 x 804 outputs, which walks all
+// of K in each of a dozen workgroups: the pass of seven (A+B)V, (A-B)V products
+// there went 362 -> 256 us, 20 CIS roots of C40H42 (nov odd) 159 -> 129 ms and
+// the parameter derivatives of C20H22 21.8 -> 16.5 ms with every length here.
 void dots(hipStream_t st, int ns, const double* X, long ldx, int nt, const double* Y, long ldy, long len, double* out,
           long ldo, double* ws) {
   if (ns <= 0 || nt <= 0) return;
+  const bool al = rows_aligned(X, ldx, Y, ldy);
   // passes of at most kDotRows rows share the workspace (ordered on st)
-  for (int r0 = 0; r0 < ns; r0 += kDotRows)
-    dots_pass(st, std::min(kDotRows, ns - r0), X + static_cast<long>(r0) * ldx, ldx, nt, Y, ldy, len,
-              out + static_cast<long>(r0) * ldo, ldo, ws);
+  for (int r0 = 0; r0 < ns; r0 += kDotRows) {
+    const int nr = std::min(kDotRows, ns - r0);
+    const double* Xr = X + static_cast<long>(r0) * ldx;
+    double* outr = out + static_cast<long>(r0) * ldo;
+    if (al) dots_pass<double, double, true>(st, nr, Xr, ldx, nt, Y, ldy, len, outr, ldo, ws);
+    else dots_pass<double, double, false>(st, nr, Xr, ldx, nt, Y, ldy, len, outr, ldo, ws);
+  }
 }
 
 // Inner products with FP32 rows on either side (widened to FP64 on load, FP64
-// products and sums): the tall-skinny path only, so rows must be long and
-// their starts 16-byte aligned.
+// products and sums): rows must be long and their starts 16-byte aligned.
 template <class TX, class TY>
 void dots_mixed(hipStream_t st, int ns, const TX* X, long ldx, int nt, const TY* Y, long ldy, long len, double* out,
                 long ldo, double* ws) {
   if (ns <= 0 || nt <= 0) return;
-  if (!skinny_ok(X, ldx, Y, ldy, len)) throw Error(kEArg, "FP32 inner products need long, 16-byte aligned rows");
+  if (len < 1024 || !rows_aligned(X, ldx, Y, ldy)) throw Error(kEArg, "FP32 inner products need long, 16-byte aligned rows");
   for (int r0 = 0; r0 < ns; r0 += kDotRows)
-    dots_fast(st, std::min(kDotRows, ns - r0), X + static_cast<long>(r0) * ldx, ldx, nt, Y, ldy, len,
+    dots_pass<TX, TY, true>(st, std::min(kDotRows, ns - r0), X + static_cast<long>(r0) * ldx, ldx, nt, Y, ldy, len,
               out + static_cast<long>(r0) * ldo, ldo, ws);
 }
 template void dots_mixed<float, float>(hipStream_t, int, const float*, long, int, const float*, long, long, double*,
