@@ -61,8 +61,9 @@ typedef enum { SEQX_CIS = 0, SEQX_TDHF = 1 } seqx_theory;
 
 /* Arithmetic of the dense MO<->AO transforms inside the sigma build.  Subspace
  * projection, Gram-Schmidt, the small eigensolves and the SCF stay FP64.
- * SEQX_FP32: C, V and the AO matrices stored in FP32, transforms on the FP32
- * matrix cores with FP32 accumulation; the NDDO contraction sums in FP64 and
+ * SEQX_FP32: C, V and the AO matrices hold FP32 values, transforms with FP32
+ * accumulation (on the FP32 matrix cores, or, from 96 AOs on, as products of
+ * exact three-way bfloat16 splits of the FP32 values); the NDDO contraction sums in FP64 and
  * the (eps_a - eps_i) V term is added in FP64 (mixed-precision mode of the
  * paper's outlook).  A seqx_solve in FP32 restarts from its Ritz vectors with
  * FP64 products once its residuals reach max(tol, the FP32 rounding floor) or
@@ -285,8 +286,9 @@ seqx_status seqx_sigma_device(seqx_job* job, int32_t mol, int32_t theory, int32_
  * outputs as for seqx_sigma_device, ordered on the context stream.
  * Limit: one vector's intermediates must fit the workspace: for n AOs,
  * v virtual MOs and np same-atom AO pairs about 8 (3 n^2 + 3 n v) + 24 np
- * bytes for TDHF in FP64 (CIS: 8 (2 n^2 + 2 n v) + 24 np) and half of the
- * matrix terms in FP32, so a 1980-AO molecule still runs one vector per pass
+ * bytes for TDHF in FP64 (CIS: 8 (2 n^2 + 2 n v) + 24 np) and at most half of
+ * the matrix terms in FP32 (plane form while it fits, FP32 matrices beyond),
+ * so a 1980-AO molecule still runs one vector per pass
  * in FP64.  Beyond it the call returns SEQX_E_BUFSIZE and writes nothing.  Every call on one GPU shares that GPU's
  * workspace, which keeps the last call's contents (every element is written
  * before it is read): calls that overlap in time on one GPU, from any

@@ -157,8 +157,8 @@ __device__ void sigma_item(const MolDesc& md, const T* __restrict__ C, const dou
   __syncthreads();
   // F = 2 J(R) - K(R): atom-diagonal blocks, then every atom pair (both orders)
   for (int A = threadIdx.x; A < md.natoms; A += blockDim.x)
-    diag_block<kSum, T, T>(md.elems[md.slot[A]], md.ao_off[A], md.pi_off[A], js, 1, R, n, F, static_cast<T*>(nullptr),
-                           2.0, -1.0, -1.0);
+    diag_block<kSum, T>(md.elems[md.slot[A]], md.ao_off[A], md.pi_off[A], js, 1, R, n, MatOut<T>{F, 0, n},
+                        MatOut<T>{nullptr, 0, n}, 2.0, -1.0, -1.0);
   for (int p = threadIdx.x; p < md.npairs[0]; p += blockDim.x)
     exchange_pair<4, 4, kSum, T, T>(md.pairs[0][p].x, md.pairs[0][p].y, md.ao_off, md.pi_off, md.W, np, R, n, F,
                                     static_cast<T*>(nullptr), -1.0, -1.0);

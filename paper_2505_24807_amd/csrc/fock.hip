@@ -9,6 +9,8 @@
 // The paper contracts the exchange twice, with the symmetrised and the
 // antisymmetrised density; here both come out of one pass over each tile of
 // atom pairs.
+#include <type_traits>
+
 #include "fock.hpp"
 #include "gemm.hpp"
 
@@ -40,14 +42,15 @@ __global__ void pack_kernel(int k, int np, int n, const int* __restrict__ pi_mu,
 // (the atom-diagonal blocks belong to diag_block_kernel).
 constexpr int kXT = 32;  // tile edge in AOs
 
-template <int NA, int NB, int MODE, class TR, class TF>
+template <int NA, int NB, int MODE, class TR, class Out>
 __global__ void __launch_bounds__(256) exchange_tile_kernel(int k, int row_at0, int nrow_at, int col_at0,
                                                             int ncol_at, int same, const int* __restrict__ ao_off,
                                                             const int* __restrict__ pi_off,
                                                             const double* __restrict__ W, int ldw,
-                                                            const TR* __restrict__ R, long sR, int n,
-                                                            TF* __restrict__ F1, TF* __restrict__ F2, long sF,
+                                                            const TR* __restrict__ R, long sR, int n, Out F1, Out F2,
                                                             double cK, double cKa) {
+  typedef typename Out::stage_t TF;
+  constexpr bool kPlanes = !std::is_same<Out, MatOut<TF>>::value;
   constexpr int TA = kXT / NA, TB = kXT / NB;    // atoms per tile edge
   constexpr int NPA = NA == 4 ? 10 : 1, NPB = NB == 4 ? 10 : 1;
   constexpr int UPT = TA * TB * NA / 256;         // work units per thread
@@ -114,8 +117,7 @@ __global__ void __launch_bounds__(256) exchange_tile_kernel(int k, int row_at0, 
     }
     __syncthreads();
     fetch(min(I + 1, k - 1));
-    TF* f1 = F1 + static_cast<long>(I) * sF;
-    TF* f2 = MODE == kTwo ? F2 + static_cast<long>(I) * sF : nullptr;
+    const Out f1 = F1.at(I), f2 = F2.at(I);
 #pragma unroll
     for (int j = 0; j < UPT; ++j) {
       if (!uon[j]) continue;
@@ -138,82 +140,111 @@ __global__ void __launch_bounds__(256) exchange_tile_kernel(int k, int row_at0, 
             kd[nu] += wv * (x1 - x2);
           }
       const long rowA = ra + al + mu;
+      float q1[4], q2[4];  // plane rows take four columns at a time
 #pragma unroll
       for (int nu = 0; nu < NB; ++nu) {
         const double s = 0.5 * ks[nu], d = 0.5 * kd[nu];
-        const long ab = rowA * n + rb + bl + nu;
-        TF vba1, vba2 = TF(0);
+        const int colB = rb + bl + nu;
+        TF vab1, vab2 = TF(0), vba1, vba2 = TF(0);
         if (MODE == kTwo) {
-          f1[ab] = static_cast<TF>(cK * s);
-          f2[ab] = static_cast<TF>(cKa * d);
-          vba1 = static_cast<TF>(cK * s);
+          vab1 = vba1 = static_cast<TF>(cK * s);
+          vab2 = static_cast<TF>(cKa * d);
           vba2 = static_cast<TF>(-cKa * d);
         } else if (MODE == kSum) {
-          f1[ab] = static_cast<TF>(cK * s + cKa * d);
+          vab1 = static_cast<TF>(cK * s + cKa * d);
           vba1 = static_cast<TF>(cK * s - cKa * d);
         } else {
-          f1[ab] = static_cast<TF>(cK * s);
-          vba1 = static_cast<TF>(cK * s);
+          vab1 = vba1 = static_cast<TF>(cK * s);
+        }
+        if constexpr (kPlanes && NB == 4) {
+          q1[nu] = vab1;
+          q2[nu] = vab2;
+        } else {
+          f1.put(rowA, colB, vab1);
+          if (MODE == kTwo) f2.put(rowA, colB, vab2);
         }
         if (diag) {
-          const long ba = static_cast<long>(rb + bl + nu) * n + rowA;
-          f1[ba] = vba1;
-          if (MODE == kTwo) f2[ba] = vba2;
+          f1.put(colB, static_cast<int>(rowA), vba1);
+          if (MODE == kTwo) f2.put(colB, static_cast<int>(rowA), vba2);
         } else {
           Sba1[bl + nu][al + mu] = vba1;
           if (MODE == kTwo) Sba2[bl + nu][al + mu] = vba2;
         }
       }
+      if constexpr (kPlanes && NB == 4) {
+        f1.put4(rowA, rb + bl, q1);
+        if (MODE == kTwo) f2.put4(rowA, rb + bl, q2);
+      }
     }
     __syncthreads();
     if (!diag) {
+      if constexpr (kPlanes) {
+        // four consecutive columns per thread (tile columns start at a multiple of 4)
+        const int r = tid / 8, c = (tid % 8) * 4;
+        if (r < nrb && c + 3 < nra) {
+          f1.put4(rb + r, ra + c, &Sba1[r][c]);
+          if (MODE == kTwo) f2.put4(rb + r, ra + c, &Sba2[r][c]);
+        } else if (r < nrb) {
+          for (int e = c; e < nra; ++e) {
+            f1.put(rb + r, ra + e, Sba1[r][e]);
+            if (MODE == kTwo) f2.put(rb + r, ra + e, Sba2[r][e]);
+          }
+        }
+      } else {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int idx = tid + 256 * e, r = idx / kXT, c = idx % kXT;
-        if (r < nrb && c < nra) {
-          const long ba = static_cast<long>(rb + r) * n + ra + c;
-          f1[ba] = Sba1[r][c];
-          if (MODE == kTwo) f2[ba] = Sba2[r][c];
+        for (int e = 0; e < 4; ++e) {
+          const int idx = tid + 256 * e, r = idx / kXT, c = idx % kXT;
+          if (r < nrb && c < nra) {
+            f1.put(rb + r, ra + c, Sba1[r][c]);
+            if (MODE == kTwo) f2.put(rb + r, ra + c, Sba2[r][c]);
+          }
         }
       }
     }
   }
 }
 
-template <int MODE, class TR, class TF>
+template <int MODE, class TR, class Out>
 __global__ void diag_block_kernel(int natoms, int np, const int* __restrict__ slot, const int* __restrict__ ao_off,
                                   const int* __restrict__ pi_off, const Elem* __restrict__ elems,
-                                  const double* __restrict__ J, const TR* __restrict__ R, long sR, int n,
-                                  TF* __restrict__ F1, TF* __restrict__ F2, long sF, double cJ, double cK,
-                                  double cKa) {
+                                  const double* __restrict__ J, const TR* __restrict__ R, long sR, int n, Out F1,
+                                  Out F2, double cJ, double cK, double cKa) {
   const int A = blockIdx.x * blockDim.x + threadIdx.x;
   const int I = blockIdx.y;
   if (A >= natoms) return;
   const Elem e = elems[slot[A]];
   // J is stored [k][np]: vector I's Coulomb values are contiguous
-  diag_block<MODE, TR, TF>(e, ao_off[A], pi_off[A], J + static_cast<long>(I) * np, 1, R + I * sR, n, F1 + I * sF,
-                           MODE == kTwo ? F2 + I * sF : nullptr, cJ, cK, cKa);
+  diag_block<MODE, TR>(e, ao_off[A], pi_off[A], J + static_cast<long>(I) * np, 1, R + I * sR, n, F1.at(I), F2.at(I),
+                       cJ, cK, cKa);
 }
 
-template <int MODE, class TR, class TF>
-void launch_pairs(const DeviceMolecule& m, int k, const TR* R, long sR, TF* F1, TF* F2, long sF, double cK, double cKa,
-                  hipStream_t st) {
+template <int MODE, class TR, class Out>
+void launch_pairs(const DeviceMolecule& m, int k, const TR* R, long sR, const Out& F1, const Out& F2, double cK,
+                  double cKa, hipStream_t st) {
   const int n = m.nao, nh = m.nheavy, nl = m.natoms - m.nheavy;
   const int th = static_cast<int>(ceil_div(nh, kXT / 4)), tl = static_cast<int>(ceil_div(nl, kXT));
   if (nh > 1)
-    hipLaunchKernelGGL((exchange_tile_kernel<4, 4, MODE, TR, TF>), dim3(th * (th + 1) / 2), dim3(256), 0, st, k, 0, nh,
-                       0, nh, 1, m.ao_off.p, m.pi_off.p, m.W.p, m.np, R, sR, n, F1, F2, sF, cK, cKa);
+    hipLaunchKernelGGL((exchange_tile_kernel<4, 4, MODE, TR, Out>), dim3(th * (th + 1) / 2), dim3(256), 0, st, k, 0, nh,
+                       0, nh, 1, m.ao_off.p, m.pi_off.p, m.W.p, m.np, R, sR, n, F1, F2, cK, cKa);
   if (nh > 0 && nl > 0)
-    hipLaunchKernelGGL((exchange_tile_kernel<4, 1, MODE, TR, TF>), dim3(th * tl), dim3(256), 0, st, k, 0, nh, nh, nl, 0,
-                       m.ao_off.p, m.pi_off.p, m.W.p, m.np, R, sR, n, F1, F2, sF, cK, cKa);
+    hipLaunchKernelGGL((exchange_tile_kernel<4, 1, MODE, TR, Out>), dim3(th * tl), dim3(256), 0, st, k, 0, nh, nh, nl, 0,
+                       m.ao_off.p, m.pi_off.p, m.W.p, m.np, R, sR, n, F1, F2, cK, cKa);
   if (nl > 1)
-    hipLaunchKernelGGL((exchange_tile_kernel<1, 1, MODE, TR, TF>), dim3(tl * (tl + 1) / 2), dim3(256), 0, st, k, nh,
-                       nl, nh, nl, 1, m.ao_off.p, m.pi_off.p, m.W.p, m.np, R, sR, n, F1, F2, sF, cK, cKa);
+    hipLaunchKernelGGL((exchange_tile_kernel<1, 1, MODE, TR, Out>), dim3(tl * (tl + 1) / 2), dim3(256), 0, st, k, nh,
+                       nl, nh, nl, 1, m.ao_off.p, m.pi_off.p, m.W.p, m.np, R, sR, n, F1, F2, cK, cKa);
 }
 
-template <class TR, class TF>
-void build_G_any(const DeviceMolecule& m, int k, const TR* R, long sR, TF* F1, TF* F2, long sF, GMode mode, double cJ,
-                 double cK, double cKa, double* r, double* J, double* ws, hipStream_t st) {
+template <int MODE, class TR, class Out>
+void build_G_mode(const DeviceMolecule& m, int k, const TR* R, long sR, const Out& F1, const Out& F2, double cJ,
+                  double cK, double cKa, const double* J, hipStream_t st) {
+  hipLaunchKernelGGL((diag_block_kernel<MODE, TR, Out>), dim3(ceil_div(m.natoms, 64), k), dim3(64), 0, st, m.natoms,
+                     m.np, m.slot.p, m.ao_off.p, m.pi_off.p, m.elems, J, R, sR, m.nao, F1, F2, cJ, cK, cKa);
+  launch_pairs<MODE>(m, k, R, sR, F1, F2, cK, cKa, st);
+}
+
+template <class TR, class Out>
+void build_G_any(const DeviceMolecule& m, int k, const TR* R, long sR, const Out& F1, const Out& F2, GMode mode,
+                 double cJ, double cK, double cKa, double* r, double* J, double* ws, hipStream_t st) {
   const int np = m.np, n = m.nao;
   if (k <= 0) return;
   hipLaunchKernelGGL(pack_kernel<TR>, dim3(ceil_div(np, 256), k), dim3(256), 0, st, k, np, n, m.pi_mu.p, m.pi_nu.p, R,
@@ -223,20 +254,9 @@ void build_G_any(const DeviceMolecule& m, int k, const TR* R, long sR, TF* F1, T
   // handful of vectors still spreads over hundreds of workgroups; FP64 whatever
   // the storage type of R and F
   dots(st, k, r, np, np, m.W.p, np, np, J, np, ws);
-  const dim3 dgrid(ceil_div(m.natoms, 64), k);
-  if (mode == kTwo) {
-    hipLaunchKernelGGL((diag_block_kernel<kTwo, TR, TF>), dgrid, dim3(64), 0, st, m.natoms, np, m.slot.p, m.ao_off.p,
-                       m.pi_off.p, m.elems, J, R, sR, n, F1, F2, sF, cJ, cK, cKa);
-    launch_pairs<kTwo>(m, k, R, sR, F1, F2, sF, cK, cKa, st);
-  } else if (mode == kSum) {
-    hipLaunchKernelGGL((diag_block_kernel<kSum, TR, TF>), dgrid, dim3(64), 0, st, m.natoms, np, m.slot.p, m.ao_off.p,
-                       m.pi_off.p, m.elems, J, R, sR, n, F1, F2, sF, cJ, cK, cKa);
-    launch_pairs<kSum>(m, k, R, sR, F1, F2, sF, cK, cKa, st);
-  } else {
-    hipLaunchKernelGGL((diag_block_kernel<kSymm, TR, TF>), dgrid, dim3(64), 0, st, m.natoms, np, m.slot.p, m.ao_off.p,
-                       m.pi_off.p, m.elems, J, R, sR, n, F1, F2, sF, cJ, cK, cKa);
-    launch_pairs<kSymm>(m, k, R, sR, F1, F2, sF, cK, cKa, st);
-  }
+  if (mode == kTwo) build_G_mode<kTwo>(m, k, R, sR, F1, F2, cJ, cK, cKa, J, st);
+  else if (mode == kSum) build_G_mode<kSum>(m, k, R, sR, F1, F2, cJ, cK, cKa, J, st);
+  else build_G_mode<kSymm>(m, k, R, sR, F1, F2, cJ, cK, cKa, J, st);
   SEQX_LAUNCH_CHECK();
 }
 
@@ -248,7 +268,8 @@ void build_G_owned(const DeviceMolecule& m, int k, const TR* R, long sR, TF* F1,
   w.r.ensure(static_cast<size_t>(k) * np);
   w.J.ensure(static_cast<size_t>(k) * np);
   w.ws.ensure(dots_workspace(k, np, np));
-  build_G_any<TR, TF>(m, k, R, sR, F1, F2, sF, mode, cJ, cK, cKa, w.r.p, w.J.p, w.ws.p, st);
+  build_G_any(m, k, R, sR, MatOut<TF>{F1, sF, m.nao}, MatOut<TF>{F2, sF, m.nao}, mode, cJ, cK, cKa, w.r.p, w.J.p,
+              w.ws.p, st);
 }
 
 }  // namespace
@@ -267,12 +288,24 @@ void build_G(const DeviceMolecule& m, int k, const float* R, long sR, float* F1,
 
 void build_G(const DeviceMolecule& m, int k, const double* R, long sR, double* F1, double* F2, long sF, GMode mode,
              double cJ, double cK, double cKa, double* r, double* J, double* ws, hipStream_t st) {
-  build_G_any<double, double>(m, k, R, sR, F1, F2, sF, mode, cJ, cK, cKa, r, J, ws, st);
+  build_G_any(m, k, R, sR, MatOut<double>{F1, sF, m.nao}, MatOut<double>{F2, sF, m.nao}, mode, cJ, cK, cKa, r, J, ws,
+              st);
 }
 
 void build_G(const DeviceMolecule& m, int k, const float* R, long sR, float* F1, float* F2, long sF, GMode mode,
              double cJ, double cK, double cKa, double* r, double* J, double* ws, hipStream_t st) {
-  build_G_any<float, float>(m, k, R, sR, F1, F2, sF, mode, cJ, cK, cKa, r, J, ws, st);
+  build_G_any(m, k, R, sR, MatOut<float>{F1, sF, m.nao}, MatOut<float>{F2, sF, m.nao}, mode, cJ, cK, cKa, r, J, ws,
+              st);
+}
+
+void build_G_planes(const DeviceMolecule& m, int k, const float* R, long sR, int planes, plane_t* F1, plane_t* F2,
+                    long sF, GMode mode, double cJ, double cK, double cKa, double* r, double* J, double* ws,
+                    hipStream_t st) {
+  const long ld = plane_row(m.nao, planes);
+  if (planes == 3)
+    build_G_any(m, k, R, sR, PlaneOut<3>{F1, sF, ld}, PlaneOut<3>{F2, sF, ld}, mode, cJ, cK, cKa, r, J, ws, st);
+  else
+    build_G_any(m, k, R, sR, PlaneOut<2>{F1, sF, ld}, PlaneOut<2>{F2, sF, ld}, mode, cJ, cK, cKa, r, J, ws, st);
 }
 
 }  // namespace seqx

@@ -37,4 +37,10 @@ void build_G(const DeviceMolecule& m, int k, const double* R, long sR, double* F
 void build_G(const DeviceMolecule& m, int k, const float* R, long sR, float* F1, float* F2, long sF, GMode mode,
              double cJ, double cK, double cKa, double* r, double* J, double* ws, hipStream_t st);
 
+// FP32 R, outputs as bfloat16 plane rows (planes.hpp; sF elements between the
+// matrices of a stack): the operand form of the back-transform.
+void build_G_planes(const DeviceMolecule& m, int k, const float* R, long sR, int planes, plane_t* F1, plane_t* F2,
+                    long sF, GMode mode, double cJ, double cK, double cKa, double* r, double* J, double* ws,
+                    hipStream_t st);
+
 }  // namespace seqx

@@ -3,6 +3,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "planes.hpp"
 
 namespace seqx {
 
@@ -95,10 +96,10 @@ __device__ inline double h1(const Elem& e, int m, int n) { return (m == 0 || n =
 
 // Diagonal block of atom A: Coulomb J (J[P * jstride] for the atom's pair
 // indices P) plus the one-centre exchange of the symmetric and antisymmetric parts.
-template <int MODE, class TR, class TF>
+template <int MODE, class TR, class Out>
 __device__ __forceinline__ void diag_block(const Elem& e, int o, int po, const double* __restrict__ J, long jstride,
-                                           const TR* __restrict__ Rv, int n, TF* __restrict__ f1,
-                                           TF* __restrict__ f2, double cJ, double cK, double cKa) {
+                                           const TR* __restrict__ Rv, int n, const Out& f1,
+                                           const Out& f2, double cJ, double cK, double cKa) {
   const int na = e.nao;
   double X[4][4];  // statically indexed (unrolled, predicated) so that it stays in registers
 #pragma unroll
@@ -128,14 +129,13 @@ __device__ __forceinline__ void diag_block(const Elem& e, int o, int po, const d
           kD = (g1(e, m, nn) - h1(e, m, nn)) * Dv;
         }
         const double jv = J[static_cast<long>(po + (na == 1 ? 0 : pair_index(m, nn))) * jstride];
-        const long idx = static_cast<long>(o + m) * n + o + nn;
         if (MODE == kTwo) {
-          f1[idx] = static_cast<TF>(cJ * jv + cK * kS);
-          f2[idx] = static_cast<TF>(cKa * kD);
+          f1.put(o + m, o + nn, cJ * jv + cK * kS);
+          f2.put(o + m, o + nn, cKa * kD);
         } else if (MODE == kSum) {
-          f1[idx] = static_cast<TF>(cJ * jv + cK * kS + cKa * kD);
+          f1.put(o + m, o + nn, cJ * jv + cK * kS + cKa * kD);
         } else {
-          f1[idx] = static_cast<TF>(cJ * jv + cK * kS);
+          f1.put(o + m, o + nn, cJ * jv + cK * kS);
         }
       }
     }

@@ -6,6 +6,11 @@
 
 namespace seqx {
 
+// From this many AOs on the low-precision transforms run on bfloat16 planes;
+// below, one 64 x 64 tile or less covers a matrix and the FP32 matrix cores
+// need no splitting passes.
+constexpr int kPlaneMinAo = 96;
+
 struct DeviceMolecule {
   Layout L;
   int natoms = 0, nheavy = 0, nao = 0, nocc = 0, nvirt = 0, np = 0;
@@ -21,6 +26,9 @@ struct DeviceMolecule {
   DBuf<double> H;               // core Hamiltonian [nao][nao]
   DBuf<double> C;               // MO coefficients, row-major [nao][nao]: C[mu][p]
   DBuf<float> C32;              // C rounded to FP32 (mixed-precision transforms)
+  // the FP32 coefficients as bfloat16 plane rows (planes.hpp), from
+  // kPlaneMinAo AOs on: C_occ and C_virt by AO, and transposed by MO
+  DBuf<unsigned short> Cop, Cvp, CoTp, CvTp;
   DBuf<double> eps;             // orbital energies [nao]
   DBuf<double> P;               // density [nao][nao]
   double commutator = 0.0;

@@ -13,6 +13,7 @@
 #include <algorithm>
 
 #include "gemm.hpp"
+#include "planes.hpp"
 #include "scf.hpp"
 
 namespace seqx {
@@ -356,6 +357,17 @@ void run_scf(DeviceMolecule& m, const ScfOptions& opt, DenseSolver& ds, GWork& g
   m.C32.ensure(nn);
   to_float(st, nn, m.C.p, m.C32.p);
   density_from_CT(st, n, o, w.CT.p, m.P.p);
+  if (n >= kPlaneMinAo) {
+    const int v = n - o;
+    m.Cop.ensure(static_cast<size_t>(n) * plane_row(o, 3));
+    m.Cvp.ensure(static_cast<size_t>(n) * plane_row(v, 3));
+    m.CoTp.ensure(static_cast<size_t>(o) * plane_row(n, 3));
+    m.CvTp.ensure(static_cast<size_t>(v) * plane_row(n, 3));
+    split_rows(st, n, o, m.C32.p, n, m.Cop.p);
+    split_rows(st, n, v, m.C32.p + o, n, m.Cvp.p);
+    split_transposed<float>(st, 3, 1, n, o, m.C32.p, n, 0, m.CoTp.p);
+    split_transposed<float>(st, 3, 1, n, v, m.C32.p + o, n, 0, m.CvTp.p);
+  }
 }
 
 }  // namespace seqx

@@ -10,6 +10,7 @@
 
 #include "gemm.hpp"
 #include "linalg.hpp"
+#include "planes.hpp"
 #include "sigma.hpp"
 
 namespace seqx {
@@ -59,11 +60,13 @@ void forward_transform(const DeviceMolecule& m, int k, const double* X, double* 
 
 namespace {
 
-// Intermediates of one chunk of kc trial vectors: the FP64 set (T1, R, F, Z)
-// or the FP32 set (V32, T1s, Rs, Fs, Zs), and the contraction's work arrays.
+// Intermediates of one chunk of kc trial vectors: the FP64 set (T1, R, F, Z),
+// the FP32 set (V32, T1s, Rs, Fs, Zs) or the plane set (Vp, T1p, Rs, Fp, Zp),
+// and the contraction's work arrays.
 struct ChunkBufs {
   double *T1 = nullptr, *R = nullptr, *F = nullptr, *Z = nullptr;
   float *V32 = nullptr, *T1s = nullptr, *Rs = nullptr, *Fs = nullptr, *Zs = nullptr;
+  plane_t *Vp = nullptr, *T1p = nullptr, *Fp = nullptr, *Zp = nullptr;
   double *gr = nullptr, *gJ = nullptr, *gws = nullptr;
 };
 
@@ -124,11 +127,51 @@ void sigma_chunk(const DeviceMolecule& m, int theory, int kc, const double* Vc, 
       dgemm(st, true, false, o, v, n, 1.0, m.C.p, n, 0, b.Z, v, nv, 0.0, out1c, v, os, kc, &ep);
       if (tdhf) dgemm(st, true, false, o, v, n, 1.0, m.C.p, n, 0, b.Z + kc * nv, v, nv, 0.0, out2c, v, os, kc, &ep);
     }
+  } else if (b.Vp) {
+    // bfloat16 planes: every operand with its summation index along the rows,
+    // so V enters transposed and Z is formed transposed
+    const int np = precision == kPrecBF16x3 ? 2 : 3;
+    const long rn = plane_row(n, np), rv = plane_row(v, np), ro = plane_row(o, np);
+    if (io) {
+      ep.V = nullptr;
+      ep.Vf = io->V;
+      split_transposed<float>(st, np, kc, o, v, io->V, v, ov, b.Vp);
+    } else {
+      split_transposed<double>(st, np, kc, o, v, Vc, v, ov, b.Vp);
+    }
+    // T1_I (n x v) = C_o V_I
+    plane_gemm_planes(st, {np, kc, v, n, o, b.Vp, m.Cop.p, v * ro, 0}, b.T1p, n * rv);
+    mark(1);
+    // R_I (n x n) = T1_I C_v^T over the stacked rows of T1
+    plane_gemm_f32(st, {np, 1, n, kc * n, v, m.Cvp.p, b.T1p, 0, 0}, b.Rs, n);
+    mark(2);
+    const long mat = n * rn, sP = merged ? 2 * mat : mat;
+    plane_t* F2 = b.Fp + (merged ? mat : kc * mat);
+    if (tdhf)
+      build_G_planes(m, kc, b.Rs, nn, np, b.Fp, F2, sP, kTwo, 4.0, -2.0, -2.0, b.gr, b.gJ, b.gws, st);
+    else
+      build_G_planes(m, kc, b.Rs, nn, np, b.Fp, b.Fp, sP, kSum, 2.0, -1.0, -1.0, b.gr, b.gJ, b.gws, st);
+    mark(3);
+    // Z_b^T (v x n) = C_v^T F_b^T
+    const long zt = v * rn;
+    plane_gemm_planes(st, {np, nb, n, v, n, b.Fp, m.CvTp.p, mat, 0}, b.Zp, zt);
+    mark(4);
+    // out_b (o x v) = C_o^T Z_b + de o V_b
+    auto back = [&](int nz, const plane_t* Z, auto* out, long stride) {
+      plane_gemm_sigma(st, {np, nz, v, o, n, Z, m.CoTp.p, zt, 0}, out, v, stride, ep);
+    };
+    auto finish = [&](auto* o1, auto* o2) {
+      if (merged) {
+        back(nb, b.Zp, o1, os / 2);
+      } else {
+        back(kc, b.Zp, o1, os);
+        if (tdhf) back(kc, b.Zp + kc * zt, o2, os);
+      }
+    };
+    if (io) finish(io->out1, io->out2);
+    else finish(out1c, out2c);
   } else {
-    // FP32 storage; products on the FP32 matrix cores or as split bfloat16 (BF16x3)
-    const bool x3 = precision == kPrecBF16x3;
-    auto mm = x3 ? sgemm3 : sgemm;
-    auto mm64 = x3 ? sgemm3_out64 : sgemm_out64;
+    // FP32 storage, products on the FP32 matrix cores
     const float* C32 = m.C32.p;
     const float* Vs = b.V32;
     if (io) {
@@ -138,29 +181,29 @@ void sigma_chunk(const DeviceMolecule& m, int theory, int kc, const double* Vc, 
     } else {
       to_float(st, kc * ov, Vc, b.V32);
     }
-    mm(st, false, false, n, v, o, 1.0, C32, n, 0, Vs, v, ov, 0.0, b.T1s, v, nv, kc, nullptr);
+    sgemm(st, false, false, n, v, o, 1.0, C32, n, 0, Vs, v, ov, 0.0, b.T1s, v, nv, kc, nullptr);
     mark(1);
-    mm(st, false, true, kc * n, n, v, 1.0, b.T1s, v, 0, C32 + o, n, 0, 0.0, b.Rs, n, 0, 1, nullptr);
+    sgemm(st, false, true, kc * n, n, v, 1.0, b.T1s, v, 0, C32 + o, n, 0, 0.0, b.Rs, n, 0, 1, nullptr);
     mark(2);
     if (tdhf)
       build_G(m, kc, b.Rs, nn, b.Fs, b.Fs + f2off, sF, kTwo, 4.0, -2.0, -2.0, b.gr, b.gJ, b.gws, st);
     else
       build_G(m, kc, b.Rs, nn, b.Fs, static_cast<float*>(nullptr), nn, kSum, 2.0, -1.0, -1.0, b.gr, b.gJ, b.gws, st);
     mark(3);
-    mm(st, false, false, nb * n, v, n, 1.0, b.Fs, n, 0, C32 + o, n, 0, 0.0, b.Zs, v, 0, 1, nullptr);
+    sgemm(st, false, false, nb * n, v, n, 1.0, b.Fs, n, 0, C32 + o, n, 0, 0.0, b.Zs, v, 0, 1, nullptr);
     mark(4);
     if (io) {
       if (merged) {
-        mm(st, true, false, o, v, n, 1.0, C32, n, 0, b.Zs, v, nv, 0.0, io->out1, v, os / 2, nb, &ep);
+        sgemm(st, true, false, o, v, n, 1.0, C32, n, 0, b.Zs, v, nv, 0.0, io->out1, v, os / 2, nb, &ep);
       } else {
-        mm(st, true, false, o, v, n, 1.0, C32, n, 0, b.Zs, v, nv, 0.0, io->out1, v, os, kc, &ep);
-        if (tdhf) mm(st, true, false, o, v, n, 1.0, C32, n, 0, b.Zs + kc * nv, v, nv, 0.0, io->out2, v, os, kc, &ep);
+        sgemm(st, true, false, o, v, n, 1.0, C32, n, 0, b.Zs, v, nv, 0.0, io->out1, v, os, kc, &ep);
+        if (tdhf) sgemm(st, true, false, o, v, n, 1.0, C32, n, 0, b.Zs + kc * nv, v, nv, 0.0, io->out2, v, os, kc, &ep);
       }
     } else if (merged) {
-      mm64(st, true, false, o, v, n, 1.0, C32, n, 0, b.Zs, v, nv, 0.0, out1c, v, os / 2, nb, &ep);
+      sgemm_out64(st, true, false, o, v, n, 1.0, C32, n, 0, b.Zs, v, nv, 0.0, out1c, v, os / 2, nb, &ep);
     } else {
-      mm64(st, true, false, o, v, n, 1.0, C32, n, 0, b.Zs, v, nv, 0.0, out1c, v, os, kc, &ep);
-      if (tdhf) mm64(st, true, false, o, v, n, 1.0, C32, n, 0, b.Zs + kc * nv, v, nv, 0.0, out2c, v, os, kc, &ep);
+      sgemm_out64(st, true, false, o, v, n, 1.0, C32, n, 0, b.Zs, v, nv, 0.0, out1c, v, os, kc, &ep);
+      if (tdhf) sgemm_out64(st, true, false, o, v, n, 1.0, C32, n, 0, b.Zs + kc * nv, v, nv, 0.0, out2c, v, os, kc, &ep);
     }
   }
   mark(5);
@@ -173,10 +216,14 @@ void check_sigma_args(const DeviceMolecule& m, int precision) {
     throw Error(kEState, "FP32 MO coefficients missing");
 }
 
+bool has_planes(const DeviceMolecule& m, int precision) { return precision != kPrecFP64 && m.Cop.n > 0; }
+
 // Pieces of one chunk's intermediates laid out in a single workspace, each
 // starting on a 256-byte boundary; returns the bytes used.  base == nullptr
-// only measures.
-size_t carve_chunk(const DeviceMolecule& m, int theory, int kc, int precision, unsigned char* base, ChunkBufs* b) {
+// only measures.  planes: the plane set instead of the FP32 set; Z then takes
+// the place of R, which the contraction has consumed.
+size_t carve_chunk(const DeviceMolecule& m, int theory, int kc, int precision, bool planes, unsigned char* base,
+                   ChunkBufs* b) {
   const size_t n = m.nao, v = m.nvirt, ov = static_cast<size_t>(m.nocc) * m.nvirt;
   const size_t nn = n * n, nv = n * v, nb = theory == 1 ? 2 * static_cast<size_t>(kc) : kc;
   size_t off = 0;
@@ -191,6 +238,15 @@ size_t carve_chunk(const DeviceMolecule& m, int theory, int kc, int precision, u
     c.R = reinterpret_cast<double*>(take(kc * nn * sizeof(double)));
     c.F = reinterpret_cast<double*>(take(nb * nn * sizeof(double)));
     c.Z = reinterpret_cast<double*>(take(nb * nv * sizeof(double)));
+  } else if (planes) {
+    const int np = precision == kPrecBF16x3 ? 2 : 3;
+    const size_t rn = plane_row(m.nao, np), rv = plane_row(m.nvirt, np), ro = plane_row(m.nocc, np);
+    c.Vp = reinterpret_cast<plane_t*>(take(kc * v * ro * sizeof(plane_t)));
+    c.T1p = reinterpret_cast<plane_t*>(take(kc * n * rv * sizeof(plane_t)));
+    unsigned char* rz = take(std::max(kc * nn * sizeof(float), nb * v * rn * sizeof(plane_t)));
+    c.Rs = reinterpret_cast<float*>(rz);
+    c.Zp = reinterpret_cast<plane_t*>(rz);
+    c.Fp = reinterpret_cast<plane_t*>(take(nb * n * rn * sizeof(plane_t)));
   } else {
     c.V32 = reinterpret_cast<float*>(take(kc * ov * sizeof(float)));
     c.T1s = reinterpret_cast<float*>(take(kc * nv * sizeof(float)));
@@ -256,16 +312,9 @@ void sigma_build_any(const DeviceMolecule& m, int theory, int k, const double* V
     const int nb = tdhf ? 2 * kc : kc;
     ChunkBufs b;
     if (precision != kPrecFP64) {
-      w.V32.ensure(static_cast<size_t>(kc) * ov);
-      w.Rs.ensure(static_cast<size_t>(kc) * nn);
-      w.Fs.ensure(static_cast<size_t>(nb) * nn);
-      w.Zs.ensure(static_cast<size_t>(nb) * nv);
-      w.T1s.ensure(static_cast<size_t>(kc) * nv);
-      b.V32 = w.V32.p;
-      b.Rs = w.Rs.p;
-      b.Fs = w.Fs.p;
-      b.Zs = w.Zs.p;
-      b.T1s = w.T1s.p;
+      const bool planes = has_planes(m, precision);
+      w.low.ensure(carve_chunk(m, theory, kc, precision, planes, nullptr, nullptr));
+      carve_chunk(m, theory, kc, precision, planes, w.low.p, &b);
     } else {
       w.R.ensure(static_cast<size_t>(kc) * nn);
       w.F.ensure(static_cast<size_t>(nb) * nn);
@@ -275,13 +324,13 @@ void sigma_build_any(const DeviceMolecule& m, int theory, int k, const double* V
       b.F = w.F.p;
       b.Z = w.Z.p;
       b.T1 = w.T1.p;
+      w.g.r.ensure(static_cast<size_t>(kc) * m.np);
+      w.g.J.ensure(static_cast<size_t>(kc) * m.np);
+      w.g.ws.ensure(dots_workspace(kc, m.np, m.np));
+      b.gr = w.g.r.p;
+      b.gJ = w.g.J.p;
+      b.gws = w.g.ws.p;
     }
-    w.g.r.ensure(static_cast<size_t>(kc) * m.np);
-    w.g.J.ensure(static_cast<size_t>(kc) * m.np);
-    w.g.ws.ensure(dots_workspace(kc, m.np, m.np));
-    b.gr = w.g.r.p;
-    b.gJ = w.g.J.p;
-    b.gws = w.g.ws.p;
     std::array<hipEvent_t, kNumPhases + 1> ev;
     for (auto& e : ev) SEQX_HIP(hipEventCreate(&e));
     bool merged;
@@ -344,11 +393,14 @@ void sigma_scratch_setup(int device) {
   g_scratch_ptr[device] = p;
 }
 
-int sigma_scratch_max_chunk(const DeviceMolecule& m, int theory, int precision) {
+namespace {
+// vectors per pass that fit the workspace (0: not even one)
+int scratch_chunk(const DeviceMolecule& m, int theory, int precision, bool planes) {
   int kc = 32;
-  while (kc > 0 && carve_chunk(m, theory, kc, precision, nullptr, nullptr) > kSigmaScratchBytes) --kc;
+  while (kc > 0 && carve_chunk(m, theory, kc, precision, planes, nullptr, nullptr) > kSigmaScratchBytes) --kc;
   return kc;
 }
+}  // namespace
 
 void sigma_build_noalloc(const DeviceMolecule& m, int theory, int k, const double* V, double* out1, double* out2,
                          hipStream_t st, int precision) {
@@ -365,17 +417,24 @@ void sigma_build_noalloc(const DeviceMolecule& m, int theory, int k, const doubl
     std::lock_guard<std::mutex> lock(g_scratch_mu);
     base = g_scratch_ptr[device];
   }
-  const int chunk = sigma_scratch_max_chunk(m, theory, precision);
+  // the plane set where one vector of it fits; the FP32 set is smaller and
+  // reaches up to about 2800 AOs
+  bool planes = has_planes(m, precision);
+  int chunk = scratch_chunk(m, theory, precision, planes);
+  if (chunk < 1 && planes) {
+    planes = false;
+    chunk = scratch_chunk(m, theory, precision, false);
+  }
   if (chunk < 1)
     throw Error(kEBufSize, "one trial vector needs " +
-                               std::to_string(carve_chunk(m, theory, 1, precision, nullptr, nullptr)) +
+                               std::to_string(carve_chunk(m, theory, 1, precision, planes, nullptr, nullptr)) +
                                " bytes of intermediates; the fixed workspace holds " +
                                std::to_string(kSigmaScratchBytes));
   const long ov = static_cast<long>(m.nocc) * m.nvirt;
   for (int c0 = 0; c0 < k; c0 += chunk) {
     const int kc = std::min(chunk, k - c0);
     ChunkBufs b;
-    carve_chunk(m, theory, kc, precision, static_cast<unsigned char*>(base), &b);
+    carve_chunk(m, theory, kc, precision, planes, static_cast<unsigned char*>(base), &b);
     sigma_chunk(m, theory, kc, V + c0 * ov, out1 + c0 * ov, out2 ? out2 + c0 * ov : nullptr, ov, precision, b, st,
                 nullptr);
   }

@@ -31,7 +31,7 @@ enum SigmaPrecision { kPrecFP64 = 0, kPrecFP32 = 1, kPrecBF16 = 2, kPrecBF16x3 =
 
 struct SigmaWork {
   DBuf<double> T1, R, F, Z;
-  DBuf<float> V32, T1s, Rs, Fs, Zs;  // FP32 storage of the mixed-precision path
+  DBuf<unsigned char> low;  // intermediates of the low-precision transforms
   GWork g;
   PhaseTimer timer;
 };
@@ -43,12 +43,13 @@ struct SigmaWork {
 // C_occ^T G C_virt + (eps_a - eps_i) V_I.  Works in chunks of at most
 // `chunk` vectors (memory cap).  out_stride: distance (doubles) between the
 // outputs of consecutive vectors (0: nocc*nvirt, i.e. contiguous).
-// precision kPrecBF16x3: the same FP32 storage, with the four transforms as
-// split-bfloat16 products on the bfloat16 matrix cores (sgemm3).
-// precision kPrecFP32: V, C, R, F and the transform intermediates are stored in
-// FP32 and the four transforms run on the FP32 matrix cores; the NDDO
-// contraction still multiplies and adds in FP64 and the (eps_a - eps_i) V term
-// is added in FP64 to the FP64 output.
+// precision kPrecFP32: V, C, R, F and the transform intermediates hold FP32
+// values.  From kPlaneMinAo AOs on they are kept as three bfloat16 planes
+// (planes.hpp), which represent them exactly, and the four transforms are
+// products of the planes with FP32 accumulation, at least as accurate as the
+// FP32 matrix cores; smaller molecules use those.  kPrecBF16x3: two planes
+// (split bfloat16).  Either way the NDDO contraction multiplies and adds in
+// FP64 and the (eps_a - eps_i) V term is added in FP64.
 void sigma_build(const DeviceMolecule& m, int theory, int k, const double* V, double* out1, double* out2,
                  SigmaWork& w, hipStream_t st, int chunk = 32, long out_stride = 0, int precision = kPrecFP64);
 
@@ -66,8 +67,6 @@ constexpr size_t kSigmaScratchBytes = static_cast<size_t>(128) << 20;
 // Device address of the workspace on `device` (the current device), looked up
 // once per device; called from context creation.
 void sigma_scratch_setup(int device);
-// Vectors per pass that fit the workspace (0: not even one).
-int sigma_scratch_max_chunk(const DeviceMolecule& m, int theory, int precision);
 void sigma_build_noalloc(const DeviceMolecule& m, int theory, int k, const double* V, double* out1, double* out2,
                          hipStream_t st, int precision);
 

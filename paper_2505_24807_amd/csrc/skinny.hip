@@ -316,10 +316,10 @@ __global__ void __launch_bounds__(256) skinny_dots_kernel(int ns, int nt, const 
 }  // namespace
 
 // Chunk length: about 1024 workgroups for long vectors, at least 256 values.
-// Vectors below 4096 values take chunks of 64 (4 MFMA blocks a wavefront): one
+// Vectors below 1024 values take chunks of 64 (4 MFMA blocks a wavefront): one
 // molecule of 30-90 AOs gives only a handful of 128-row groups, and the short
 // chunks keep the serial part near a microsecond.
-constexpr long kShortDot = 4096;
+constexpr long kShortDot = 1024;
 long skinny_chunk(int nt, long len) {
   const long groups = (nt + 127) / 128;
   const long want = std::max<long>(1, 1024 / groups);
@@ -333,11 +333,11 @@ long skinny_chunk(int nt, long len) {
 constexpr int kDotRows = 48;
 
 // Partial sums of one pass of at most kDotRows rows: whatever nt is, at most
-// 64 chunks of a vector below kShortDot and min(1024, len / 256) above.  The
+// 16 chunks of a vector below kShortDot and min(1024, len / 256) above.  The
 // bound is monotone in ns, nt and len: a workspace sized for the largest shape
 // serves every smaller one.
 size_t dots_workspace(int ns, int nt, long len) {
-  const long nchunks = std::max(std::min<long>(64, (len + 63) / 64), std::min<long>(1024, (len + 255) / 256));
+  const long nchunks = std::max(std::min<long>(16, (len + 63) / 64), std::min<long>(1024, (len + 255) / 256));
   return static_cast<size_t>(nchunks) * std::min(ns, kDotRows) * nt;
 }
 

@@ -67,3 +67,27 @@ def test_roots_of_odd_rows(ctx, n_carbon, theory):
     ref = excited.cis_dense(A, 4, o, v) if theory == seqx.CIS else excited.tdhf_dense(A, B, 4, o, v)
     assert np.abs(job.results().omega_eV - ref.omega * model.HARTREE_EV).max() <= 1e-8
     job.free()
+
+
+# 92 AOs (FP32 matrix cores), 96 and 102 (smallest plane transforms; o = v = 51 leaves remainders of every tile and
+# block), 402 with 32 vectors (large tiles, 96 wide on the side that pads less), 7 and 1
+@pytest.mark.parametrize("mol, k", [(_noisy(molecules.polyene(18), 18), 3), (molecules.water_cluster(16, 16), 3),
+                                    (_noisy(molecules.polyene(20), 20), 5), (molecules.water_cluster(67, 67), 32),
+                                    (molecules.water_cluster(67, 67), 7), (molecules.water_cluster(67, 67), 1)],
+                         ids=lambda x: getattr(x, "name", str(x)))
+@pytest.mark.parametrize("theory", [seqx.CIS, seqx.TDHF])
+def test_low_precision_products(ctx, mol, k, theory):
+    """FP32 and split-bfloat16 products against the library's FP64 ones: each element of the two-electron part within
+    8 n u of its largest one (four chained sums of at most n terms), u = 2^-24 for FP32 and 3 * 2^-16 for the split."""
+    print(f"[gpu] low-precision products {mol.name} k={k} theory={theory}", flush=True)
+    job = ctx.prepare([mol.natoms], mol.Z, mol.xyz)
+    n, o, v = job.dims()
+    eps = job.scf_results()[0] / model.HARTREE_EV
+    V = np.random.default_rng(2).normal(size=(k, o, v))
+    diag = (eps[None, o:] - eps[:o, None]) * V
+    ref = [x for x in job.sigma(V, theory=theory) if x is not None]
+    for precision, u in ((seqx.FP32, 2.0 ** -24), (seqx.BF16X3, 3 * 2.0 ** -16)):
+        got = [x for x in job.sigma(V, theory=theory, precision=precision) if x is not None]
+        for a, b in zip(got, ref):
+            assert np.abs(a - b).max() <= 8 * n * u * np.abs(b - diag).max()
+    job.free()
