@@ -60,12 +60,12 @@ void DenseSolver::eigh(int n, double* A, int lda, double* w) {
 void DenseSolver::eigh_lowest(int n, double* A, int lda, int k, double* w) {
   if (n <= 0 || k <= 0) return;
   k = std::min(k, n);
-  if (n <= kJacobiMax || n > kSmallDense) {
+  if (n <= kJacobiMax || n > kEigMax) {
     eigh(n, A, lda, w);
     return;
   }
-  small_.ensure(small_syevx_scratch(n, k));
-  launch_small_syevx(st_, n, A, lda, k, w, small_.p, info_.p);
+  small_.ensure(eig_lowest_scratch(n, k));
+  launch_eig_lowest(st_, n, A, lda, k, w, small_.p, info_.p);
 }
 
 void DenseSolver::potrf(int n, double* A, int lda) {

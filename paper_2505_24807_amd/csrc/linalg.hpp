@@ -8,12 +8,18 @@
 
 namespace seqx {
 
-constexpr int kSmallDense = 256;  // largest n of the one-workgroup dense kernels
+constexpr int kSmallDense = 256;  // largest n of the one-workgroup Cholesky kernel
+constexpr int kEigMax = 512;      // largest n of the k-lowest eigensolver
+// largest n whose reduction stays in one workgroup: a step there costs 1.2 us at
+// n = 64, 2.0 at 128 and 3.5 at 192 (instructions of 8 wavefronts on one compute
+// unit) against 2.8-2.9 across compute units
+constexpr int kEigOneGroup = 128;
 
-// one-workgroup kernels (small_dense.hip): k lowest eigenpairs (A's columns
-// 0..k-1 and w), lower Cholesky; scratch holds small_syevx_scratch(n, k) doubles
-size_t small_syevx_scratch(int n, int k);
-void launch_small_syevx(hipStream_t st, int n, double* A, int lda, int k, double* w, double* scratch, int* info);
+// k lowest eigenpairs, 2 <= n <= kEigMax (eig_lowest.hip): A's columns 0..k-1
+// and w; reads the lower triangle.  scratch holds eig_lowest_scratch(n, k) doubles.
+size_t eig_lowest_scratch(int n, int k);
+void launch_eig_lowest(hipStream_t st, int n, double* A, int lda, int k, double* w, double* scratch, int* info);
+// lower Cholesky in one workgroup (small_dense.hip)
 void launch_small_potrf(hipStream_t st, int n, double* A, int lda, int* info);
 
 // Dense symmetric eigensolver / Cholesky on the device (rocSOLVER), FP64,
@@ -27,9 +33,8 @@ class DenseSolver {
   // eigenvalues ascending into w[n]; eigenvectors overwrite A (columns)
   void eigh(int n, double* A, int lda, double* w);
   // the k lowest eigenpairs only: w[0..k), eigenvectors in columns 0..k-1 of A
-  // (the rest of A is overwritten).  n <= kSmallDense runs as one workgroup
-  // (Householder tridiagonalisation, Sturm bisection, inverse iteration,
-  // back-transformation); larger n uses eigh.  Reads the lower triangle.
+  // (the rest of A is overwritten).  n <= kEigMax runs on the kernels of
+  // eig_lowest.hip; larger n uses eigh.  Reads the lower triangle.
   void eigh_lowest(int n, double* A, int lda, int k, double* w);
   // lower Cholesky factor in place (upper triangle untouched); info reports
   // the first non-positive pivot.  n <= kSmallDense runs as one workgroup.

@@ -91,3 +91,24 @@ def test_low_precision_products(ctx, mol, k, theory):
         for a, b in zip(got, ref):
             assert np.abs(a - b).max() <= 8 * n * u * np.abs(b - diag).max()
     job.free()
+
+
+# subspaces that pass the edges of the eigensolver (49, 64, 65, 128, 129, 192, 256, 257, 384, 512 rows): the cap holds
+# the basis at that size, a few roots fill it
+@pytest.mark.parametrize("cap", [49, 64, 65, 129, 193, 257, 385, 512])
+def test_subspace_sizes(ctx, cap):
+    """CIS roots from subspaces of up to `cap` vectors against dense diagonalisation (C20H22, 2601 pairs)."""
+    mol = _noisy(molecules.polyene(20), 21)
+    print(f"[gpu] subspace cap {cap}", flush=True)
+    job = ctx.prepare([mol.natoms], mol.Z, mol.xyz)
+    n, o, v = job.dims()
+    k = max(5, cap // 20)
+    job.solve(theory=seqx.CIS, nroots=k, tol=1e-8, max_iter=300, max_subspace=cap)
+    sy = model.make_system(mol.Z, mol.xyz, PR)
+    ints = integrals.build(sy)
+    res = scf.run(sy, ints)
+    A, _ = excited.build_AB(ints, res.eps, res.C, o)
+    ref = excited.cis_dense(A, k, o, v)
+    assert np.abs(job.results().omega_eV - ref.omega * model.HARTREE_EV).max() <= 1e-8
+    assert job.stats().max_subspace_used <= cap
+    job.free()
