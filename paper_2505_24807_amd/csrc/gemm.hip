@@ -121,39 +121,40 @@ __global__ void __launch_bounds__(256) gemm_kernel(int M, int N, int K, double a
       }
 }
 
-// ---------------------------------------------------------------- 128 x 128 tiles
-// For the dense transforms: each of the four wavefronts owns a 64 x 64
-// quadrant (4 x 4 MFMA tiles); loads of element pairs.  The K panels are
+// ---------------------------------------------------------------- large tiles
+// For the dense transforms: BM x BN tiles, each of the four wavefronts owns a
+// BM / 2 x BN / 2 quadrant (64 x 64 of a 128 x 128 tile: 4 x 4 MFMA tiles);
+// loads of element pairs.  The K panels are
 // double-buffered in LDS: the loads of a later panel are issued (and kept
 // ahead of the MFMAs by a scheduling barrier) before the MFMAs of the current
 // one and land in the other LDS buffer afterwards, so one barrier per panel
 // suffices.  Both precisions prefetch two panels ahead with two register sets
 // and use buffer loads on interior tiles; FP32 also issues its LDS operand
 // reads one k-step ahead of the MFMAs.  Interior and edge tiles take separate code
-// paths.  Needs even leading dimensions and batch strides and pair-aligned
-// base pointers (checked by the dispatcher).  Panel depth: 16 (FP64) or 32
+// paths.  Pair loads are buffer loads, which need element-aligned (dword)
+// addresses only, so any leading dimension will do.  Every tile size sums an
+// element in the same order: the size never changes a result.  Panel depth: 16 (FP64) or 32
 // (FP32), which keeps the loads of one panel at 16 registers per lane either
 // way.
-constexpr int kBM = 128, kBN = 128, kPad = 2;
+constexpr int kPad = 2;
 
 template <class T>
 struct Panel {
   static constexpr int BK = sizeof(T) == 8 ? 16 : 32;
-  static constexpr int NP = kBM * BK / 2 / 256;  // element pairs of A per thread
 };
-// element pairs of B per thread for a tile BN columns wide
-template <class T, int BN>
-constexpr int kNPB = BN * Panel<T>::BK / 2 / 256;
+// element pairs per thread of a panel W rows (A) or columns (B) wide
+template <class T, int W>
+constexpr int kPairs = W * Panel<T>::BK / 2 / 256;
 
 // Edge tiles and the K head panel: element loads at clamped indices, so every
 // load is issued unconditionally (which keeps the wait counters exact).  Rows
 // past M and columns past N only feed outputs that are never stored, so their
 // clamped values are harmless; columns k >= K are set to zero.
-template <class T, bool TA, bool TB, int BN>
+template <class T, bool TA, bool TB, int BM, int BN>
 __device__ __forceinline__ void panel_load_edge(const T* __restrict__ A, long lda, const T* __restrict__ B, long ldb,
                                                 int M, int N, int K, int m0, int n0, int k0, int tid,
                                                 typename Mfma<T>::pair_t* ra, typename Mfma<T>::pair_t* rb) {
-  constexpr int BK = Panel<T>::BK, HK = BK / 2, HM = kBM / 2, HN = BN / 2;
+  constexpr int BK = Panel<T>::BK, HK = BK / 2, HM = BM / 2, HN = BN / 2;
   auto ld_a = [&](int gi, int gk) {
     const T v = TA ? A[static_cast<long>(min(gk, K - 1)) * lda + min(gi, M - 1)]
                    : A[static_cast<long>(min(gi, M - 1)) * lda + min(gk, K - 1)];
@@ -165,7 +166,7 @@ __device__ __forceinline__ void panel_load_edge(const T* __restrict__ A, long ld
     return gk < K ? v : T(0);
   };
 #pragma unroll
-  for (int j = 0; j < Panel<T>::NP; ++j) {
+  for (int j = 0; j < kPairs<T, BM>; ++j) {
     const int c = tid + 256 * j;
     if (!TA) {
       const int gi = m0 + c / HK, gk = k0 + (c % HK) * 2;
@@ -178,7 +179,7 @@ __device__ __forceinline__ void panel_load_edge(const T* __restrict__ A, long ld
     }
   }
 #pragma unroll
-  for (int j = 0; j < kNPB<T, BN>; ++j) {
+  for (int j = 0; j < kPairs<T, BN>; ++j) {
     const int c = tid + 256 * j;
     if (!TB) {
       const int gk = k0 + c / HN, gj = n0 + (c % HN) * 2;
@@ -212,22 +213,22 @@ __device__ __forceinline__ d2 buffer_pair<double>(__amdgpu_buffer_rsrc_t r, unsi
   return __builtin_bit_cast(d2, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
 }
 
-template <class T, int BN>
+template <class T, int BM, int BN>
 __device__ __forceinline__ void panel_load_fast(__amdgpu_buffer_rsrc_t ar, unsigned asoff, __amdgpu_buffer_rsrc_t br,
                                                 unsigned bsoff, const unsigned* oa, const unsigned* ob,
                                                 typename Mfma<T>::pair_t* ra, typename Mfma<T>::pair_t* rb) {
 #pragma unroll
-  for (int j = 0; j < Panel<T>::NP; ++j) ra[j] = buffer_pair<T>(ar, oa[j], asoff);
+  for (int j = 0; j < kPairs<T, BM>; ++j) ra[j] = buffer_pair<T>(ar, oa[j], asoff);
 #pragma unroll
-  for (int j = 0; j < kNPB<T, BN>; ++j) rb[j] = buffer_pair<T>(br, ob[j], bsoff);
+  for (int j = 0; j < kPairs<T, BN>; ++j) rb[j] = buffer_pair<T>(br, ob[j], bsoff);
 }
 
-template <class T, bool TA, bool TB, int BN>
-__device__ __forceinline__ void panel_store(T (*As)[kBM + kPad], T (*Bs)[BN + kPad], int tid,
+template <class T, bool TA, bool TB, int BM, int BN>
+__device__ __forceinline__ void panel_store(T (*As)[BM + kPad], T (*Bs)[BN + kPad], int tid,
                                             const typename Mfma<T>::pair_t* ra, const typename Mfma<T>::pair_t* rb) {
-  constexpr int BK = Panel<T>::BK, HK = BK / 2, HM = kBM / 2, HN = BN / 2;
+  constexpr int BK = Panel<T>::BK, HK = BK / 2, HM = BM / 2, HN = BN / 2;
 #pragma unroll
-  for (int j = 0; j < Panel<T>::NP; ++j) {
+  for (int j = 0; j < kPairs<T, BM>; ++j) {
     const int c = tid + 256 * j;
     if (!TA) {
       const int i = c / HK, kk = (c % HK) * 2;
@@ -240,7 +241,7 @@ __device__ __forceinline__ void panel_store(T (*As)[kBM + kPad], T (*Bs)[BN + kP
     }
   }
 #pragma unroll
-  for (int j = 0; j < kNPB<T, BN>; ++j) {
+  for (int j = 0; j < kPairs<T, BN>; ++j) {
     const int c = tid + 256 * j;
     if (!TB) {
       const int kk = c / HN, jj = (c % HN) * 2;
@@ -258,29 +259,29 @@ __device__ __forceinline__ void panel_store(T (*As)[kBM + kPad], T (*Bs)[BN + kP
 // step s are issued, so the LDS latency overlaps the matrix-core work.  FP64
 // keeps one operand set: its accumulators take twice the registers, and a
 // second set would cost a wavefront per SIMD.
-template <class T, int TN>
-__device__ __forceinline__ void panel_mfma(const T (*As)[kBM + kPad], const T (*Bs)[TN * 32 + kPad], int lane, int wm,
+template <class T, int TM, int TN>
+__device__ __forceinline__ void panel_mfma(const T (*As)[TM * 32 + kPad], const T (*Bs)[TN * 32 + kPad], int lane, int wm,
                                            int wn, typename Mfma<T>::acc_t (*acc)[TN]) {
   constexpr int NS = Panel<T>::BK / 4;
   if constexpr (sizeof(T) == 8) {  // FP64: one operand set, order left to the compiler
 #pragma unroll
     for (int ks = 0; ks < Panel<T>::BK; ks += 4) {
-      T a[4], bb[TN];
+      T a[TM], bb[TN];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[ks + (lane >> 4)][wm + i * 16 + (lane & 15)];
+      for (int i = 0; i < TM; ++i) a[i] = As[ks + (lane >> 4)][wm + i * 16 + (lane & 15)];
 #pragma unroll
       for (int j = 0; j < TN; ++j) bb[j] = Bs[ks + (lane >> 4)][wn + j * 16 + (lane & 15)];
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = Mfma<T>::op(a[i], bb[j], acc[i][j]);
     }
     return;
   }
-  T a[2][4], bb[2][TN];
+  T a[2][TM], bb[2][TN];
   auto read = [&](int ks, T* ar, T* br) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) ar[i] = As[ks + (lane >> 4)][wm + i * 16 + (lane & 15)];
+    for (int i = 0; i < TM; ++i) ar[i] = As[ks + (lane >> 4)][wm + i * 16 + (lane & 15)];
 #pragma unroll
     for (int j = 0; j < TN; ++j) br[j] = Bs[ks + (lane >> 4)][wn + j * 16 + (lane & 15)];
   };
@@ -289,38 +290,36 @@ __device__ __forceinline__ void panel_mfma(const T (*As)[kBM + kPad], const T (*
   for (int s = 0; s < NS; ++s) {
     if (s + 1 < NS) read(4 * (s + 1), a[(s + 1) & 1], bb[(s + 1) & 1]);
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j) acc[i][j] = Mfma<T>::op(a[s & 1][i], bb[s & 1][j], acc[i][j]);
   }
   // schedule: the LDS reads of step 0, then per step the reads of step s + 1
   // ahead of the 4 TN MFMAs of step s (masks: 0x100 LDS read, 0x008 MFMA)
-  __builtin_amdgcn_sched_group_barrier(0x100, 4 + TN, 0);
+  __builtin_amdgcn_sched_group_barrier(0x100, TM + TN, 0);
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
-    if (s + 1 < NS) __builtin_amdgcn_sched_group_barrier(0x100, 4 + TN, 0);
-    __builtin_amdgcn_sched_group_barrier(0x008, 4 * TN, 0);
+    if (s + 1 < NS) __builtin_amdgcn_sched_group_barrier(0x100, TM + TN, 0);
+    __builtin_amdgcn_sched_group_barrier(0x008, TM * TN, 0);
   }
 }
 
 // EM: 0 interior tile; 1 edge tile whose pair dimensions (M when A is
 // transposed, N when B is not) are even, loaded like an interior tile at
 // clamped offsets; 2 other edge tiles, element loads.
-// BN: tile width, 128 or 96 (each wavefront then owns 64 x BN / 2, TN = BN / 32
-// MFMA tiles across).
-template <class T, class To, bool TA, bool TB, bool EPI, int EM, int BN>
-__device__ __forceinline__ void tile128(int M, int N, int K, double alpha, const T* __restrict__ A, long lda,
+template <class T, class To, bool TA, bool TB, bool EPI, int EM, int BM, int BN>
+__device__ __forceinline__ void tile_product(int M, int N, int K, double alpha, const T* __restrict__ A, long lda,
                                         const T* __restrict__ B, long ldb, double beta, To* __restrict__ C, long ldc,
-                                        long b, const SigmaEpilogue& ep, int m0, int n0, T (*As)[kBM + kPad],
+                                        long b, const SigmaEpilogue& ep, int m0, int n0, T (*As)[BM + kPad],
                                         T (*Bs)[BN + kPad]) {
   typedef Mfma<T> MF;
-  constexpr int BK = Panel<T>::BK, TN = BN / 32, NPB = kNPB<T, BN>;
+  constexpr int BK = Panel<T>::BK, TM = BM / 32, TN = BN / 32, NPA = kPairs<T, BM>, NPB = kPairs<T, BN>;
   constexpr bool EDGE = EM != 0;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = (wave >> 1) * 64, wn = (wave & 1) * (BN / 2);
-  typename MF::acc_t acc[4][TN];
+  const int wm = (wave >> 1) * (BM / 2), wn = (wave & 1) * (BN / 2);
+  typename MF::acc_t acc[TM][TN];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = typename MF::acc_t{0, 0, 0, 0};
   typedef typename MF::pair_t P2;
@@ -333,18 +332,18 @@ __device__ __forceinline__ void tile128(int M, int N, int K, double alpha, const
     // stored to LDS.  The loads are unconditional (past the last panel they
     // repeat it and are not stored): a conditional load would make the wait
     // before the LDS stores cover the newest loads as well.
-    P2 ra0[Panel<T>::NP], rb0[NPB], ra1[Panel<T>::NP], rb1[NPB];
+    P2 ra0[kPairs<T, BM>], rb0[NPB], ra1[kPairs<T, BM>], rb1[NPB];
     const int kr = K % BK;
     const int npan = K / BK + (kr ? 1 : 0);
     const int kshift = kr ? kr - BK : 0;  // panel p >= 1 starts at p * BK + kshift
-    constexpr int HK = BK / 2, HM = kBM / 2, HN = BN / 2;
+    constexpr int HK = BK / 2, HM = BM / 2, HN = BN / 2;
     // Byte offsets inside a panel.  On edge tiles (EM == 1) rows and columns
     // past M and N are clamped to the last ones (pair starts to the last
     // pair): they only feed outputs that are not stored.
     const int im = M - 1 - m0, in = N - 1 - n0;  // last valid row / column of the tile
-    unsigned oa[Panel<T>::NP], ob[NPB];
+    unsigned oa[kPairs<T, BM>], ob[NPB];
 #pragma unroll
-    for (int j = 0; j < Panel<T>::NP; ++j) {
+    for (int j = 0; j < kPairs<T, BM>; ++j) {
       const int c = tid + 256 * j;
       int i = TA ? (c % HM) * 2 : c / HK, kk = TA ? c / HM : (c % HK) * 2;
       if (EM == 1) i = TA ? min(i, im - 1) : min(i, im);
@@ -362,34 +361,34 @@ __device__ __forceinline__ void tile128(int M, int N, int K, double alpha, const
     auto load_full = [&](int p, P2* ra, P2* rb) {
       const int k0 = p * BK + kshift;
       if (EM < 2)
-        panel_load_fast<T, BN>(ar, static_cast<unsigned>(TA ? k0 * lda : k0) * sizeof(T), br,
+        panel_load_fast<T, BM, BN>(ar, static_cast<unsigned>(TA ? k0 * lda : k0) * sizeof(T), br,
                                static_cast<unsigned>(TB ? k0 : k0 * ldb) * sizeof(T), oa, ob, ra, rb);
       else
-        panel_load_edge<T, TA, TB, BN>(A, lda, B, ldb, M, N, K, m0, n0, k0, tid, ra, rb);
+        panel_load_edge<T, TA, TB, BM, BN>(A, lda, B, ldb, M, N, K, m0, n0, k0, tid, ra, rb);
     };
     // LDS buffers 0 and 1: rows [0, BK) and [BK, 2 BK) of As / Bs
-    if (kr) panel_load_edge<T, TA, TB, BN>(A, lda, B, ldb, M, N, kr, m0, n0, 0, tid, ra0, rb0);
+    if (kr) panel_load_edge<T, TA, TB, BM, BN>(A, lda, B, ldb, M, N, kr, m0, n0, 0, tid, ra0, rb0);
     else load_full(0, ra0, rb0);
     load_full(min(1, npan - 1), ra1, rb1);
-    panel_store<T, TA, TB, BN>(As, Bs, tid, ra0, rb0);
+    panel_store<T, TA, TB, BM, BN>(As, Bs, tid, ra0, rb0);
     __syncthreads();
     int kt = 0;
     for (; kt + 1 < npan; kt += 2) {
       load_full(min(kt + 2, npan - 1), ra0, rb0);
       __builtin_amdgcn_sched_barrier(0);
-      panel_mfma<T, TN>(As, Bs, lane, wm, wn, acc);
-      panel_store<T, TA, TB, BN>(As + BK, Bs + BK, tid, ra1, rb1);
+      panel_mfma<T, TM, TN>(As, Bs, lane, wm, wn, acc);
+      panel_store<T, TA, TB, BM, BN>(As + BK, Bs + BK, tid, ra1, rb1);
       __syncthreads();
       load_full(min(kt + 3, npan - 1), ra1, rb1);
       __builtin_amdgcn_sched_barrier(0);
-      panel_mfma<T, TN>(As + BK, Bs + BK, lane, wm, wn, acc);
-      if (kt + 2 < npan) panel_store<T, TA, TB, BN>(As, Bs, tid, ra0, rb0);
+      panel_mfma<T, TM, TN>(As + BK, Bs + BK, lane, wm, wn, acc);
+      if (kt + 2 < npan) panel_store<T, TA, TB, BM, BN>(As, Bs, tid, ra0, rb0);
       __syncthreads();
     }
-    if (kt < npan) panel_mfma<T, TN>(As, Bs, lane, wm, wn, acc);  // odd panel count: the last one is in buffer 0
+    if (kt < npan) panel_mfma<T, TM, TN>(As, Bs, lane, wm, wn, acc);  // odd panel count: the last one is in buffer 0
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
@@ -400,13 +399,13 @@ __device__ __forceinline__ void tile128(int M, int N, int K, double alpha, const
       }
 }
 
-template <class T, class To, bool TA, bool TB, bool EPI, int BN>
-__global__ void __launch_bounds__(256) gemm128_kernel(int M, int N, int K, double alpha, const T* __restrict__ A,
+template <class T, class To, bool TA, bool TB, bool EPI, int BM, int BN>
+__global__ void __launch_bounds__(256) gemm_tile_kernel(int M, int N, int K, double alpha, const T* __restrict__ A,
                                                       long lda, long sA, const T* __restrict__ B, long ldb, long sB,
                                                       double beta, To* __restrict__ C, long ldc, long sC,
                                                       SigmaEpilogue ep) {
   constexpr int BK = Panel<T>::BK;
-  __shared__ T As[2 * BK][kBM + kPad];
+  __shared__ T As[2 * BK][BM + kPad];
   __shared__ T Bs[2 * BK][BN + kPad];
   const long b = blockIdx.z;
   // Workgroups go to the 8 XCDs round-robin by linear id, and each XCD has its
@@ -416,16 +415,15 @@ __global__ void __launch_bounds__(256) gemm128_kernel(int M, int N, int K, doubl
   const int nbx = gridDim.x, nb = gridDim.x * gridDim.y, nfull = nb - nb % 8;
   int bid = blockIdx.y * nbx + blockIdx.x;
   if (bid < nfull) bid = (bid % 8) * (nfull / 8) + bid / 8;
-  const int m0 = (bid / nbx) * kBM, n0 = (bid % nbx) * BN;
-  const bool keven = (K & 1) == 0;  // panels start at even k (pair loads)
-  if (m0 + kBM <= M && n0 + BN <= N && keven)
-    tile128<T, To, TA, TB, EPI, 0, BN>(M, N, K, alpha, A + b * sA, lda, B + b * sB, ldb, beta, C + b * sC, ldc, b, ep,
+  const int m0 = (bid / nbx) * BM, n0 = (bid % nbx) * BN;
+  if (m0 + BM <= M && n0 + BN <= N)
+    tile_product<T, To, TA, TB, EPI, 0, BM, BN>(M, N, K, alpha, A + b * sA, lda, B + b * sB, ldb, beta, C + b * sC, ldc, b, ep,
                                        m0, n0, As, Bs);
-  else if (keven && (!TA || (M & 1) == 0) && (TB || (N & 1) == 0))
-    tile128<T, To, TA, TB, EPI, 1, BN>(M, N, K, alpha, A + b * sA, lda, B + b * sB, ldb, beta, C + b * sC, ldc, b, ep,
+  else if ((!TA || (M & 1) == 0) && (TB || (N & 1) == 0))
+    tile_product<T, To, TA, TB, EPI, 1, BM, BN>(M, N, K, alpha, A + b * sA, lda, B + b * sB, ldb, beta, C + b * sC, ldc, b, ep,
                                        m0, n0, As, Bs);
   else
-    tile128<T, To, TA, TB, EPI, 2, BN>(M, N, K, alpha, A + b * sA, lda, B + b * sB, ldb, beta, C + b * sC, ldc, b, ep,
+    tile_product<T, To, TA, TB, EPI, 2, BM, BN>(M, N, K, alpha, A + b * sA, lda, B + b * sB, ldb, beta, C + b * sC, ldc, b, ep,
                                        m0, n0, As, Bs);
 }
 
@@ -443,31 +441,59 @@ __global__ void __launch_bounds__(256) gemm128_kernel(int M, int N, int K, doubl
                             alpha, A, lda, sA, B, ldb, sB, beta, C, ldc, sC, ep);                       \
   } while (0)
 
-template <class T, class To, bool EPI, int BN>
-void launch128(hipStream_t st, bool ta, bool tb, int M, int N, int K, double alpha, const T* A, long lda, long sA,
-               const T* B, long ldb, long sB, double beta, To* C, long ldc, long sC, int batch,
-               const SigmaEpilogue& ep) {
-  dim3 grid(ceil_div(N, BN), ceil_div(M, kBM), batch);
+template <class T, class To, bool EPI, int BM, int BN>
+void launch_tile(hipStream_t st, bool ta, bool tb, int M, int N, int K, double alpha, const T* A, long lda, long sA,
+                 const T* B, long ldb, long sB, double beta, To* C, long ldc, long sC, int batch,
+                 const SigmaEpilogue& ep) {
+  dim3 grid(ceil_div(N, BN), ceil_div(M, BM), batch);
   const dim3 blk(256);
   if (!ta && !tb)
-    hipLaunchKernelGGL((gemm128_kernel<T, To, false, false, EPI, BN>), grid, blk, 0, st, M, N, K, alpha, A, lda, sA, B,
-                       ldb, sB, beta, C, ldc, sC, ep);
+    hipLaunchKernelGGL((gemm_tile_kernel<T, To, false, false, EPI, BM, BN>), grid, blk, 0, st, M, N, K, alpha, A, lda,
+                       sA, B, ldb, sB, beta, C, ldc, sC, ep);
   else if (!ta && tb)
-    hipLaunchKernelGGL((gemm128_kernel<T, To, false, true, EPI, BN>), grid, blk, 0, st, M, N, K, alpha, A, lda, sA, B,
-                       ldb, sB, beta, C, ldc, sC, ep);
+    hipLaunchKernelGGL((gemm_tile_kernel<T, To, false, true, EPI, BM, BN>), grid, blk, 0, st, M, N, K, alpha, A, lda,
+                       sA, B, ldb, sB, beta, C, ldc, sC, ep);
   else if (ta && !tb)
-    hipLaunchKernelGGL((gemm128_kernel<T, To, true, false, EPI, BN>), grid, blk, 0, st, M, N, K, alpha, A, lda, sA, B,
-                       ldb, sB, beta, C, ldc, sC, ep);
+    hipLaunchKernelGGL((gemm_tile_kernel<T, To, true, false, EPI, BM, BN>), grid, blk, 0, st, M, N, K, alpha, A, lda,
+                       sA, B, ldb, sB, beta, C, ldc, sC, ep);
   else
-    hipLaunchKernelGGL((gemm128_kernel<T, To, true, true, EPI, BN>), grid, blk, 0, st, M, N, K, alpha, A, lda, sA, B,
-                       ldb, sB, beta, C, ldc, sC, ep);
+    hipLaunchKernelGGL((gemm_tile_kernel<T, To, true, true, EPI, BM, BN>), grid, blk, 0, st, M, N, K, alpha, A, lda,
+                       sA, B, ldb, sB, beta, C, ldc, sC, ep);
 }
 
-// Tile width of the 128-row tiles: 96 when it pads N by at least 3 % less
-// than 128 does (N = 660: 672 columns instead of 768).
-int tile_width(int N) {
-  const long w128 = static_cast<long>(ceil_div(N, 128)) * 128, w96 = static_cast<long>(ceil_div(N, 96)) * 96;
-  return 100 * w96 < 97 * w128 ? 96 : 128;
+// Tile size: 128 rows by 128 columns, or 96 where that pads N by at least 3 %
+// less (N = 660: 672 columns instead of 768), one workgroup per compute unit.
+// 64 x 64 tiles, four workgroups per compute unit, where the padding and the
+// last round of the large ones waste more than the small ones' lower rate (47
+// against 63 TFLOP/s): 10040 x 502 x 251 as 316 large tiles took 80 us.
+// 32 x 32 where even those leave compute units without work: one product of
+// 502 rows went 71 -> 13 us, the 20 products of C100H102 (odd row
+// lengths, formerly element loads in 64 x 64 tiles) 541 -> 346 us.
+constexpr long kComputeUnits = 256;
+
+template <class T, class To, bool EPI>
+void launch_tiles(hipStream_t st, bool ta, bool tb, int M, int N, int K, double alpha, const T* A, long lda, long sA,
+                  const T* B, long ldb, long sB, double beta, To* C, long ldc, long sC, int batch,
+                  const SigmaEpilogue& ep) {
+  auto padded = [](long x, long t) { return static_cast<double>(ceil_div(x, t) * t); };
+  auto groups = [&](long bm, long bn) { return static_cast<long>(ceil_div(M, bm) * ceil_div(N, bn)) * batch; };
+  const bool n96 = 100.0 * padded(N, 96) < 97.0 * padded(N, 128);
+  const long bn = n96 ? 96 : 128, large = groups(128, bn);
+  // share of the occupied compute-unit time that forms stored elements
+  const double work = static_cast<double>(M) * N;
+  const double use128 = work / (padded(M, 128) * padded(N, bn)) * large / padded(large, kComputeUnits);
+  const double use64 = work / (padded(M, 64) * padded(N, 64));
+#define SEQX_TILE(BM_, BN_)                                                                                        \
+  launch_tile<T, To, EPI, BM_, BN_>(st, ta, tb, M, N, K, alpha, A, lda, sA, B, ldb, sB, beta, C, ldc, sC, batch, ep)
+  if (large >= kComputeUnits && use128 >= 0.72 * use64) {
+    if (n96) SEQX_TILE(128, 96);
+    else SEQX_TILE(128, 128);
+  } else if (groups(64, 64) >= kComputeUnits) {
+    SEQX_TILE(64, 64);
+  } else {
+    SEQX_TILE(32, 32);
+  }
+#undef SEQX_TILE
 }
 
 template <class T, class To, int WM, int WN, int TM, int TN, bool EPI>
@@ -478,8 +504,6 @@ void launch_cfg(hipStream_t st, bool ta, bool tb, int M, int N, int K, double al
   dim3 grid(ceil_div(N, BN), ceil_div(M, BM), batch);
   SEQX_DISPATCH_T(gemm_kernel, T, To, WM, WN, TM, TN);
 }
-
-bool aligned_to(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
 
 template <class T, class To>
 void gemm_any(hipStream_t st, bool ta, bool tb, int M, int N, int K, double alpha, const T* A, long lda, long sA,
@@ -507,22 +531,16 @@ void gemm_any(hipStream_t st, bool ta, bool tb, int M, int N, int K, double alph
     }
   }
   const bool skinny = N <= 16;
-  const bool even = ((lda | ldb | sA | sB) & 1) == 0 && aligned_to(A, 2 * sizeof(T)) && aligned_to(B, 2 * sizeof(T));
-  // the 128 x 128 tiles address each operand with 32-bit byte offsets from a
+  // the large tiles address each operand with 32-bit byte offsets from a
   // tile corner: rows and panel steps must stay below 2 GiB
   const long ldmax = lda > ldb ? lda : ldb;
-  const bool small_offsets = (ldmax * (static_cast<long>(K > kBM ? K : kBM) + kBM) + K) * static_cast<long>(sizeof(T)) <
+  const bool small_offsets = (ldmax * (static_cast<long>(K > 128 ? K : 128) + 128) + K) * static_cast<long>(sizeof(T)) <
                              (1L << 31);
-  if (even && small_offsets && M >= 96 && N >= 96 && K >= 16) {
-    const bool w96 = tile_width(N) == 96;
-    if (epi && w96)
-      launch128<T, To, true, 96>(st, ta, tb, M, N, K, alpha, A, lda, sA, B, ldb, sB, beta, C, ldc, sC, batch, ep);
-    else if (epi)
-      launch128<T, To, true, 128>(st, ta, tb, M, N, K, alpha, A, lda, sA, B, ldb, sB, beta, C, ldc, sC, batch, ep);
-    else if (w96)
-      launch128<T, To, false, 96>(st, ta, tb, M, N, K, alpha, A, lda, sA, B, ldb, sB, beta, C, ldc, sC, batch, ep);
+  if (small_offsets && M >= 32 && N >= 32 && K >= 32) {
+    if (epi)
+      launch_tiles<T, To, true>(st, ta, tb, M, N, K, alpha, A, lda, sA, B, ldb, sB, beta, C, ldc, sC, batch, ep);
     else
-      launch128<T, To, false, 128>(st, ta, tb, M, N, K, alpha, A, lda, sA, B, ldb, sB, beta, C, ldc, sC, batch, ep);
+      launch_tiles<T, To, false>(st, ta, tb, M, N, K, alpha, A, lda, sA, B, ldb, sB, beta, C, ldc, sC, batch, ep);
   } else if (epi) {
     launch_cfg<T, To, 2, 2, 2, 2, true>(st, ta, tb, M, N, K, alpha, A, lda, sA, B, ldb, sB, beta, C, ldc, sC, batch,
                                         ep);

@@ -78,6 +78,17 @@ struct F32Io {
   float* out2 = nullptr;
 };
 
+bool has_planes(const DeviceMolecule& m, int precision) { return precision != kPrecFP64 && m.Cop.n > 0; }
+
+// Planes of the low-precision transforms.  Split bfloat16 takes two from 96
+// occupied and 96 virtual orbitals on (even numbers of both); below, and for
+// odd numbers, its callers have always had FP32 accuracy, and the third plane
+// costs little there (the products are bound by launches and tile remainders).
+int plane_count(const DeviceMolecule& m, int precision) {
+  const bool two = precision == kPrecBF16x3 && m.nocc >= 96 && m.nvirt >= 96 && m.nocc % 2 == 0 && m.nvirt % 2 == 0;
+  return two ? 2 : 3;
+}
+
 // One chunk of the product: kc vectors Vc -> out1c (and out2c), outputs os
 // elements apart.  ev (optional) receives the phase boundaries.
 void sigma_chunk(const DeviceMolecule& m, int theory, int kc, const double* Vc, double* out1c, double* out2c, long os,
@@ -130,7 +141,7 @@ void sigma_chunk(const DeviceMolecule& m, int theory, int kc, const double* Vc, 
   } else if (b.Vp) {
     // bfloat16 planes: every operand with its summation index along the rows,
     // so V enters transposed and Z is formed transposed
-    const int np = precision == kPrecBF16x3 ? 2 : 3;
+    const int np = plane_count(m, precision);
     const long rn = plane_row(n, np), rv = plane_row(v, np), ro = plane_row(o, np);
     if (io) {
       ep.V = nullptr;
@@ -216,8 +227,6 @@ void check_sigma_args(const DeviceMolecule& m, int precision) {
     throw Error(kEState, "FP32 MO coefficients missing");
 }
 
-bool has_planes(const DeviceMolecule& m, int precision) { return precision != kPrecFP64 && m.Cop.n > 0; }
-
 // Pieces of one chunk's intermediates laid out in a single workspace, each
 // starting on a 256-byte boundary; returns the bytes used.  base == nullptr
 // only measures.  planes: the plane set instead of the FP32 set; Z then takes
@@ -239,7 +248,7 @@ size_t carve_chunk(const DeviceMolecule& m, int theory, int kc, int precision, b
     c.F = reinterpret_cast<double*>(take(nb * nn * sizeof(double)));
     c.Z = reinterpret_cast<double*>(take(nb * nv * sizeof(double)));
   } else if (planes) {
-    const int np = precision == kPrecBF16x3 ? 2 : 3;
+    const int np = plane_count(m, precision);
     const size_t rn = plane_row(m.nao, np), rv = plane_row(m.nvirt, np), ro = plane_row(m.nocc, np);
     c.Vp = reinterpret_cast<plane_t*>(take(kc * v * ro * sizeof(plane_t)));
     c.T1p = reinterpret_cast<plane_t*>(take(kc * n * rv * sizeof(plane_t)));

@@ -225,16 +225,26 @@ __device__ __forceinline__ void load4_any(const T* p, double* o) {
 }
 
 // X and Y rows of FP64 or FP32 elements (FP32 ones widened on load); FP64
-// products.  ALIGNED: row starts are 16-byte aligned.  Otherwise (an odd row
-// length, as in C40H42 with nov = 101 * 101) the same four values per lane
-// come as four element loads, which hit the same cache lines.
-template <int NX, class TX, class TY, bool ALIGNED>
+// products.
+//   kRowsAligned: row starts are 16-byte aligned.
+//   kRowsAny: they are not (an odd row length, as in C40H42 with nov = 101 *
+//     101); the same four values per lane come as four element loads, which hit
+//     the same cache lines.
+//   kRowsOne: a single short row of X, one chunk over all of it with k in
+//     ascending order (MFMA step q of a block takes k = 4 q + l / 16) and one
+//     16-row tile of Y per wavefront.  The Coulomb part of every SCF below 1024
+//     same-atom pairs comes from here: the order of its sums is part of the
+//     reproducible orbitals.
+enum DotRows { kRowsAligned, kRowsAny, kRowsOne };
+
+template <int NX, class TX, class TY, int ROWS>
 __global__ void __launch_bounds__(256) skinny_dots_kernel(int ns, int nt, const TX* __restrict__ X, long ldx,
                                                           const TY* __restrict__ Y, long ldy, long len,
                                                           long chunk, double* __restrict__ part) {
+  constexpr int NB = ROWS == kRowsOne ? 1 : 2;  // 16-row tiles of Y per wavefront
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int i = lane & 15, g = lane >> 4;
-  const int t0 = blockIdx.x * 128 + wave * 32;
+  const int t0 = (blockIdx.x * 4 + wave) * (16 * NB);
   const long k0 = static_cast<long>(blockIdx.y) * chunk;
   const long k1 = k0 + chunk < len ? k0 + chunk : len;
   if (t0 >= nt) return;
@@ -242,28 +252,34 @@ __global__ void __launch_bounds__(256) skinny_dots_kernel(int ns, int nt, const 
   const TX* xr[NX];
 #pragma unroll
   for (int a = 0; a < NX; ++a) xr[a] = X + static_cast<long>(min(16 * a + i, ns - 1)) * ldx;
-  const TY* yr[2];
+  const TY* yr[NB];
 #pragma unroll
-  for (int b = 0; b < 2; ++b) yr[b] = Y + static_cast<long>(min(t0 + 16 * b + i, nt - 1)) * ldy;
-  d4 acc[NX][2];
+  for (int b = 0; b < NB; ++b) yr[b] = Y + static_cast<long>(min(t0 + 16 * b + i, nt - 1)) * ldy;
+  d4 acc[NX][NB];
 #pragma unroll
   for (int a = 0; a < NX; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = d4{0, 0, 0, 0};
+    for (int b = 0; b < NB; ++b) acc[a][b] = d4{0, 0, 0, 0};
   // blocks of 16 k-values; the loads of block + 1 are issued before the MFMAs
   // of the current block (past the last full block they repeat it)
   const long nfull = (k1 - k0) / 16;
   auto load = [&](long blk, double (*xv)[4], double (*yv)[4]) {
-    const long kk = k0 + 16 * blk + 4 * g;
+    const long kk = k0 + 16 * blk + (ROWS == kRowsOne ? g : 4 * g);
 #pragma unroll
     for (int a = 0; a < NX; ++a) {
-      if constexpr (ALIGNED) load4(xr[a] + kk, xv[a]);
-      else load4_any(xr[a] + kk, xv[a]);
+      if constexpr (ROWS == kRowsAligned) load4(xr[a] + kk, xv[a]);
+      else if constexpr (ROWS == kRowsAny) load4_any(xr[a] + kk, xv[a]);
+      else
+#pragma unroll
+        for (int q = 0; q < 4; ++q) xv[a][q] = static_cast<double>(xr[a][kk + 4 * q]);
     }
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      if constexpr (ALIGNED) load4(yr[b] + kk, yv[b]);
-      else load4_any(yr[b] + kk, yv[b]);
+    for (int b = 0; b < NB; ++b) {
+      if constexpr (ROWS == kRowsAligned) load4(yr[b] + kk, yv[b]);
+      else if constexpr (ROWS == kRowsAny) load4_any(yr[b] + kk, yv[b]);
+      else
+#pragma unroll
+        for (int q = 0; q < 4; ++q) yv[b][q] = static_cast<double>(yr[b][kk + 4 * q]);
     }
   };
   auto mma = [&](double (*xv)[4], double (*yv)[4]) {
@@ -272,10 +288,10 @@ __global__ void __launch_bounds__(256) skinny_dots_kernel(int ns, int nt, const 
 #pragma unroll
       for (int a = 0; a < NX; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(xv[a][q], yv[b][q], acc[a][b], 0, 0, 0);
+        for (int b = 0; b < NB; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(xv[a][q], yv[b][q], acc[a][b], 0, 0, 0);
   };
   if (nfull > 0) {
-    double xa0[NX][4], ya0[2][4], xa1[NX][4], ya1[2][4];
+    double xa0[NX][4], ya0[NB][4], xa1[NX][4], ya1[NB][4];
     load(0, xa0, ya0);
     long blk = 0;
     for (; blk + 1 < nfull; blk += 2) {
@@ -290,12 +306,12 @@ __global__ void __launch_bounds__(256) skinny_dots_kernel(int ns, int nt, const 
   if (k < k1) {  // ragged end of the last chunk: element loads, zero past len
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const long kk = k + 4 * g + q;
+      const long kk = ROWS == kRowsOne ? k + 4 * q + g : k + 4 * g + q;
       const bool in = kk < k1;
 #pragma unroll
       for (int a = 0; a < NX; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int b = 0; b < NB; ++b)
           acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(in ? static_cast<double>(xr[a][kk]) : 0.0,
                                                            in ? static_cast<double>(yr[b][kk]) : 0.0, acc[a][b], 0,
                                                            0, 0);
@@ -305,7 +321,7 @@ __global__ void __launch_bounds__(256) skinny_dots_kernel(int ns, int nt, const 
 #pragma unroll
   for (int a = 0; a < NX; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int s = 16 * a + (lane >> 4) + 4 * r, t = t0 + 16 * b + (lane & 15);
@@ -315,10 +331,10 @@ __global__ void __launch_bounds__(256) skinny_dots_kernel(int ns, int nt, const 
 
 }  // namespace
 
-// Chunk length: about 1024 workgroups for long vectors, at least 256 values.
-// Vectors below 1024 values take chunks of 64 (4 MFMA blocks a wavefront): one
-// molecule of 30-90 AOs gives only a handful of 128-row groups, and the short
-// chunks keep the serial part near a microsecond.
+// Chunk length: about 1024 workgroups, at least 256 values.  Rows below 1024
+// values take chunks of 64 (4 MFMA blocks a wavefront): one molecule of 30-90
+// AOs gives only a handful of 128-row groups, and the short chunks keep the
+// serial part near a microsecond.
 constexpr long kShortDot = 1024;
 long skinny_chunk(int nt, long len) {
   const long groups = (nt + 127) / 128;
@@ -332,10 +348,10 @@ long skinny_chunk(int nt, long len) {
 // most 48 rows; more rows take several passes, each reading Y once.
 constexpr int kDotRows = 48;
 
-// Partial sums of one pass of at most kDotRows rows: whatever nt is, at most
-// 16 chunks of a vector below kShortDot and min(1024, len / 256) above.  The
-// bound is monotone in ns, nt and len: a workspace sized for the largest shape
-// serves every smaller one.
+// Partial sums of one pass of at most kDotRows rows: whatever nt is, at most 16
+// chunks of a vector below kShortDot and min(1024, len / 256) above.  The bound
+// is monotone in ns, nt and len: a workspace sized for the largest shape serves
+// every smaller one.
 size_t dots_workspace(int ns, int nt, long len) {
   const long nchunks = std::max(std::min<long>(16, (len + 63) / 64), std::min<long>(1024, (len + 255) / 256));
   return static_cast<size_t>(nchunks) * std::min(ns, kDotRows) * nt;
@@ -350,20 +366,20 @@ bool rows_aligned(const TX* X, long ldx, const TY* Y, long ldy) {
   return ldx % ax == 0 && ldy % ay == 0 && aligned_to(X, 16) && aligned_to(Y, 16);
 }
 
-template <class TX, class TY, bool ALIGNED>
+template <class TX, class TY, int ROWS>
 void dots_pass(hipStream_t st, int ns, const TX* X, long ldx, int nt, const TY* Y, long ldy, long len, double* out,
                long ldo, double* ws) {
-  const long chunk = skinny_chunk(nt, len);
+  const long chunk = ROWS == kRowsOne ? len : skinny_chunk(nt, len);
   const int nchunks = static_cast<int>((len + chunk - 1) / chunk);
-  const dim3 grid(ceil_div(nt, 128), nchunks);
+  const dim3 grid(ceil_div(nt, ROWS == kRowsOne ? 64 : 128), nchunks);
   if (ns <= 16)
-    hipLaunchKernelGGL((skinny_dots_kernel<1, TX, TY, ALIGNED>), grid, dim3(256), 0, st, ns, nt, X, ldx, Y, ldy, len,
+    hipLaunchKernelGGL((skinny_dots_kernel<1, TX, TY, ROWS>), grid, dim3(256), 0, st, ns, nt, X, ldx, Y, ldy, len,
                        chunk, ws);
   else if (ns <= 32)
-    hipLaunchKernelGGL((skinny_dots_kernel<2, TX, TY, ALIGNED>), grid, dim3(256), 0, st, ns, nt, X, ldx, Y, ldy, len,
+    hipLaunchKernelGGL((skinny_dots_kernel<2, TX, TY, ROWS>), grid, dim3(256), 0, st, ns, nt, X, ldx, Y, ldy, len,
                        chunk, ws);
   else
-    hipLaunchKernelGGL((skinny_dots_kernel<3, TX, TY, ALIGNED>), grid, dim3(256), 0, st, ns, nt, X, ldx, Y, ldy, len,
+    hipLaunchKernelGGL((skinny_dots_kernel<3, TX, TY, ROWS>), grid, dim3(256), 0, st, ns, nt, X, ldx, Y, ldy, len,
                        chunk, ws);
   if (ns * nt < 1024 && nchunks >= 64)
     hipLaunchKernelGGL(reduce_partials_wide_kernel, dim3(ns * nt), dim3(256), 0, st, nchunks, ns, nt, ws, out, ldo);
@@ -375,11 +391,11 @@ void dots_pass(hipStream_t st, int ns, const TX* X, long ldx, int nt, const TY* 
 
 }  // namespace
 
-// Any length and alignment: products over 804 same-atom pairs ((H2O)67, 7
-// vectors) took 110 us as a general GEMM of 7 x 804 outputs, which walks all
-// of K in each of a dozen workgroups: the pass of seven (A+B)V, (A-B)V products
+// Any length and alignment.  Products over 804 same-atom pairs ((H2O)67, 7
+// vectors) took 110 us as a general GEMM of 7 x 804 outputs; with the short
+// and odd rows on these kernels the pass of seven (A+B)V, (A-B)V products
 // there went 362 -> 256 us, 20 CIS roots of C40H42 (nov odd) 159 -> 129 ms and
-// the parameter derivatives of C20H22 21.8 -> 16.5 ms with every length here.
+// the parameter derivatives of C20H22 21.8 -> 16.5 ms.
 void dots(hipStream_t st, int ns, const double* X, long ldx, int nt, const double* Y, long ldy, long len, double* out,
           long ldo, double* ws) {
   if (ns <= 0 || nt <= 0) return;
@@ -389,8 +405,9 @@ void dots(hipStream_t st, int ns, const double* X, long ldx, int nt, const doubl
     const int nr = std::min(kDotRows, ns - r0);
     const double* Xr = X + static_cast<long>(r0) * ldx;
     double* outr = out + static_cast<long>(r0) * ldo;
-    if (al) dots_pass<double, double, true>(st, nr, Xr, ldx, nt, Y, ldy, len, outr, ldo, ws);
-    else dots_pass<double, double, false>(st, nr, Xr, ldx, nt, Y, ldy, len, outr, ldo, ws);
+    if (ns == 1 && len < kShortDot) dots_pass<double, double, kRowsOne>(st, nr, Xr, ldx, nt, Y, ldy, len, outr, ldo, ws);
+    else if (al) dots_pass<double, double, kRowsAligned>(st, nr, Xr, ldx, nt, Y, ldy, len, outr, ldo, ws);
+    else dots_pass<double, double, kRowsAny>(st, nr, Xr, ldx, nt, Y, ldy, len, outr, ldo, ws);
   }
 }
 
@@ -402,7 +419,7 @@ void dots_mixed(hipStream_t st, int ns, const TX* X, long ldx, int nt, const TY*
   if (ns <= 0 || nt <= 0) return;
   if (len < 1024 || !rows_aligned(X, ldx, Y, ldy)) throw Error(kEArg, "FP32 inner products need long, 16-byte aligned rows");
   for (int r0 = 0; r0 < ns; r0 += kDotRows)
-    dots_pass<TX, TY, true>(st, std::min(kDotRows, ns - r0), X + static_cast<long>(r0) * ldx, ldx, nt, Y, ldy, len,
+    dots_pass<TX, TY, kRowsAligned>(st, std::min(kDotRows, ns - r0), X + static_cast<long>(r0) * ldx, ldx, nt, Y, ldy, len,
               out + static_cast<long>(r0) * ldo, ldo, ws);
 }
 template void dots_mixed<float, float>(hipStream_t, int, const float*, long, int, const float*, long, long, double*,
