@@ -119,6 +119,14 @@ __global__ void cg_dir_kernel(long nov, const double* __restrict__ beta, const d
   p[b] = z[b] + beta[blockIdx.y] * p[b];
 }
 
+// table 2 y -= table 2 y + 1, len elements each
+__global__ void pair_difference_kernel(long len, double* __restrict__ T) {
+  const long x = blockIdx.x * static_cast<long>(blockDim.x) + threadIdx.x;
+  if (x >= len) return;
+  double* t = T + 2 * static_cast<long>(blockIdx.y) * len;
+  t[x] -= t[len + x];
+}
+
 // diagonal of the k x k inner products of the rows of X and Y, to the host
 std::vector<double> row_dots(hipStream_t st, int k, const double* X, const double* Y, long len, double* kk,
                              double* ws) {
@@ -148,11 +156,28 @@ GradientResult param_gradient(DeviceMolecule& m, int theory, const Elem* elems_h
   const double per_root = 8.0 * (10.0 * nn + npp + 8.0 * nov + 2.0 * nv + no + v * static_cast<double>(v) +
                                  o * static_cast<double>(o));
   const int kg_max = static_cast<int>(std::max(1.0, std::min<double>(16.0, 4e9 / per_root)));
-  // parameter perturbations: which (slot, parameter) pairs apply
+  // parameter perturbations: the (slot, parameter) pairs that apply
+  struct Param {
+    int slot, p;
+    double h;
+  };
+  std::vector<Param> params;
   std::vector<int> present(kNumSlots, 0);
   for (int s : m.L.slot) present[s] = 1;
-  DBuf<Elem> dtab(2 * kNumSlots);
-  DBuf<double> Wp(2 * npp), Hp(2 * nn);  // tables at theta + h and theta - h
+  for (int s = 0; s < kNumSlots; ++s)
+    for (int p = 0; present[s] && p < kNumElemParams; ++p) {
+      if (elems_host[s].Z == 1 && !(p == 0 || p == 2 || p == 4 || p == 6)) continue;  // H: zeta_s, U_ss, beta_s, g_ss
+      params.push_back({s, p, 1e-5 * std::max(std::fabs(raw[s][p]), 1e-2)});
+    }
+  // Tables at theta + h and theta - h of as many parameters at a time as keep
+  // them below about 2 GB: the builders take a thread per atom pair, a few
+  // hundred of a small molecule, so one parameter's tables leave the GPU
+  // nearly empty.  One launch over all of them: C20H22 15.2 -> 4.5 ms.
+  const long per_param = 2 * (npp + nn);
+  const int pg_max = static_cast<int>(std::max<long>(1, std::min<long>(params.size(), (2L << 30) / 8 / per_param)));
+  std::vector<Elem> tab(static_cast<size_t>(2) * kNumSlots * pg_max);
+  DBuf<Elem> dtab(tab.size());
+  DBuf<double> Wp(static_cast<size_t>(2) * npp * pg_max), Hp(static_cast<size_t>(2) * nn * pg_max);
   for (int k0 = 0; k0 < K; k0 += kg_max) {
     const int kg = std::min(kg_max, K - k0);
     DBuf<double> T(kg * nov), U(kg * nov), L(kg * nov), Z(kg * nov), R(kg * nov), Pz(kg * nov), Q(kg * nov),
@@ -161,7 +186,7 @@ GradientResult param_gradient(DeviceMolecule& m, int theory, const Elem* elems_h
     DBuf<double> Mvv(static_cast<size_t>(kg) * v * v), Moo(static_cast<size_t>(kg) * o * o), Tnv(kg * nv),
         Tno(kg * no);
     DBuf<double> kk(static_cast<size_t>(kg) * kg), coef(2 * kg), ws;
-    ws.alloc(std::max<size_t>(std::max(dots_workspace(kg, kg, nov), dots_workspace(kg, 1, std::max(npp, nn))), 1024));
+    ws.alloc(std::max<size_t>(std::max(dots_workspace(kg, kg, nov), dots_workspace(kg, pg_max, std::max(npp, nn))), 1024));
     const double* X = m.X.p + k0 * nov;
     const double* Y = m.Y.p + k0 * nov;
     const dim3 rows(ceil_div(nov, 256), kg);
@@ -248,36 +273,37 @@ GradientResult param_gradient(DeviceMolecule& m, int theory, const Elem* elems_h
     hipLaunchKernelGGL(gamma_kernel, dim3(ceil_div(np, 256), np, kg), dim3(256), 0, st, np, n, m.pi_mu.p,
                        m.pi_nu.p, Dm.p, m.P.p, Ts, Ua, Gam.p);
     SEQX_LAUNCH_CHECK();
-    // derivative tables by central differences of the integral builder, contracted per parameter
-    std::vector<double> hg(kg), hh(kg);
-    for (int s = 0; s < kNumSlots; ++s) {
-      if (!present[s]) continue;
-      const int Zs = elems_host[s].Z;
-      for (int p = 0; p < kNumElemParams; ++p) {
-        if (Zs == 1 && !(p == 0 || p == 2 || p == 4 || p == 6)) continue;  // H: zeta_s, U_ss, beta_s, g_ss
-        const double h = 1e-5 * std::max(std::fabs(raw[s][p]), 1e-2);
-        Elem tab[2 * kNumSlots];
+    // derivative tables by central differences of the integral builder, contracted with Gamma and D
+    for (size_t p0 = 0; p0 < params.size(); p0 += pg_max) {
+      const int pg = static_cast<int>(std::min<size_t>(pg_max, params.size() - p0));
+      for (int q = 0; q < pg; ++q) {
+        const Param& pr = params[p0 + q];
         for (int sg = 0; sg < 2; ++sg) {
           double rv[kNumElemParams];
-          for (int q = 0; q < kNumElemParams; ++q) rv[q] = raw[s][q];
-          rv[p] += sg == 0 ? h : -h;
-          for (int t = 0; t < kNumSlots; ++t) tab[sg * kNumSlots + t] = elems_host[t];
-          tab[sg * kNumSlots + s] = make_elem(Zs, rv);
+          for (int x = 0; x < kNumElemParams; ++x) rv[x] = raw[pr.slot][x];
+          rv[pr.p] += sg == 0 ? pr.h : -pr.h;
+          Elem* t = tab.data() + static_cast<size_t>(2 * q + sg) * kNumSlots;
+          std::copy(elems_host, elems_host + kNumSlots, t);
+          t[pr.slot] = make_elem(elems_host[pr.slot].Z, rv);
         }
-        SEQX_HIP(hipMemcpyAsync(dtab.p, tab, sizeof(tab), hipMemcpyHostToDevice, st));
-        build_integrals(m, dtab.p, Wp.p, Hp.p, st);
-        build_integrals(m, dtab.p + kNumSlots, Wp.p + npp, Hp.p + nn, st);
-        axpby(st, npp, -1.0, Wp.p + npp, 1.0, Wp.p);  // W+ - W-
-        axpby(st, nn, -1.0, Hp.p + nn, 1.0, Hp.p);
-        dots(st, kg, Gam.p, npp, 1, Wp.p, npp, npp, kk.p, 1, ws.p);
-        dots(st, kg, Dm.p, nn, 1, Hp.p, nn, nn, kk.p + kg, 1, ws.p);
-        SEQX_HIP(hipMemcpyAsync(hg.data(), kk.p, kg * sizeof(double), hipMemcpyDeviceToHost, st));
-        SEQX_HIP(hipMemcpyAsync(hh.data(), kk.p + kg, kg * sizeof(double), hipMemcpyDeviceToHost, st));
-        SEQX_HIP(hipStreamSynchronize(st));  // also keeps `tab` alive until its copy is done
-        for (int j = 0; j < kg; ++j)
-          grad[(static_cast<size_t>(k0 + j) * kNumSlots + s) * kNumElemParams + p] =
-              kHartreeEV * (hg[j] + hh[j]) / (2.0 * h);
       }
+      SEQX_HIP(hipMemcpyAsync(dtab.p, tab.data(), sizeof(Elem) * 2 * kNumSlots * pg, hipMemcpyHostToDevice, st));
+      build_integrals(m, dtab.p, Wp.p, Hp.p, st, 2 * pg);
+      hipLaunchKernelGGL(pair_difference_kernel, dim3(ceil_div(npp, 256), pg), dim3(256), 0, st, npp, Wp.p);
+      hipLaunchKernelGGL(pair_difference_kernel, dim3(ceil_div(nn, 256), pg), dim3(256), 0, st, nn, Hp.p);
+      SEQX_LAUNCH_CHECK();
+      DBuf<double> contr(static_cast<size_t>(2) * kg * pg);
+      dots(st, kg, Gam.p, npp, pg, Wp.p, 2 * npp, npp, contr.p, pg, ws.p);
+      dots(st, kg, Dm.p, nn, pg, Hp.p, 2 * nn, nn, contr.p + static_cast<size_t>(kg) * pg, pg, ws.p);
+      std::vector<double> hc2(contr.n);
+      SEQX_HIP(hipMemcpyAsync(hc2.data(), contr.p, hc2.size() * sizeof(double), hipMemcpyDeviceToHost, st));
+      SEQX_HIP(hipStreamSynchronize(st));  // also keeps `tab` as it is until its copy is done
+      for (int j = 0; j < kg; ++j)
+        for (int q = 0; q < pg; ++q) {
+          const Param& pr = params[p0 + q];
+          grad[(static_cast<size_t>(k0 + j) * kNumSlots + pr.slot) * kNumElemParams + pr.p] =
+              kHartreeEV * (hc2[static_cast<size_t>(j) * pg + q] + hc2[static_cast<size_t>(kg + j) * pg + q]) / (2.0 * pr.h);
+        }
     }
   }
   return res;

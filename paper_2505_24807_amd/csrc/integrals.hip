@@ -118,6 +118,8 @@ __global__ void __launch_bounds__(128) two_centre_kernel(int npairs, const int2*
                                                          double* __restrict__ W, int ldw) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= npairs) return;
+  elems += blockIdx.y * kNumSlots;
+  W += static_cast<size_t>(blockIdx.y) * ldw * ldw;
   const int A = pairs[p].x, B = pairs[p].y;
   const Elem ea = elems[slot[A]], eb = elems[slot[B]];
   double f[3][3];
@@ -160,6 +162,8 @@ __global__ void one_centre_kernel(int natoms, const int* __restrict__ slot, cons
                                   const Elem* __restrict__ elems, double* __restrict__ W, int ldw) {
   const int A = blockIdx.x;
   if (A >= natoms) return;
+  elems += blockIdx.y * kNumSlots;
+  W += static_cast<size_t>(blockIdx.y) * ldw * ldw;
   const Elem e = elems[slot[A]];
   const int o = pi_off[A];
   const int np = e.nao == 4 ? 10 : 1;
@@ -305,6 +309,8 @@ __global__ void __launch_bounds__(128) resonance_kernel(int npairs, const int2* 
                                                         double* __restrict__ H, int ldh) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= npairs) return;
+  elems += blockIdx.y * kNumSlots;
+  H += static_cast<size_t>(blockIdx.y) * ldh * ldh;
   const int A = pairs[p].x, B = pairs[p].y;
   const Elem ea = elems[slot[A]], eb = elems[slot[B]];
   double f[3][3];
@@ -330,6 +336,9 @@ __global__ void core_diag_kernel(int natoms, const int* __restrict__ slot, const
                                  const int* __restrict__ pi_off, const Elem* __restrict__ elems,
                                  const double* __restrict__ W, int ldw, double* __restrict__ H, int ldh) {
   const int A = blockIdx.x;
+  elems += blockIdx.y * kNumSlots;
+  W += static_cast<size_t>(blockIdx.y) * ldw * ldw;
+  H += static_cast<size_t>(blockIdx.y) * ldh * ldh;
   const Elem e = elems[slot[A]];
   const int np = e.nao == 4 ? 10 : 1;
   __shared__ double part[10][64];
@@ -359,37 +368,37 @@ __global__ void core_diag_kernel(int natoms, const int* __restrict__ slot, const
 
 }  // namespace
 
-void build_integrals(const DeviceMolecule& m, const Elem* elems, double* W, double* H, hipStream_t st) {
+void build_integrals(const DeviceMolecule& m, const Elem* elems, double* W, double* H, hipStream_t st, int ntab) {
   const int ldw = m.np;
   // two-centre blocks, one launch per pair type (heavy-heavy, heavy-H, H-H)
   if (m.npairs[0])
-    hipLaunchKernelGGL((two_centre_kernel<10, 10>), dim3(ceil_div(m.npairs[0], 128)), dim3(128), 0, st, m.npairs[0],
+    hipLaunchKernelGGL((two_centre_kernel<10, 10>), dim3(ceil_div(m.npairs[0], 128), ntab), dim3(128), 0, st, m.npairs[0],
                        m.pairs[0].p, m.slot.p, m.xyz.p, m.pi_off.p, elems, W, ldw);
   if (m.npairs[1])
-    hipLaunchKernelGGL((two_centre_kernel<10, 1>), dim3(ceil_div(m.npairs[1], 128)), dim3(128), 0, st, m.npairs[1],
+    hipLaunchKernelGGL((two_centre_kernel<10, 1>), dim3(ceil_div(m.npairs[1], 128), ntab), dim3(128), 0, st, m.npairs[1],
                        m.pairs[1].p, m.slot.p, m.xyz.p, m.pi_off.p, elems, W, ldw);
   if (m.npairs[2])
-    hipLaunchKernelGGL((two_centre_kernel<1, 1>), dim3(ceil_div(m.npairs[2], 128)), dim3(128), 0, st, m.npairs[2],
+    hipLaunchKernelGGL((two_centre_kernel<1, 1>), dim3(ceil_div(m.npairs[2], 128), ntab), dim3(128), 0, st, m.npairs[2],
                        m.pairs[2].p, m.slot.p, m.xyz.p, m.pi_off.p, elems, W, ldw);
-  hipLaunchKernelGGL(one_centre_kernel, dim3(m.natoms), dim3(128), 0, st, m.natoms, m.slot.p, m.pi_off.p, elems,
+  hipLaunchKernelGGL(one_centre_kernel, dim3(m.natoms, ntab), dim3(128), 0, st, m.natoms, m.slot.p, m.pi_off.p, elems,
                      W, ldw);
   SEQX_LAUNCH_CHECK();
   // core Hamiltonian: off-atom resonance blocks, then atom-diagonal blocks
   const int ldh = m.nao;
   if (m.npairs[0])
-    hipLaunchKernelGGL((resonance_kernel<4, 4>), dim3(ceil_div(m.npairs[0], 128)), dim3(128), 0, st, m.npairs[0],
+    hipLaunchKernelGGL((resonance_kernel<4, 4>), dim3(ceil_div(m.npairs[0], 128), ntab), dim3(128), 0, st, m.npairs[0],
                        m.pairs[0].p, m.slot.p, m.xyz.p, m.ao_off.p, elems, H, ldh);
   if (m.npairs[1])
-    hipLaunchKernelGGL((resonance_kernel<4, 1>), dim3(ceil_div(m.npairs[1], 128)), dim3(128), 0, st, m.npairs[1],
+    hipLaunchKernelGGL((resonance_kernel<4, 1>), dim3(ceil_div(m.npairs[1], 128), ntab), dim3(128), 0, st, m.npairs[1],
                        m.pairs[1].p, m.slot.p, m.xyz.p, m.ao_off.p, elems, H, ldh);
   if (m.npairs[2])
-    hipLaunchKernelGGL((resonance_kernel<1, 1>), dim3(ceil_div(m.npairs[2], 128)), dim3(128), 0, st, m.npairs[2],
+    hipLaunchKernelGGL((resonance_kernel<1, 1>), dim3(ceil_div(m.npairs[2], 128), ntab), dim3(128), 0, st, m.npairs[2],
                        m.pairs[2].p, m.slot.p, m.xyz.p, m.ao_off.p, elems, H, ldh);
-  hipLaunchKernelGGL(core_diag_kernel, dim3(m.natoms), dim3(640), 0, st, m.natoms, m.slot.p, m.ao_off.p, m.pi_off.p,
+  hipLaunchKernelGGL(core_diag_kernel, dim3(m.natoms, ntab), dim3(640), 0, st, m.natoms, m.slot.p, m.ao_off.p, m.pi_off.p,
                      elems, W, ldw, H, ldh);
   SEQX_LAUNCH_CHECK();
 }
 
-void build_integrals(const DeviceMolecule& m, hipStream_t st) { build_integrals(m, m.elems, m.W.p, m.H.p, st); }
+void build_integrals(const DeviceMolecule& m, hipStream_t st) { build_integrals(m, m.elems, m.W.p, m.H.p, st, 1); }
 
 }  // namespace seqx
