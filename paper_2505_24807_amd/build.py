@@ -19,7 +19,7 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libseqx.so")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 
-SOURCES = ["model.cpp", "integrals.hip", "gemm.hip", "planes.hip", "fock.hip", "linalg.hip", "scf.hip", "sigma.hip",
+SOURCES = ["model.cpp", "integrals.hip", "gemm.hip", "planes.hip", "fock.hip", "linalg.hip", "scf.hip", "scf_small.hip", "sigma.hip",
            "davidson.hip", "skinny.hip", "batch.hip", "mlp.hip", "small_dense.hip", "eig_lowest.hip", "spectrum.hip", "gradient.hip", "abi.cpp"]
 
 CFLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",

@@ -62,6 +62,7 @@ struct seqx_job {
   std::vector<std::unique_ptr<DeviceMolecule>> mols;
   GWork gw;
   ScfWork sw;
+  ScfSmallWork ssw;
   DavWork dw;
   BatchWork bw;
   DBuf<double> guess_v;
@@ -184,14 +185,14 @@ double elapsed_ms(hipEvent_t a, hipEvent_t b) {
   return ms;
 }
 
-// Molecules of a batch are independent.  One molecule's launches are small and
-// its SCF waits on the host every few purification steps, so a single stream
-// leaves the GPU mostly idle: from kPrepareParallelMin molecules on, a few
-// host threads, each with its own stream, dense solver and work buffers, take
-// molecules in turn.  Every molecule gets exactly the computation of the
-// sequential path.  Buffers come from hipMalloc here (with a caller allocator
-// the sequential path runs, so its callbacks are only entered from the calling
-// thread).  Times are summed over molecules.
+// Molecules of a batch are independent.  From kPrepareParallelMin molecules on,
+// a few host threads, each with its own stream, dense solver and work buffers,
+// take molecules in turn for their set-up, integrals and final eigensolve (and
+// the whole SCF of those too large for one workgroup); the SCF of all small
+// molecules is one launch in between.  Every molecule gets exactly the
+// computation of a single preparation.  Buffers come from hipMalloc here (with
+// a caller allocator the molecules run one by one, so its callbacks are only
+// entered from the calling thread).  Times are summed over molecules.
 constexpr int kPrepareParallelMin = 4;
 constexpr int kPrepareThreads = 8;
 
@@ -207,16 +208,39 @@ int prepare_threads() {
   return n;
 }
 
-void prepare_parallel(seqx_ctx* ctx, seqx_job* job, int nmol, const int32_t* natoms, const int32_t* Z,
-                      const double* xyz, const ScfOptions& so, bool integrals_only) {
-  std::vector<size_t> offs(nmol, 0);
-  for (int m = 1; m < nmol; ++m) offs[m] = offs[m - 1] + natoms[m - 1];
-  std::vector<std::unique_ptr<DeviceMolecule>> mols(nmol);
-  std::vector<double> t_int(nmol, 0.0), t_scf(nmol, 0.0);
+// what a worker thread keeps over its molecules: a stream of its own, a dense
+// solver and work buffers
+struct Worker {
+  hipStream_t stream = nullptr;
+  hipEvent_t e[3] = {nullptr, nullptr, nullptr};
+  std::unique_ptr<DenseSolver> ds;
+  GWork gw;
+  ScfWork sw;
+  Worker() {
+    SEQX_HIP(hipStreamCreateWithFlags(&stream, hipStreamNonBlocking));
+    for (auto& ev : e) SEQX_HIP(hipEventCreate(&ev));
+  }
+  DenseSolver& solver() {
+    if (!ds) ds.reset(new DenseSolver(stream));
+    return *ds;
+  }
+  ~Worker() {
+    if (stream) (void)hipStreamSynchronize(stream);
+    ds.reset();
+    for (auto& ev : e)
+      if (ev) (void)hipEventDestroy(ev);
+    if (stream) (void)hipStreamDestroy(stream);
+  }
+};
+
+// f(molecule, worker) for every molecule, taken in turn by one thread per
+// worker (made by its thread on first use); rethrows a thread's exception after
+// all of them have stopped
+template <class F>
+void parallel_molecules(int device, std::vector<std::unique_ptr<Worker>>& workers, int nmol, F&& f) {
+  const int nw = static_cast<int>(workers.size());
   std::atomic<int> next{0};
-  const int nw = std::min(nmol, prepare_threads());
   std::vector<std::exception_ptr> errs(nw);
-  SEQX_HIP(hipStreamSynchronize(ctx->stream));  // element data uploaded on the context stream
   std::vector<std::thread> pool;
   // joins the started workers however this function is left (a thread that
   // cannot be started stops the others after their current molecule)
@@ -233,42 +257,9 @@ void prepare_parallel(seqx_ctx* ctx, seqx_job* job, int nmol, const int32_t* nat
   for (int wk = 0; wk < nw; ++wk)
     pool.emplace_back([&, wk] {
       try {
-        SEQX_HIP(hipSetDevice(ctx->device));
-        hipStream_t ws = nullptr;
-        SEQX_HIP(hipStreamCreateWithFlags(&ws, hipStreamNonBlocking));
-        struct StreamGuard {
-          hipStream_t s;
-          ~StreamGuard() {
-            (void)hipStreamSynchronize(s);
-            (void)hipStreamDestroy(s);
-          }
-        } guard{ws};
-        hipEvent_t e[3] = {nullptr, nullptr, nullptr};
-        struct EventGuard {
-          hipEvent_t* e;
-          ~EventGuard() {
-            for (int i = 0; i < 3; ++i)
-              if (e[i]) (void)hipEventDestroy(e[i]);
-          }
-        } eguard{e};
-        for (auto& ev : e) SEQX_HIP(hipEventCreate(&ev));
-        DenseSolver ds(ws);
-        GWork gw;
-        ScfWork sw;
-        for (int m = next.fetch_add(1); m < nmol; m = next.fetch_add(1)) {
-          std::unique_ptr<DeviceMolecule> dm(new DeviceMolecule());
-          setup_molecule(ctx, *dm, natoms[m], Z + offs[m], xyz + 3 * offs[m], ws);
-          SEQX_HIP(hipEventRecord(e[0], ws));
-          build_integrals(*dm, ws);
-          SEQX_HIP(hipEventRecord(e[1], ws));
-          if (!integrals_only) run_scf(*dm, so, ds, gw, sw, ws);
-          dm->scf_done = !integrals_only;
-          SEQX_HIP(hipEventRecord(e[2], ws));
-          SEQX_HIP(hipStreamSynchronize(ws));
-          t_int[m] = elapsed_ms(e[0], e[1]);
-          t_scf[m] = elapsed_ms(e[1], e[2]);
-          mols[m] = std::move(dm);
-        }
+        SEQX_HIP(hipSetDevice(device));
+        if (!workers[wk]) workers[wk].reset(new Worker());
+        for (int m = next.fetch_add(1); m < nmol; m = next.fetch_add(1)) f(m, *workers[wk]);
       } catch (...) {
         errs[wk] = std::current_exception();
         next.store(nmol);  // the others stop after their current molecule
@@ -277,6 +268,52 @@ void prepare_parallel(seqx_ctx* ctx, seqx_job* job, int nmol, const int32_t* nat
   for (auto& t : pool) t.join();
   for (auto& e : errs)
     if (e) std::rethrow_exception(e);
+}
+
+void prepare_parallel(seqx_ctx* ctx, seqx_job* job, int nmol, const int32_t* natoms, const int32_t* Z,
+                      const double* xyz, const ScfOptions& so, bool integrals_only) {
+  std::vector<size_t> offs(nmol, 0);
+  for (int m = 1; m < nmol; ++m) offs[m] = offs[m - 1] + natoms[m - 1];
+  std::vector<std::unique_ptr<DeviceMolecule>> mols(nmol);
+  std::vector<double> t_int(nmol, 0.0), t_scf(nmol, 0.0);
+  std::vector<std::unique_ptr<Worker>> workers(std::min(nmol, prepare_threads()));
+  SEQX_HIP(hipStreamSynchronize(ctx->stream));  // element data uploaded on the context stream
+  // setup and integrals of every molecule (and the whole SCF of the large
+  // ones), the small molecules' SCF in one launch, then their orbitals
+  std::vector<DeviceMolecule*> small;
+  for (int phase = 0; phase < 2; ++phase) {
+    parallel_molecules(ctx->device, workers, nmol, [&](int m, Worker& wk) {
+      if (phase == 0) {
+        std::unique_ptr<DeviceMolecule> dm(new DeviceMolecule());
+        setup_molecule(ctx, *dm, natoms[m], Z + offs[m], xyz + 3 * offs[m], wk.stream);
+        SEQX_HIP(hipEventRecord(wk.e[0], wk.stream));
+        build_integrals(*dm, wk.stream);
+        SEQX_HIP(hipEventRecord(wk.e[1], wk.stream));
+        const bool later = integrals_only || scf_is_small(*dm, so);
+        if (!later) run_scf(*dm, so, wk.solver(), wk.gw, wk.sw, wk.stream);
+        SEQX_HIP(hipEventRecord(wk.e[2], wk.stream));
+        SEQX_HIP(hipStreamSynchronize(wk.stream));
+        t_int[m] = elapsed_ms(wk.e[0], wk.e[1]);
+        t_scf[m] = elapsed_ms(wk.e[1], wk.e[2]);
+        dm->scf_done = !later;
+        mols[m] = std::move(dm);
+      } else if (!mols[m]->scf_done) {
+        SEQX_HIP(hipEventRecord(wk.e[0], wk.stream));
+        finish_scf(*mols[m], mols[m]->C.p, wk.solver(), wk.sw, wk.stream);
+        SEQX_HIP(hipEventRecord(wk.e[1], wk.stream));
+        SEQX_HIP(hipStreamSynchronize(wk.stream));
+        t_scf[m] += elapsed_ms(wk.e[0], wk.e[1]);
+        mols[m]->scf_done = true;
+      }
+    });
+    if (integrals_only || phase == 1) break;
+    for (auto& dm : mols)
+      if (!dm->scf_done) small.push_back(dm.get());
+    if (small.empty()) break;
+    const auto t0 = std::chrono::steady_clock::now();
+    run_scf_small(small, so, job->ssw, ctx->stream);
+    t_scf[0] += 1e3 * std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
+  }
   double ti = 0.0, ts = 0.0;
   for (int m = 0; m < nmol; ++m) {
     ti += t_int[m];
@@ -566,7 +603,14 @@ seqx_status seqx_prepare(seqx_ctx* ctx, int32_t nmol, const int32_t* natoms, con
         SEQX_HIP(hipEventRecord(e[0], st));
         build_integrals(*dm, st);
         SEQX_HIP(hipEventRecord(e[1], st));
-        if (!integrals_only) run_scf(*dm, so, *ctx->ds, job->gw, job->sw, st);
+        if (!integrals_only) {
+          if (scf_is_small(*dm, so)) {
+            run_scf_small({dm.get()}, so, job->ssw, st);
+            finish_scf(*dm, dm->C.p, *ctx->ds, job->sw, st);
+          } else {
+            run_scf(*dm, so, *ctx->ds, job->gw, job->sw, st);
+          }
+        }
         dm->scf_done = !integrals_only;
         SEQX_HIP(hipEventRecord(e[2], st));
         SEQX_HIP(hipStreamSynchronize(st));

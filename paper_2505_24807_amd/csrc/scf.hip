@@ -349,8 +349,17 @@ void run_scf(DeviceMolecule& m, const ScfOptions& opt, DenseSolver& ds, GWork& g
   m.commutator = err;
   m.scf_iterations = it;
   if (err > opt.tol) throw Error(kEScfNoConv, "SCF did not converge: max|FP-PF| = " + std::to_string(err));
-  // final orbitals of the converged Fock matrix
-  copy(st, w.CT.p, w.F.p, nn);
+  finish_scf(m, w.F.p, ds, w, st);
+}
+
+void finish_scf(DeviceMolecule& m, const double* F, DenseSolver& ds, ScfWork& w, hipStream_t st) {
+  const int n = m.nao, o = m.nocc;
+  const long nn = static_cast<long>(n) * n;
+  w.CT.ensure(nn);
+  m.C.ensure(nn);
+  m.P.ensure(nn);
+  m.eps.ensure(n);
+  copy(st, w.CT.p, F, nn);
   ds.eigh(n, w.CT.p, n, m.eps.p);
   if (ds.info_eigh() != 0) throw Error(kEDevice, "dense eigensolver failed in SCF");
   transpose(st, n, n, w.CT.p, n, m.C.p, n);  // C[mu][p] = CT[p][mu]

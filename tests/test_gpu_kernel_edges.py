@@ -112,3 +112,43 @@ def test_subspace_sizes(ctx, cap):
     assert np.abs(job.results().omega_eV - ref.omega * model.HARTREE_EV).max() <= 1e-8
     assert job.stats().max_subspace_used <= cap
     job.free()
+
+
+def _joined(*parts):
+    """One molecule of several placed 10 Angstrom apart."""
+    Z = np.concatenate([p.Z for p in parts])
+    xyz = np.concatenate([p.xyz - p.xyz.mean(0) + [10.0 * i, 0, 0] for i, p in enumerate(parts)])
+    return molecules.Molecule(Z, xyz, "+".join(p.name for p in parts))
+
+
+# AOs 2, 6, 16 and 18 (edge of the first tile), 32, 42, 112, 130, 136 (largest of the one-workgroup SCF) and 138
+SCF_MOLS = [molecules.h2(), molecules.water_cluster(1, 1), _joined(molecules.ethylene(), *[molecules.h2()] * 2),
+            molecules.water_cluster(3, 3), _noisy(molecules.polyene(6), 6), molecules.water_cluster(7, 7),
+            _noisy(molecules.polyene(22), 22), _joined(molecules.water_cluster(21, 21), *[molecules.h2()] * 2),
+            _joined(molecules.water_cluster(19, 19), _noisy(molecules.polyene(4), 4)), molecules.water_cluster(23, 23)]
+
+
+@pytest.mark.parametrize("mol", SCF_MOLS, ids=lambda m: m.name)
+def test_ground_states_of_small_molecules(ctx, mol):
+    """A commutator below 1e-10 and a gap above 0.1 hartree leave the density and the orbital energies within 1e-8."""
+    print(f"[gpu] ground state {mol.name}", flush=True)
+    job = ctx.prepare([mol.natoms], mol.Z, mol.xyz)
+    eps, C, P = job.scf_results()
+    sy = model.make_system(mol.Z, mol.xyz, PR)
+    res = scf.run(sy, integrals.build(sy))
+    assert job.stats().commutator <= 1e-10
+    assert np.abs(eps - res.eps * model.HARTREE_EV).max() <= 1e-8
+    assert np.abs(P - res.P).max() <= 1e-8
+    assert np.abs(C.T @ C - np.eye(len(eps))).max() <= 1e-12
+    job.free()
+
+
+def test_ground_states_do_not_depend_on_the_batch(ctx):
+    """Small and large molecules prepared together have the ground states they have alone, to the bit."""
+    job = ctx.prepare(*molecules.concat(SCF_MOLS))
+    for i, mol in enumerate(SCF_MOLS):
+        alone = ctx.prepare([mol.natoms], mol.Z, mol.xyz)
+        for x, y in zip(job.scf_results(i), alone.scf_results()):
+            assert np.array_equal(x, y)
+        alone.free()
+    job.free()
