@@ -11,7 +11,7 @@
 //   F = 2 J(R) - K(R)                 (packed Coulomb, one-centre and pair exchange)
 //   Z = F C_v,  A V = C_o^T Z + de V  (workgroup MFMA GEMMs, FP64 epilogue)
 // with R, F and T/Z in a per-workgroup slice of global scratch (L2-resident).
-// The subspace steps (projection, Jacobi eigensolve, Ritz vectors and
+// The subspace steps (projection, eigensolve, Ritz vectors and
 // residuals, preconditioning, collapse, Gram-Schmidt) are one launch each over
 // all molecules, with per-molecule flags on the device, so the iteration is a
 // fixed sequence of launches (captured once as a HIP graph); the host reads one
@@ -25,12 +25,11 @@
 #include "batch.hpp"
 #include "wave.hpp"
 #include "fock_blocks.hpp"
-#include "jacobi.hpp"
 #include "linalg.hpp"
 
 namespace seqx {
 
-static_assert(kBatchMaxSub <= kJacobiMax, "the batched subspace must fit the LDS eigensolver");
+static_assert(kBatchMaxSub <= 64 && 2 * kBatchMaxRoots <= kEigBatchPairs, "range of the batched eigensolver");
 
 namespace {
 
@@ -251,7 +250,7 @@ __device__ double block_sum(double s, double* red) {  // 256 threads; fixed orde
 // (ties by flat index i*v + a), found by ng rounds of lexicographic minimum.
 __global__ void __launch_bounds__(256) guess_kernel(int nmol, const MolDesc* __restrict__ mols, int K,
                                                     double* __restrict__ Vp, int* S, int* knew, int* active, int* conv,
-                                                    int* coll, int* qcol, int* evn) {
+                                                    int* coll, int* qcol) {
   __shared__ double bg[256];
   __shared__ long bi[256];
   const int m = blockIdx.x;
@@ -300,7 +299,6 @@ __global__ void __launch_bounds__(256) guess_kernel(int nmol, const MolDesc* __r
     conv[m] = 0;
     coll[m] = 0;
     qcol[m] = 0;
-    evn[m] = 0;
   }
 }
 
@@ -447,86 +445,6 @@ __global__ void advance_kernel(int nmol, int* S, const int* __restrict__ knew, c
   if (m < nmol && active[m]) S[m] += knew[m];
 }
 
-// Symmetric eigensolve of the S x S projected matrix of each molecule
-// (Jacobi in LDS, jacobi.hpp).  Eigenvalues ascending in eval, eigenvectors
-// as columns of evec (ld Smax).  Warm start: the leading evn x evn block of M
-// is unchanged since the last eigensolve, whose eigenvectors are still in
-// evec, so M is first rotated into that basis (extended by the identity for
-// the new columns) and Jacobi continues from the nearly diagonal result,
-// accumulating onto the same basis.
-constexpr int kEigThreads = 256;  // measured faster than one wavefront per molecule
-
-__global__ void __launch_bounds__(kEigThreads) eig_kernel(int Smax, const double* __restrict__ Mp,
-                                                          const int* __restrict__ S, const int* __restrict__ active,
-                                                          int* __restrict__ evn, double* __restrict__ evec,
-                                                          double* __restrict__ eval) {
-  __shared__ JacobiLds L;
-  const int m = blockIdx.x;
-  if (!active[m]) return;
-  const int n = S[m];
-  const int p = min(evn[m], n);
-  const double* M = Mp + static_cast<long>(m) * Smax * Smax;
-  double* ev = evec + static_cast<long>(m) * Smax * Smax;
-  constexpr int kPer = (kJacobiMax * kJacobiMax + kEigThreads - 1) / kEigThreads;
-  for (int idx = threadIdx.x; idx < n * n; idx += kEigThreads) {
-    const int i = idx / n, j = idx % n;
-    L.A[i][j] = M[i + static_cast<long>(j) * Smax];
-    L.Q[i][j] = (i < p && j < p) ? ev[i + static_cast<long>(j) * Smax] : (i == j ? 1.0 : 0.0);
-  }
-  __syncthreads();
-  if (p > 0) {
-    // T = M Q (only the first p columns change), then A = Q^T T (only the first p rows change)
-    double t[kPer];
-#pragma unroll
-    for (int e = 0; e < kPer; ++e) {
-      const int idx = threadIdx.x + kEigThreads * e;
-      t[e] = 0.0;
-      if (idx < n * n) {
-        const int i = idx / n, j = idx % n;
-        if (j < p) {
-          for (int k = 0; k < p; ++k) t[e] += L.A[i][k] * L.Q[k][j];
-        } else {
-          t[e] = L.A[i][j];
-        }
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < kPer; ++e) {
-      const int idx = threadIdx.x + kEigThreads * e;
-      if (idx < n * n) L.A[idx / n][idx % n] = t[e];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < kPer; ++e) {
-      const int idx = threadIdx.x + kEigThreads * e;
-      t[e] = 0.0;
-      if (idx < n * n) {
-        const int i = idx / n, j = idx % n;
-        if (i < p) {
-          for (int k = 0; k < p; ++k) t[e] += L.Q[k][i] * L.A[k][j];
-        } else {
-          t[e] = L.A[i][j];
-        }
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < kPer; ++e) {
-      const int idx = threadIdx.x + kEigThreads * e;
-      if (idx < n * n) L.A[idx / n][idx % n] = t[e];
-    }
-    __syncthreads();
-  }
-  jacobi_lds<kEigThreads>(n, L, true);
-  for (int idx = threadIdx.x; idx < n * n; idx += kEigThreads) {
-    const int r = idx / n, i = idx % n;
-    ev[i + static_cast<long>(r) * Smax] = L.Q[i][L.perm[r]];
-  }
-  for (int r = threadIdx.x; r < n; r += kEigThreads) eval[static_cast<long>(m) * Smax + r] = L.A[L.perm[r]][L.perm[r]];
-  if (threadIdx.x == 0) evn[m] = n;
-}
-
 // Ritz vectors of molecule m, X_j = sum_s evec(s, j) V_s, and residuals
 // r_j = A X_j - w_j X_j into Wc, for all K roots in one pass over V and A V
 // (each basis element read once); block (m, c) takes chunk c of the nov
@@ -665,8 +583,7 @@ __global__ void __launch_bounds__(256) collapse_copy_kernel(const MolDesc* __res
                                                             const double* __restrict__ TAVp,
                                                             const double* __restrict__ eval, int* S, int* coll,
                                                             const int* __restrict__ qcol, double* __restrict__ Vp,
-                                                            double* __restrict__ AVp, double* __restrict__ Mp,
-                                                            int* __restrict__ evn) {
+                                                            double* __restrict__ AVp, double* __restrict__ Mp) {
   const int m = blockIdx.x, s = blockIdx.y;
   if (!coll[m]) return;
   const int q = qcol[m];
@@ -678,8 +595,7 @@ __global__ void __launch_bounds__(256) collapse_copy_kernel(const MolDesc* __res
       Vp[md.vbase + s * nov + x] = TVp[md.tbase + s * nov + x];
       AVp[md.vbase + s * nov + x] = TAVp[md.tbase + s * nov + x];
     }
-  } else {  // block s == q: the projected matrix (diagonal: no previous eigenvectors to start from)
-    if (threadIdx.x == 0) evn[m] = 0;
+  } else {  // block s == q: the projected matrix
     double* M = Mp + static_cast<long>(m) * Smax * Smax;
     for (int idx = threadIdx.x; idx < q * q; idx += 256) {
       const int i = idx / q, j = idx % q;
@@ -951,7 +867,7 @@ BatchResult batched_cis(const std::vector<DeviceMolecule*>& mols, const BatchOpt
 
   w.mols.ensure(nmol);
   w.order.ensure(nmol);
-  for (DBuf<int>* b : {&w.S, &w.knew, &w.active, &w.coll, &w.qcol, &w.conv, &w.evn}) b->ensure(nmol);
+  for (DBuf<int>* b : {&w.S, &w.knew, &w.active, &w.coll, &w.qcol, &w.conv}) b->ensure(nmol);
   w.unc.ensure(static_cast<size_t>(nmol) * K);
   w.counters.ensure(4);
   w.nsig.ensure(3);
@@ -1012,7 +928,7 @@ BatchResult batched_cis(const std::vector<DeviceMolecule*>& mols, const BatchOpt
     for (int m = 0; m < nmol; ++m) bucket[m] = bucket_of(h[m].n);
     upload_desc();
     hipLaunchKernelGGL(guess_kernel, dim3(nmol), dim3(256), 0, st, nmol, w.mols.p, K, w.V.p, w.S.p, w.knew.p,
-                       w.active.p, w.conv.p, w.coll.p, w.qcol.p, w.evn.p);
+                       w.active.p, w.conv.p, w.coll.p, w.qcol.p);
     SEQX_LAUNCH_CHECK();
     const auto ta0 = std::chrono::steady_clock::now();
     for (int b = 0; b < kNumSizeBuckets; ++b) {
@@ -1059,6 +975,14 @@ BatchResult batched_cis(const std::vector<DeviceMolecule*>& mols, const BatchOpt
 
     // ---- one iteration as a fixed launch sequence
     const int Q = 2 * K;
+    // The projected eigenproblems: K pairs, and the 2K of a collapse where the
+    // new directions may not fit.  One Jacobi solve of all pairs in LDS, started
+    // from the previous vectors, took 430 us an iteration however few molecules
+    // were left; the lowest pairs by reduction and inverse iteration take 205 (65
+    // + 100 + 40) with all 512 molecules or few.  Their
+    // scratch is the partial inner products' (free between project and gs_dots).
+    const EigBatch eig{Smax, K, Q, static_cast<long>(kXChunks) * kPartStride, w.S.p, w.active.p,
+                       w.Mp.p, w.evec.p, w.eval.p, w.part.p};
     auto iteration = [&](bool timed) {
       hipLaunchKernelGGL(items_kernel, dim3(1), dim3(256), 0, st, nmol, w.mols.p, w.order.p, w.S.p, w.knew.p,
                          w.active.p, w.items.p, w.counters.p, w.nsig.p);
@@ -1070,8 +994,7 @@ BatchResult batched_cis(const std::vector<DeviceMolecule*>& mols, const BatchOpt
                          w.active.p);
       hipLaunchKernelGGL(advance_kernel, dim3(ceil_div(nmol, 256)), dim3(256), 0, st, nmol, w.S.p, w.knew.p,
                          w.active.p);
-      hipLaunchKernelGGL(eig_kernel, dim3(nmol), dim3(kEigThreads), 0, st, Smax, w.Mp.p, w.S.p, w.active.p,
-                         w.evn.p, w.evec.p, w.eval.p);
+      launch_eig_batch(st, nmol, eig);
       hipLaunchKernelGGL(ritz_kernel, dim3(nmol, kXChunks), dim3(256), 0, st, w.mols.p, K, Smax, w.V.p, w.AV.p,
                          w.evec.p, w.eval.p, w.S.p, w.active.p, w.X.p, w.Wc.p, w.omega.p, w.rpart.p);
       hipLaunchKernelGGL(select_kernel, dim3(1), dim3(256), 0, st, nmol, K, Smax, opt.tol, w.rpart.p, w.rnorm.p,
@@ -1079,7 +1002,7 @@ BatchResult batched_cis(const std::vector<DeviceMolecule*>& mols, const BatchOpt
       hipLaunchKernelGGL(collapse_kernel, dim3(nmol, Q), dim3(256), 0, st, w.mols.p, Smax, w.V.p, w.AV.p, w.evec.p,
                          w.S.p, w.coll.p, w.qcol.p, w.TV.p, w.TAV.p);
       hipLaunchKernelGGL(collapse_copy_kernel, dim3(nmol, Q + 1), dim3(256), 0, st, w.mols.p, Smax, w.TV.p, w.TAV.p,
-                         w.eval.p, w.S.p, w.coll.p, w.qcol.p, w.V.p, w.AV.p, w.Mp.p, w.evn.p);
+                         w.eval.p, w.S.p, w.coll.p, w.qcol.p, w.V.p, w.AV.p, w.Mp.p);
       const dim3 chunks(nmol, kXChunks);
       hipLaunchKernelGGL(precond_kernel, chunks, dim3(256), 0, st, w.mols.p, K, w.Wc.p, w.knew.p, w.active.p,
                          w.unc.p, w.omega.p, w.n0.p);

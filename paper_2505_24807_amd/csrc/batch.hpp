@@ -36,7 +36,7 @@ struct MolDesc {
   const Elem* elems;
 };
 
-constexpr int kBatchMaxSub = 48;    // subspace cap per molecule (the eigensolve holds it in LDS)
+constexpr int kBatchMaxSub = 48;    // subspace cap per molecule (Gram-Schmidt and the Ritz step hold its coefficients in LDS)
 constexpr int kBatchMaxNp = 1536;   // packed pair indices per molecule (Coulomb step holds them in LDS)
 constexpr int kBatchMaxRoots = 16;
 constexpr int kNumTileVariants = 3; // (TM, TN) = (1, 1), (2, 1), (2, 2) MFMA 16x16 tiles per wave
@@ -74,7 +74,6 @@ struct BatchResult {
 struct BatchWork {
   DBuf<MolDesc> mols;
   DBuf<int> order, S, knew, active, coll, qcol, unc, conv, counters;
-  DBuf<int> evn;           // leading block of each molecule's M whose eigenvectors are in evec (0: none)
   DBuf<int2> items;
   DBuf<long long> nsig;    // [0] sigma vectors, [1] wall-clock ticks inside sigma launches, [2] flops
   DBuf<long long> stamps;  // start / end tick of each workgroup of the last sigma launch

@@ -101,10 +101,8 @@ __device__ __forceinline__ unsigned long long peek(const double* p) {
 // scope; no counter, no ordering between values).  The grid is at most 128
 // single-wavefront workgroups, which are resident together.
 template <int NC, int NR, int NW, bool GRID>
-__global__ void __launch_bounds__(GRID ? 64 : 64 * NW) tridiag_kernel(int n, const double* __restrict__ A, int lda,
-                                                                      double* __restrict__ W,
-                                                                      double* __restrict__ dte, double* xch,
-                                                                      int* failed) {
+__device__ __forceinline__ void tridiagonalise(int n, const double* __restrict__ A, int lda, double* __restrict__ W,
+                                               double* __restrict__ dte, double* xch, int* failed) {
   static_assert(NW * NR >= 64 * NC, "rows must be covered");
   __shared__ double sp[2][GRID ? 1 : 64 * NC], sy[2][GRID ? 1 : 64 * NC];
   const int lane = threadIdx.x & 63;
@@ -280,6 +278,14 @@ __global__ void __launch_bounds__(GRID ? 64 : 64 * NW) tridiag_kernel(int n, con
       if (wave + NW * k == n - 1 && lane + 64 * c == n - 1) dd[n - 1] = a[k][c];
 }
 
+template <int NC, int NR, int NW, bool GRID>
+__global__ void __launch_bounds__(GRID ? 64 : 64 * NW) tridiag_kernel(int n, const double* __restrict__ A, int lda,
+                                                                      double* __restrict__ W,
+                                                                      double* __restrict__ dte, double* xch,
+                                                                      int* failed) {
+  tridiagonalise<NC, NR, NW, GRID>(n, A, lda, W, dte, xch, failed);
+}
+
 // ---------------------------------------------------------------- 2. eigenpairs of T
 
 // number of eigenvalues of T (d, e2 = e^2) below x: the sign changes of the
@@ -320,16 +326,13 @@ __device__ int sturm_count(int n, const double* d, const double* e2, double x) {
 // instructions, and 512 points took twice the time for one round less in seven
 constexpr int kPairThreads = 256;
 
-// eigenpair blockIdx.x: lam[t], Z[t * n ..]; workgroup 0 also stores |T|
+// eigenpair tt: lam[tt], Z[tt * n ..]; the workgroup of pair 0 also stores |T|
 template <int NC>
-__global__ void __launch_bounds__(kPairThreads) tridiag_pair_kernel(int n, const double* __restrict__ dte,
-                                                                    double* __restrict__ lam,
-                                                                    double* __restrict__ Z,
-                                                                    double* __restrict__ norm) {
+__device__ __forceinline__ void tridiag_pair(int tt, int n, const double* __restrict__ dte, double* __restrict__ lam,
+                                             double* __restrict__ Z, double* __restrict__ norm) {
   __shared__ double d[64 * NC], e2[64 * NC];  // e2[i] = e_{i-1}^2
   __shared__ int first[2][kPairThreads / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int tt = blockIdx.x;
   double dr[NC], er[NC];  // d_i and e_i of rows lane + 64 c (e_{n-1} = 0)
   double lo = 1e300, hi = -1e300;
 #pragma unroll
@@ -476,6 +479,14 @@ __global__ void __launch_bounds__(kPairThreads) tridiag_pair_kernel(int n, const
     if (lane + 64 * c < n) Z[static_cast<long>(tt) * n + lane + 64 * c] = y[c];
 }
 
+template <int NC>
+__global__ void __launch_bounds__(kPairThreads) tridiag_pair_kernel(int n, const double* __restrict__ dte,
+                                                                    double* __restrict__ lam,
+                                                                    double* __restrict__ Z,
+                                                                    double* __restrict__ norm) {
+  tridiag_pair<NC>(blockIdx.x, n, dte, lam, Z, norm);
+}
+
 // ---------------------------------------------------------------- 3. clusters
 
 constexpr int kClusterThreads = 1024;
@@ -485,11 +496,11 @@ constexpr int kClusterLds = 16384;  // eigenvector elements staged in LDS
 // 1e-3 |T|): vector t against the cluster members s < t, in order of t, two
 // classical Gram-Schmidt passes (one wavefront per inner product).  Vectors
 // are staged in LDS when they fit, else stay in memory.
-template <bool STAGED>
-__global__ void __launch_bounds__(kClusterThreads) cluster_kernel(int n, int k, const double* __restrict__ lam,
-                                                                  const double* __restrict__ norm, double* Z) {
-  __shared__ double stage[STAGED ? kClusterLds : 1];
-  __shared__ double red[512];
+template <bool STAGED, int NT, int LDS, int KMAX>
+__device__ __forceinline__ void orthogonalise_clusters(int n, int k, const double* __restrict__ lam,
+                                                       const double* __restrict__ norm, double* Z) {
+  __shared__ double stage[STAGED ? LDS : 1];
+  __shared__ double red[KMAX];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const double gap = 1e-3 * *norm;
   // eigenvalues ascend: without a close pair of neighbours there is no cluster
@@ -498,7 +509,7 @@ __global__ void __launch_bounds__(kClusterThreads) cluster_kernel(int n, int k, 
   if (!any) return;
   double* V = STAGED ? stage : Z;
   if (STAGED) {
-    for (int x = tid; x < k * n; x += kClusterThreads) stage[x] = Z[x];
+    for (int x = tid; x < k * n; x += NT) stage[x] = Z[x];
     __syncthreads();
   }
   for (int t = 1; t < k; ++t) {
@@ -507,7 +518,7 @@ __global__ void __launch_bounds__(kClusterThreads) cluster_kernel(int n, int k, 
     if (s0 == t) continue;
     double* vt = V + static_cast<long>(t) * n;
     for (int pass = 0; pass < 2; ++pass) {
-      for (int s = s0 + wave; s < t; s += kClusterThreads / 64) {
+      for (int s = s0 + wave; s < t; s += NT / 64) {
         const double* vs = V + static_cast<long>(s) * n;
         double dot = 0.0;
         for (int i = lane; i < n; i += 64) dot += vs[i] * vt[i];
@@ -526,14 +537,20 @@ __global__ void __launch_bounds__(kClusterThreads) cluster_kernel(int n, int k, 
       double nr = 0.0;
       for (int i = lane; i < n; i += 64) nr += vt[i] * vt[i];
       nr = wave_sum64(nr);
-      if (lane == 0) red[511] = 1.0 / sqrt(nr);
+      if (lane == 0) red[KMAX - 1] = 1.0 / sqrt(nr);
     }
     __syncthreads();
-    if (tid < n) vt[tid] *= red[511];
+    if (tid < n) vt[tid] *= red[KMAX - 1];
     __syncthreads();
   }
   if (STAGED)
-    for (int x = tid; x < k * n; x += kClusterThreads) Z[x] = stage[x];
+    for (int x = tid; x < k * n; x += NT) Z[x] = stage[x];
+}
+
+template <bool STAGED>
+__global__ void __launch_bounds__(kClusterThreads) cluster_kernel(int n, int k, const double* __restrict__ lam,
+                                                                  const double* __restrict__ norm, double* Z) {
+  orthogonalise_clusters<STAGED, kClusterThreads, kClusterLds, 512>(n, k, lam, norm, Z);
 }
 
 // ---------------------------------------------------------------- 4. y = Q z
@@ -543,12 +560,10 @@ __global__ void __launch_bounds__(kClusterThreads) cluster_kernel(int n, int k, 
 // a pair costs the latency of one.  The next four reflectors are loaded while
 // four are applied.
 template <int NC>
-__global__ void __launch_bounds__(64) reflect_kernel(int n, int lda, const double* __restrict__ W,
-                                                     const double* __restrict__ tau,
-                                                     const double* __restrict__ lam, const double* __restrict__ Z,
-                                                     double* __restrict__ A, double* __restrict__ w,
-                                                     const int* __restrict__ failed, int* __restrict__ info) {
-  const int lane = threadIdx.x, tt = blockIdx.x;
+__device__ __forceinline__ void reflect(int tt, int n, int lda, const double* __restrict__ W,
+                                        const double* __restrict__ tau, const double* __restrict__ Z,
+                                        double* __restrict__ A) {
+  const int lane = threadIdx.x & 63;
   double z[NC], tr[NC];
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
@@ -595,10 +610,66 @@ __global__ void __launch_bounds__(64) reflect_kernel(int n, int lda, const doubl
     const int i = lane + 64 * c;
     if (i < n) A[static_cast<long>(tt) * lda + i] = z[c];
   }
-  if (lane == 0) {
+}
+
+template <int NC>
+__global__ void __launch_bounds__(64) reflect_kernel(int n, int lda, const double* __restrict__ W,
+                                                     const double* __restrict__ tau,
+                                                     const double* __restrict__ lam, const double* __restrict__ Z,
+                                                     double* __restrict__ A, double* __restrict__ w,
+                                                     const int* __restrict__ failed, int* __restrict__ info) {
+  const int tt = blockIdx.x;
+  reflect<NC>(tt, n, lda, W, tau, Z, A);
+  if (threadIdx.x == 0) {
     w[tt] = lam[tt];
     if (tt == 0) info[0] = failed ? *failed : 0;
   }
+}
+
+// ---------------------------------------------------------------- many problems
+
+// Scratch of one problem of a batch: reflectors, eigenvectors of T, (d, tau, e), eigenvalues and |T|.
+struct BatchScratch {
+  double *W, *Z, *dte, *lam, *norm;
+  __device__ BatchScratch(const EigBatch& b, int m) {
+    W = b.scratch + static_cast<long>(m) * b.scratch_stride;
+    Z = W + b.ld * b.ld;
+    dte = Z + b.kcap * b.ld;
+    lam = dte + 3 * b.ld;
+    norm = lam + b.kcap;
+  }
+};
+
+__device__ __forceinline__ int batch_pairs(const EigBatch& b, int n) {
+  return min(n, n + b.kfew > b.ld ? b.kcap : b.kfew);
+}
+
+__global__ void __launch_bounds__(512) batch_tridiag_kernel(EigBatch b) {
+  const int m = blockIdx.x;
+  if (!b.active[m]) return;
+  const BatchScratch s(b, m);
+  tridiagonalise<1, 8, 8, false>(b.n[m], b.A + static_cast<long>(m) * b.ld * b.ld, b.ld, s.W, s.dte, nullptr, nullptr);
+}
+
+__global__ void __launch_bounds__(kPairThreads) batch_pair_kernel(EigBatch b) {
+  const int m = blockIdx.x, t = blockIdx.y;
+  if (!b.active[m] || t >= batch_pairs(b, b.n[m])) return;
+  const BatchScratch s(b, m);
+  tridiag_pair<1>(t, b.n[m], s.dte, s.lam, s.Z, s.norm);
+}
+
+// clusters, then y = Q z, one wavefront per vector
+__global__ void __launch_bounds__(256) batch_vectors_kernel(EigBatch b) {
+  const int m = blockIdx.x;
+  if (!b.active[m]) return;
+  const BatchScratch s(b, m);
+  const int n = b.n[m], k = batch_pairs(b, n);
+  orthogonalise_clusters<true, 256, kEigBatchPairs * 64, kEigBatchPairs + 1>(n, k, s.lam, s.norm, s.Z);
+  __syncthreads();  // orders the workgroup's own stores to Z
+  double* out = b.vec + static_cast<long>(m) * b.ld * b.ld;
+  for (int t = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); t < k; t += 4)
+    reflect<1>(t, n, b.ld, s.W, s.dte + 2 * n, s.Z, out);
+  for (int t = threadIdx.x; t < k; t += 256) b.val[static_cast<long>(m) * b.ld + t] = s.lam[t];
 }
 
 // scratch layout (doubles)
@@ -645,6 +716,20 @@ void launch_tridiag(hipStream_t st, int n, const double* A, int lda, const EigSc
 }
 
 }  // namespace
+
+size_t eig_batch_scratch(int ld, int kcap) {
+  return static_cast<size_t>(ld) * ld + static_cast<size_t>(kcap) * ld + 3 * static_cast<size_t>(ld) + kcap + 1;
+}
+
+void launch_eig_batch(hipStream_t st, int nprob, const EigBatch& b) {
+  if (b.ld > 64 || b.kcap > kEigBatchPairs || b.kfew > b.kcap ||
+      static_cast<size_t>(b.scratch_stride) < eig_batch_scratch(b.ld, b.kcap))
+    throw Error(kEArg, "eigenproblem batch out of range");
+  hipLaunchKernelGGL(batch_tridiag_kernel, dim3(nprob), dim3(512), 0, st, b);
+  hipLaunchKernelGGL(batch_pair_kernel, dim3(nprob, b.kcap), dim3(kPairThreads), 0, st, b);
+  hipLaunchKernelGGL(batch_vectors_kernel, dim3(nprob), dim3(256), 0, st, b);
+  SEQX_LAUNCH_CHECK();
+}
 
 size_t eig_lowest_scratch(int n, int k) {
   return static_cast<size_t>(n) * n + static_cast<size_t>(n) * k + 3 * static_cast<size_t>(n) + k + 2 +

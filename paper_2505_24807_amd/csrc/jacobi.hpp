@@ -1,8 +1,7 @@
 // Symmetric eigensolver for small matrices held in LDS by one workgroup of
 // NT threads (a power of two, at most 256): cyclic Jacobi with the round-robin (tournament) ordering, so each
 // round rotates ne/2 disjoint index pairs at once (rows, then columns), with
-// ne = n rounded up to even.  Used for the subspace problems of the batched
-// solver and for the small Gram and collapse matrices of the single-molecule
+// ne = n rounded up to even.  Used for the small Gram and collapse matrices of the single-molecule
 // solver.
 #pragma once
 
@@ -23,22 +22,18 @@ struct JacobiLds {
   double red[256];
 };
 
-// On entry L.A holds the symmetric n x n matrix (n <= kJacobiMax) and, with
-// q_given, L.Q an orthogonal matrix that the rotations accumulate onto
-// (otherwise the identity).  On exit L.Q holds the eigenvectors as columns, diag(L.A) the eigenvalues, and
+// On entry L.A holds the symmetric n x n matrix (n <= kJacobiMax).  On exit L.Q holds the eigenvectors as columns, diag(L.A) the eigenvalues, and
 // L.perm the ascending order of the eigenvalues.  Sweeps stop when the
 // off-diagonal sum of squares is below 1e-28 of the total (elements ~1e-14 of
 // the largest; FP64 rounding keeps the sum near n * 1e-32 of the total) or
 // after 40 sweeps.
 template <int NT>
-__device__ inline void jacobi_lds(int n, JacobiLds& L, bool q_given = false) {
-  if (!q_given) {
-    for (int idx = threadIdx.x; idx < n * n; idx += NT) {
-      const int i = idx / n, j = idx % n;
-      L.Q[i][j] = (i == j) ? 1.0 : 0.0;
-    }
-    __syncthreads();
+__device__ inline void jacobi_lds(int n, JacobiLds& L) {
+  for (int idx = threadIdx.x; idx < n * n; idx += NT) {
+    const int i = idx / n, j = idx % n;
+    L.Q[i][j] = (i == j) ? 1.0 : 0.0;
   }
+  __syncthreads();
   const int ne = n + (n & 1), half = ne / 2;
   if (threadIdx.x == 0) L.nact = 0;  // seen by all after the first barrier of the sweep
   for (int sweep = 0; sweep < 40; ++sweep) {

@@ -19,6 +19,22 @@ constexpr int kEigOneGroup = 128;
 // and w; reads the lower triangle.  scratch holds eig_lowest_scratch(n, k) doubles.
 size_t eig_lowest_scratch(int n, int k);
 void launch_eig_lowest(hipStream_t st, int n, double* A, int lda, int k, double* w, double* scratch, int* info);
+// The lowest eigenpairs of many small problems (eig_lowest.hip), one workgroup
+// each for the reduction and one for every pair: problem m (of order n[m] <= ld
+// <= 64, where active[m]) reads the lower triangle of A + m ld^2 and writes its
+// min(n, kfew) lowest pairs to val + m ld and to columns of vec + m ld^2, or
+// min(n, kcap) pairs where n + kfew > ld.  scratch_stride >=
+// eig_batch_scratch(ld, kcap) doubles of scratch a problem.
+constexpr int kEigBatchPairs = 32;  // largest kcap
+struct EigBatch {
+  int ld, kfew, kcap;
+  long scratch_stride;
+  const int *n, *active;
+  const double* A;
+  double *vec, *val, *scratch;
+};
+size_t eig_batch_scratch(int ld, int kcap);
+void launch_eig_batch(hipStream_t st, int nprob, const EigBatch& b);
 // lower Cholesky in one workgroup (small_dense.hip)
 void launch_small_potrf(hipStream_t st, int n, double* A, int lda, int* info);
 

@@ -152,3 +152,31 @@ def test_ground_states_do_not_depend_on_the_batch(ctx):
             assert np.array_equal(x, y)
         alone.free()
     job.free()
+
+
+# subspaces from 1 row (H2: one pair) to the cap of 48, all pairs wanted (water, 8 of 8) and few of many
+@pytest.mark.parametrize("k, mols", [(1, [molecules.h2(), molecules.water_cluster(1, 1), molecules.ethylene()]),
+                                     (8, [molecules.water_cluster(1, 1), molecules.ethylene(),
+                                          _noisy(molecules.polyene(6), 6)]),
+                                     (16, [molecules.ethylene(), molecules.water_cluster(3, 3),
+                                           _noisy(molecules.polyene(6), 6)])])
+def test_subspace_sizes_of_a_batch(ctx, k, mols):
+    """Batched CIS roots against dense diagonalisation: the lowest ones, but for ethylene, whose symmetry keeps a root
+    apart from every vector of the gap guess (any k of its dense roots then)."""
+    print(f"[gpu] batch roots k={k}", flush=True)
+    job = ctx.prepare(*molecules.concat(mols))
+    job.solve(theory=seqx.CIS, nroots=k, tol=1e-8, max_iter=300, batched=True)
+    for m, mol in enumerate(mols):
+        n, o, v = job.dims(m)
+        sy = model.make_system(mol.Z, mol.xyz, PR)
+        ints = integrals.build(sy)
+        res = scf.run(sy, ints)
+        A, _ = excited.build_AB(ints, res.eps, res.C, o)
+        got = job.results(m).omega_eV
+        ref = excited.cis_dense(A, o * v, o, v).omega * model.HARTREE_EV
+        if mol.name == molecules.ethylene().name:
+            near = np.abs(got[:, None] - ref[None, :]).argmin(1)
+            assert len(set(near)) == k
+            ref = ref[near]
+        assert np.abs(got - ref[:k]).max() <= 1e-8
+    job.free()
