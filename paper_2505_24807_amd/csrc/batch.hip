@@ -21,6 +21,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
+#include <type_traits>
 
 #include "batch.hpp"
 #include "wave.hpp"
@@ -348,42 +349,104 @@ __global__ void __launch_bounds__(256) items_kernel(int nmol, const MolDesc* __r
   }
 }
 
-// Subspace steps of a molecule are split over kXChunks blocks along the nov
-// entries, so that the largest molecules spread over several CUs; partial
+// Subspace steps of a molecule are split over blocks along its nov entries, so
+// that the largest molecules spread over several CUs: chunks of about 256
+// entries (one a thread in the row combinations), at most kXChunks.  Partial
 // inner products go to per-chunk slots and are summed in a fixed order.
 constexpr int kXChunks = 8;
 constexpr int kPartStride = kBatchMaxSub * 2 * kBatchMaxRoots;  // one chunk's [s][j] partials
 
-__device__ __forceinline__ long chunk_begin(long nov, int ch) { return nov * ch / kXChunks; }
+__device__ __forceinline__ int chunks_of(long nov) {
+  return static_cast<int>(min(static_cast<long>(kXChunks), (nov + 255) / 256));
+}
+__device__ __forceinline__ long chunk_begin(long nov, int ch) {
+  const int nch = chunks_of(nov);
+  const long len = ((nov + nch - 1) / nch + 15) / 16 * 16;
+  return min(nov, len * ch);
+}
 
-// Inner products over x in [x0, x1) of up to 16 vectors b_u (nb of them) with
-// the rows s0, s0 + 1 of V (rows past ns repeat the last), one wavefront: each
-// V element is read once, the b_u stay in L1/L2.  Results in every lane: d[i][u].
-__device__ __forceinline__ void wave_dots2x16(const double* __restrict__ V, long nov, int s0, int ns, long x0,
-                                              long x1, const double* const* b, int nb,
-                                              double (*d)[kBatchMaxRoots]) {
-  const int lane = threadIdx.x & 63;
-  const double* a0 = V + static_cast<long>(min(s0, ns - 1)) * nov;
-  const double* a1 = V + static_cast<long>(min(s0 + 1, ns - 1)) * nov;
-  double acc[2][kBatchMaxRoots];
+struct __attribute__((packed, aligned(8))) Row4 {  // four row elements at any element offset
+  double v[4];
+};
+
+constexpr int kSubTiles = (kBatchMaxSub + 15) / 16;
+struct DotsLds {
+  double part[4][kSubTiles][16][17];
+};
+
+// P[s * 2 kBatchMaxRoots + u] = sum over x in [x0, x1) of V_s[x] b_u[x] for s <
+// ns, u < nb <= 16, one workgroup of 4 wavefronts.  b is this lane's column
+// (that of u = lane & 15, any valid row for u >= nb).  The products are 16 x 16
+// tiles of the FP64 matrix cores, so nothing is summed across lanes and every
+// element of V is read once; a lane takes four neighbouring elements of its row
+// and the k index of the tile is permuted alike on both sides.  (One wavefront
+// per two rows with a lane sum for each product: 325 us for the two passes of a
+// Gram-Schmidt step over 512 molecules with 20 rows, here 89.)
+__device__ __forceinline__ void chunk_dots(const double* __restrict__ V, long nov, int ns,
+                                           const double* __restrict__ b, int nb, long x0, long x1,
+                                           double* __restrict__ P, DotsLds& L) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r16 = lane & 15, k4 = lane >> 4, nt = (ns + 15) / 16;
+  const long len = (x1 - x0 + 63) / 64 * 16, xa = x0 + wave * len, xb = min(x1, xa + len);
+  const double* row[kSubTiles];
+  d4 acc[kSubTiles];
 #pragma unroll
-  for (int u = 0; u < kBatchMaxRoots; ++u) acc[0][u] = acc[1][u] = 0.0;
-  for (long x = x0 + lane; x < x1; x += 64) {
-    const double v0 = a0[x], v1 = a1[x];
-#pragma unroll
-    for (int u = 0; u < kBatchMaxRoots; ++u)
-      if (u < nb) {
-        const double bx = b[u][x];
-        acc[0][u] += v0 * bx;
-        acc[1][u] += v1 * bx;
-      }
+  for (int t = 0; t < kSubTiles; ++t) {
+    row[t] = V + static_cast<long>(min(16 * t + r16, ns - 1)) * nov;
+    acc[t] = d4{0, 0, 0, 0};
   }
+  for (long x = xa; x < xb; x += 16) {
+    const long xl = x + 4 * k4;
+    Row4 bv, av[kSubTiles];
+    if (x + 16 <= xb) {
+      bv = *reinterpret_cast<const Row4*>(b + xl);
 #pragma unroll
-  for (int u = 0; u < kBatchMaxRoots; ++u)
-    if (u < nb) {
-      d[0][u] = wave_sum(acc[0][u]);
-      d[1][u] = wave_sum(acc[1][u]);
+      for (int t = 0; t < kSubTiles; ++t)
+        if (t < nt) av[t] = *reinterpret_cast<const Row4*>(row[t] + xl);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        bv.v[i] = xl + i < xb ? b[xl + i] : 0.0;
+#pragma unroll
+        for (int t = 0; t < kSubTiles; ++t)
+          if (t < nt) av[t].v[i] = xl + i < xb ? row[t][xl + i] : 0.0;
+      }
     }
+#pragma unroll
+    for (int t = 0; t < kSubTiles; ++t)
+      if (t < nt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[t] = WgMfma<double>::op(av[t].v[i], bv.v[i], acc[t]);
+  }
+  __syncthreads();  // L may still be read from the previous call
+#pragma unroll
+  for (int t = 0; t < kSubTiles; ++t)
+    if (t < nt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) L.part[wave][t][WgMfma<double>::row(lane, r)][r16] = acc[t][r];
+  __syncthreads();
+  for (int idx = threadIdx.x; idx < 16 * ns; idx += 256) {
+    const int sidx = idx >> 4, u = idx & 15, t = sidx >> 4, i = sidx & 15;
+    if (u < nb)
+      P[sidx * 2 * kBatchMaxRoots + u] =
+          (L.part[0][t][i][u] + L.part[1][t][i][u]) + (L.part[2][t][i][u] + L.part[3][t][i][u]);
+  }
+}
+
+// acc[j] = sum_s c[s][j] row_s[x] over n rows (ld nov), four rows' loads ahead
+// of their products; c is zero-padded to a multiple of four rows
+template <int NR>
+__device__ __forceinline__ void combine_at(const double* __restrict__ rows, long nov, int n, long x,
+                                           const double (*c)[NR], double (&acc)[NR]) {
+  for (int s0 = 0; s0 < n; s0 += 4) {
+    double v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = rows[min(s0 + q, n - 1) * nov + x];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int j = 0; j < NR; ++j) acc[j] += c[s0 + q][j] * v[q];
+  }
 }
 
 // New columns of M = V^T A V, first half: block (m, c) forms the partial
@@ -394,35 +457,25 @@ __global__ void __launch_bounds__(256) project_part_kernel(const MolDesc* __rest
                                                            const double* __restrict__ AVp, const int* __restrict__ S,
                                                            const int* __restrict__ knew,
                                                            const int* __restrict__ active, double* __restrict__ part) {
+  __shared__ DotsLds L;
   const int m = blockIdx.x, ch = blockIdx.y;
   if (!active[m]) return;
   const MolDesc md = mols[m];
-  const long nov = md.nov, x0 = chunk_begin(nov, ch), x1 = chunk_begin(nov, ch + 1);
-  const int S0 = S[m], kn = knew[m], ns = S0 + kn;
-  const double* V = Vp + md.vbase;
+  const long nov = md.nov;
+  if (ch >= chunks_of(nov)) return;
+  const int S0 = S[m], kn = knew[m];
   double* P = part + (static_cast<long>(m) * kXChunks + ch) * kPartStride;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int j0 = 0; j0 < kn; j0 += kBatchMaxRoots) {
-    const int nb = min(kBatchMaxRoots, kn - j0);
-    const double* b[kBatchMaxRoots];
-#pragma unroll
-    for (int u = 0; u < kBatchMaxRoots; ++u) b[u] = AVp + md.vbase + static_cast<long>(S0 + j0 + min(u, nb - 1)) * nov;
-    for (int s0 = 2 * wave; s0 < ns; s0 += 8) {
-      double d[2][kBatchMaxRoots];
-      wave_dots2x16(V, nov, s0, ns, x0, x1, b, nb, d);
-      if (lane == 0)
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int u = 0; u < kBatchMaxRoots; ++u)
-            if (u < nb && s0 + i < ns) P[(s0 + i) * 2 * kBatchMaxRoots + j0 + u] = d[i][u];
-    }
+  for (int j0 = 0; j0 < kn; j0 += 16) {
+    const int nb = min(16, kn - j0);
+    const double* b = AVp + md.vbase + static_cast<long>(S0 + j0 + min(static_cast<int>(threadIdx.x & 15), nb - 1)) * nov;
+    chunk_dots(Vp + md.vbase, nov, S0 + kn, b, nb, chunk_begin(nov, ch), chunk_begin(nov, ch + 1), P + j0, L);
   }
 }
 
 // Second half: sum the chunks in order and write both triangles of the new
 // columns (column-major, ld Smax).  S is advanced by advance_kernel afterwards.
-__global__ void __launch_bounds__(256) project_kernel(int Smax, const double* __restrict__ part,
+__global__ void __launch_bounds__(256) project_kernel(const MolDesc* __restrict__ mols, int Smax,
+                                                      const double* __restrict__ part,
                                                       double* __restrict__ Mp, const int* __restrict__ S,
                                                       const int* __restrict__ knew, const int* __restrict__ active) {
   const int m = blockIdx.x;
@@ -430,11 +483,12 @@ __global__ void __launch_bounds__(256) project_kernel(int Smax, const double* __
   const int S0 = S[m], kn = knew[m], ns = S0 + kn;
   double* M = Mp + static_cast<long>(m) * Smax * Smax;
   const double* P = part + static_cast<long>(m) * kXChunks * kPartStride;
+  const int nch = chunks_of(mols[m].nov);
   for (int idx = threadIdx.x; idx < ns * kn; idx += 256) {
     const int sidx = idx / kn, jn = idx % kn, j = S0 + jn;
     if (sidx > j) continue;
     double d = 0.0;
-    for (int c = 0; c < kXChunks; ++c) d += P[c * kPartStride + sidx * 2 * kBatchMaxRoots + jn];
+    for (int c = 0; c < nch; ++c) d += P[c * kPartStride + sidx * 2 * kBatchMaxRoots + jn];
     M[sidx + static_cast<long>(j) * Smax] = d;
     M[j + static_cast<long>(sidx) * Smax] = d;
   }
@@ -446,52 +500,43 @@ __global__ void advance_kernel(int nmol, int* S, const int* __restrict__ knew, c
 }
 
 // Ritz vectors of molecule m, X_j = sum_s evec(s, j) V_s, and residuals
-// r_j = A X_j - w_j X_j into Wc, for all K roots in one pass over V and A V
+// r_j = A X_j - w_j X_j into Wc, for all K <= NR roots in one pass over V and A V
 // (each basis element read once); block (m, c) takes chunk c of the nov
 // entries and leaves its partial sums of |r_j|^2 in rpart[m][c][j].
+template <int NR>
 __global__ void __launch_bounds__(256) ritz_kernel(const MolDesc* __restrict__ mols, int K, int Smax,
                                                    const double* __restrict__ Vp, const double* __restrict__ AVp,
                                                    const double* __restrict__ evec, const double* __restrict__ eval,
                                                    const int* __restrict__ S, const int* __restrict__ active,
                                                    double* __restrict__ Xp, double* __restrict__ Wcp,
                                                    double* __restrict__ omega, double* __restrict__ rpart) {
-  __shared__ double c[kBatchMaxRoots][kBatchMaxSub];
-  __shared__ double wr[kBatchMaxRoots];
-  __shared__ double red[4][kBatchMaxRoots];
+  __shared__ double c[kBatchMaxSub][NR];
+  __shared__ double wr[NR];
+  __shared__ double red[4][NR];
   const int m = blockIdx.x, ch = blockIdx.y;
   if (!active[m]) return;
   const MolDesc md = mols[m];
   const long nov = md.nov;
+  if (ch >= chunks_of(nov)) return;
   const int n = S[m];
-  for (int idx = threadIdx.x; idx < K * n; idx += 256) {
-    const int j = idx / n, sidx = idx % n;
-    c[j][sidx] = evec[static_cast<long>(m) * Smax * Smax + sidx + static_cast<long>(j) * Smax];
+  for (int idx = threadIdx.x; idx < kBatchMaxSub * NR; idx += 256) {
+    const int sidx = idx / NR, j = idx % NR;
+    c[sidx][j] = (sidx < n && j < K) ? evec[static_cast<long>(m) * Smax * Smax + sidx + static_cast<long>(j) * Smax] : 0.0;
   }
-  if (threadIdx.x < K) wr[threadIdx.x] = eval[static_cast<long>(m) * Smax + threadIdx.x];
+  if (threadIdx.x < NR) wr[threadIdx.x] = threadIdx.x < K ? eval[static_cast<long>(m) * Smax + threadIdx.x] : 0.0;
   __syncthreads();
-  const double* V = Vp + md.vbase;
-  const double* AV = AVp + md.vbase;
   double* X = Xp + md.xbase;
   double* Wc = Wcp + md.xbase;
   const long x0 = chunk_begin(nov, ch), x1 = chunk_begin(nov, ch + 1);
-  double ss[kBatchMaxRoots];
+  double ss[NR];
 #pragma unroll
-  for (int j = 0; j < kBatchMaxRoots; ++j) ss[j] = 0.0;
+  for (int j = 0; j < NR; ++j) ss[j] = 0.0;
   for (long x = x0 + threadIdx.x; x < x1; x += 256) {
-    double xv[kBatchMaxRoots], av[kBatchMaxRoots];
+    double xv[NR] = {}, av[NR] = {};
+    combine_at<NR>(Vp + md.vbase, nov, n, x, c, xv);
+    combine_at<NR>(AVp + md.vbase, nov, n, x, c, av);
 #pragma unroll
-    for (int j = 0; j < kBatchMaxRoots; ++j) xv[j] = av[j] = 0.0;
-    for (int sidx = 0; sidx < n; ++sidx) {
-      const double v = V[sidx * nov + x], a = AV[sidx * nov + x];
-#pragma unroll
-      for (int j = 0; j < kBatchMaxRoots; ++j)
-        if (j < K) {
-          xv[j] += c[j][sidx] * v;
-          av[j] += c[j][sidx] * a;
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < kBatchMaxRoots; ++j)
+    for (int j = 0; j < NR; ++j)
       if (j < K) {
         const double r = av[j] - wr[j] * xv[j];
         X[j * nov + x] = xv[j];
@@ -501,7 +546,7 @@ __global__ void __launch_bounds__(256) ritz_kernel(const MolDesc* __restrict__ m
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-  for (int j = 0; j < kBatchMaxRoots; ++j)
+  for (int j = 0; j < NR; ++j)
     if (j < K) {
       const double t = wave_sum(ss[j]);
       if (lane == 0) red[wave][j] = t;
@@ -514,7 +559,8 @@ __global__ void __launch_bounds__(256) ritz_kernel(const MolDesc* __restrict__ m
 }
 
 // Convergence and bookkeeping for every molecule; counts the active ones.
-__global__ void __launch_bounds__(256) select_kernel(int nmol, int K, int Smax, double tol,
+__global__ void __launch_bounds__(256) select_kernel(int nmol, const MolDesc* __restrict__ mols, int K, int Smax,
+                                                     double tol,
                                                      const double* __restrict__ rpart, double* __restrict__ rnorm,
                                                      const int* __restrict__ S, int* knew, int* active, int* coll,
                                                      int* qcol, int* unc, int* conv, int* counters) {
@@ -524,9 +570,10 @@ __global__ void __launch_bounds__(256) select_kernel(int nmol, int K, int Smax, 
   for (int m = threadIdx.x; m < nmol; m += 256) {
     if (!active[m]) continue;
     int nu = 0;
+    const int nch = chunks_of(mols[m].nov);
     for (int j = 0; j < K; ++j) {
       double r2 = 0.0;
-      for (int c = 0; c < kXChunks; ++c) r2 += rpart[(static_cast<long>(m) * kXChunks + c) * kBatchMaxRoots + j];
+      for (int c = 0; c < nch; ++c) r2 += rpart[(static_cast<long>(m) * kXChunks + c) * kBatchMaxRoots + j];
       const double rn = sqrt(r2);
       rnorm[m * K + j] = rn;
       if (rn > tol) unc[m * K + nu++] = j;
@@ -548,54 +595,38 @@ __global__ void __launch_bounds__(256) select_kernel(int nmol, int K, int Smax, 
   }
 }
 
-// Collapse onto the q lowest Ritz vectors: TV_s = sum_t evec(t, s) V_t (and A V).
+// Collapse onto the q <= NQ lowest Ritz vectors, V_s <- sum_t evec(t, s) V_t (and
+// A V), in place: a thread forms all q new elements of its entry before it
+// writes them.  The projected matrix becomes diag(lowest q eigenvalues).
+template <int NQ>
 __global__ void __launch_bounds__(256) collapse_kernel(const MolDesc* __restrict__ mols, int Smax,
-                                                       const double* __restrict__ Vp, const double* __restrict__ AVp,
-                                                       const double* __restrict__ evec, const int* __restrict__ S,
+                                                       double* __restrict__ Vp, double* __restrict__ AVp,
+                                                       const double* __restrict__ evec,
+                                                       const double* __restrict__ eval, const int* __restrict__ S,
                                                        const int* __restrict__ coll, const int* __restrict__ qcol,
-                                                       double* __restrict__ TVp, double* __restrict__ TAVp) {
-  __shared__ double c[kBatchMaxSub];
-  const int m = blockIdx.x, s = blockIdx.y;
-  if (!coll[m] || s >= qcol[m]) return;
-  const MolDesc md = mols[m];
-  const long nov = md.nov;
-  const int n = S[m];
-  for (int t = threadIdx.x; t < n; t += 256) c[t] = evec[static_cast<long>(m) * Smax * Smax + t + static_cast<long>(s) * Smax];
-  __syncthreads();
-  const double* V = Vp + md.vbase;
-  const double* AV = AVp + md.vbase;
-  double* TV = TVp + md.tbase + s * nov;
-  double* TAV = TAVp + md.tbase + s * nov;
-  for (long x = threadIdx.x; x < nov; x += 256) {
-    double a = 0.0, b = 0.0;
-    for (int t = 0; t < n; ++t) {
-      a += c[t] * V[t * nov + x];
-      b += c[t] * AV[t * nov + x];
-    }
-    TV[x] = a;
-    TAV[x] = b;
-  }
-}
-
-// Second half of the collapse: copy back, M = diag(lowest q eigenvalues), S = q.
-__global__ void __launch_bounds__(256) collapse_copy_kernel(const MolDesc* __restrict__ mols, int Smax,
-                                                            const double* __restrict__ TVp,
-                                                            const double* __restrict__ TAVp,
-                                                            const double* __restrict__ eval, int* S, int* coll,
-                                                            const int* __restrict__ qcol, double* __restrict__ Vp,
-                                                            double* __restrict__ AVp, double* __restrict__ Mp) {
-  const int m = blockIdx.x, s = blockIdx.y;
+                                                       double* __restrict__ Mp) {
+  __shared__ double c[kBatchMaxSub][NQ];
+  const int m = blockIdx.x, ch = blockIdx.y;
   if (!coll[m]) return;
-  const int q = qcol[m];
-  if (s > q) return;
   const MolDesc md = mols[m];
   const long nov = md.nov;
-  if (s < q) {
-    for (long x = threadIdx.x; x < nov; x += 256) {
-      Vp[md.vbase + s * nov + x] = TVp[md.tbase + s * nov + x];
-      AVp[md.vbase + s * nov + x] = TAVp[md.tbase + s * nov + x];
+  if (ch >= chunks_of(nov)) return;
+  const int n = S[m], q = qcol[m];
+  for (int idx = threadIdx.x; idx < kBatchMaxSub * NQ; idx += 256) {
+    const int t = idx / NQ, j = idx % NQ;
+    c[t][j] = (t < n && j < q) ? evec[static_cast<long>(m) * Smax * Smax + t + static_cast<long>(j) * Smax] : 0.0;
+  }
+  __syncthreads();
+  const long x0 = chunk_begin(nov, ch), x1 = chunk_begin(nov, ch + 1);
+  for (long x = x0 + threadIdx.x; x < x1; x += 256)
+    for (double* rows : {Vp + md.vbase, AVp + md.vbase}) {
+      double acc[NQ] = {};
+      combine_at<NQ>(rows, nov, n, x, c, acc);
+#pragma unroll
+      for (int j = 0; j < NQ; ++j)
+        if (j < q) rows[j * nov + x] = acc[j];
     }
-  } else {  // block s == q: the projected matrix
+  if (ch == 0) {
     double* M = Mp + static_cast<long>(m) * Smax * Smax;
     for (int idx = threadIdx.x; idx < q * q; idx += 256) {
       const int i = idx / q, j = idx % q;
@@ -617,6 +648,7 @@ __global__ void __launch_bounds__(256) precond_kernel(const MolDesc* __restrict_
   if (!active[m]) return;
   const MolDesc md = mols[m];
   const long nov = md.nov, x0 = chunk_begin(nov, ch), x1 = chunk_begin(nov, ch + 1);
+  if (ch >= chunks_of(nov)) return;
   const int nu = knew[m];
   double* w[kBatchMaxRoots];
 #pragma unroll
@@ -660,115 +692,119 @@ __global__ void __launch_bounds__(256) gs_dots_kernel(const MolDesc* __restrict_
                                                       const int* __restrict__ active, const int* __restrict__ coll,
                                                       const int* __restrict__ qcol, const int* __restrict__ unc,
                                                       double* __restrict__ part) {
+  __shared__ DotsLds L;
   const int m = blockIdx.x, ch = blockIdx.y;
   if (!active[m]) return;
   const MolDesc md = mols[m];
-  const long nov = md.nov, x0 = chunk_begin(nov, ch), x1 = chunk_begin(nov, ch + 1);
+  const long nov = md.nov;
+  if (ch >= chunks_of(nov)) return;
   const int nb = coll[m] ? qcol[m] : S[m];
   const int nu = knew[m];
-  const double* w[kBatchMaxRoots];
-#pragma unroll
-  for (int u = 0; u < kBatchMaxRoots; ++u) w[u] = Wcp + md.xbase + unc[m * K + min(u, nu - 1)] * nov;
-  double* P = part + (static_cast<long>(m) * kXChunks + ch) * kPartStride;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int s0 = 2 * wave; s0 < nb; s0 += 8) {
-    double d[2][kBatchMaxRoots];
-    wave_dots2x16(Vp + md.vbase, nov, s0, nb, x0, x1, w, nu, d);
-    if (lane == 0)
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int u = 0; u < kBatchMaxRoots; ++u)
-          if (u < nu && s0 + i < nb) P[(s0 + i) * 2 * kBatchMaxRoots + u] = d[i][u];
-  }
+  const double* w = Wcp + md.xbase + unc[m * K + min(static_cast<int>(threadIdx.x & 15), nu - 1)] * nov;
+  chunk_dots(Vp + md.vbase, nov, nb, w, nu, chunk_begin(nov, ch), chunk_begin(nov, ch + 1),
+             part + (static_cast<long>(m) * kXChunks + ch) * kPartStride, L);
 }
 
 // ... then the update of chunk c: h = the inner products summed over the
-// chunks in order, w_u -= sum_s h[s][u] V_s.
+// chunks in order, w_u -= sum_s h[s][u] V_s for the nu <= NR corrections.
+template <int NR>
 __global__ void __launch_bounds__(256) gs_update_kernel(const MolDesc* __restrict__ mols, int K,
                                                         const double* __restrict__ Vp, double* __restrict__ Wcp,
                                                         const int* __restrict__ S, const int* __restrict__ knew,
                                                         const int* __restrict__ active, const int* __restrict__ coll,
                                                         const int* __restrict__ qcol, const int* __restrict__ unc,
                                                         const double* __restrict__ part) {
-  __shared__ double h[kBatchMaxSub][kBatchMaxRoots];
+  __shared__ double h[kBatchMaxSub][NR];
   const int m = blockIdx.x, ch = blockIdx.y;
   if (!active[m]) return;
   const MolDesc md = mols[m];
   const long nov = md.nov, x0 = chunk_begin(nov, ch), x1 = chunk_begin(nov, ch + 1);
+  const int nch = chunks_of(nov);
+  if (ch >= nch) return;
   const int nb = coll[m] ? qcol[m] : S[m];
   const int nu = knew[m];
   const double* P = part + static_cast<long>(m) * kXChunks * kPartStride;
-  for (int idx = threadIdx.x; idx < nb * nu; idx += 256) {
-    const int sidx = idx / nu, u = idx % nu;
+  for (int idx = threadIdx.x; idx < kBatchMaxSub * NR; idx += 256) {
+    const int sidx = idx / NR, u = idx % NR;
     double d = 0.0;
-    for (int c = 0; c < kXChunks; ++c) d += P[c * kPartStride + sidx * 2 * kBatchMaxRoots + u];
-    h[sidx][u] = d;
+    if (sidx < nb && u < nu)
+      for (int c = 0; c < nch; ++c) d += P[c * kPartStride + sidx * 2 * kBatchMaxRoots + u];
+    h[sidx][u] = -d;
   }
   __syncthreads();
-  const double* V = Vp + md.vbase;
-  double* w[kBatchMaxRoots];
+  double* w[NR];
 #pragma unroll
-  for (int u = 0; u < kBatchMaxRoots; ++u) w[u] = Wcp + md.xbase + unc[m * K + min(u, nu - 1)] * nov;
+  for (int u = 0; u < NR; ++u) w[u] = Wcp + md.xbase + unc[m * K + min(u, nu - 1)] * nov;
   for (long x = x0 + threadIdx.x; x < x1; x += 256) {
-    double t[kBatchMaxRoots];
+    double t[NR];
 #pragma unroll
-    for (int u = 0; u < kBatchMaxRoots; ++u) t[u] = u < nu ? w[u][x] : 0.0;
-    for (int sidx = 0; sidx < nb; ++sidx) {
-      const double v = V[sidx * nov + x];
+    for (int u = 0; u < NR; ++u) t[u] = u < nu ? w[u][x] : 0.0;
+    combine_at<NR>(Vp + md.vbase, nov, nb, x, h, t);
 #pragma unroll
-      for (int u = 0; u < kBatchMaxRoots; ++u)
-        if (u < nu) t[u] -= h[sidx][u] * v;
-    }
-#pragma unroll
-    for (int u = 0; u < kBatchMaxRoots; ++u)
+    for (int u = 0; u < NR; ++u)
       if (u < nu) w[u][x] = t[u];
   }
 }
 
 // Orthonormalise the deflated corrections among themselves (modified
 // Gram-Schmidt, twice) and append the survivors (norm above 1e-8 of the
-// correction's norm before deflation) to the basis.
-__global__ void __launch_bounds__(256) append_kernel(const MolDesc* __restrict__ mols, int K, int Smax,
+// correction's norm before deflation) to the basis.  The pass that takes one
+// direction out also forms the inner product with the next (or the norm at the
+// end), so each costs one pass and one workgroup sum; a thread always holds the
+// same entries, so no barrier orders the passes.
+constexpr int kAppendThreads = 512;
+__global__ void __launch_bounds__(kAppendThreads) append_kernel(const MolDesc* __restrict__ mols, int K, int Smax,
                                                      double* __restrict__ Vp, double* __restrict__ Wcp, int* S,
                                                      int* knew, int* active, int* coll, const int* __restrict__ qcol,
                                                      const int* __restrict__ unc, int* conv,
                                                      const int* __restrict__ counters,
                                                      const double* __restrict__ n0part) {
-  __shared__ double red[256];
+  __shared__ double red[2][kAppendThreads / 64];
   const int m = blockIdx.x;
   if (!active[m]) return;
   const MolDesc md = mols[m];
   const long nov = md.nov;
   const int S0 = coll[m] ? qcol[m] : S[m];
-  const int nu = knew[m];
-  double* V = Vp + md.vbase;
-  int acc = 0;
+  const int nu = knew[m], nch = chunks_of(nov);
+  double* V = Vp + md.vbase + static_cast<long>(S0) * nov;
+  int acc = 0, turn = 0;
+  auto sum = [&](double v) {  // over the workgroup, fixed order; two slots in turn need one barrier a sum
+    double* r = red[turn ^= 1];
+    v = wave_sum64(v);
+    if ((threadIdx.x & 63) == 0) r[threadIdx.x >> 6] = v;
+    __syncthreads();
+    v = 0.0;
+    for (int q = 0; q < kAppendThreads / 64; ++q) v += r[q];
+    return v;
+  };
   for (int u = 0; u < nu; ++u) {
     if (S0 + acc >= Smax) break;
     double* w = Wcp + md.xbase + unc[m * K + u] * nov;
-    for (int pass = 0; pass < 2; ++pass)
-      for (int t = 0; t < acc; ++t) {
-        const double* a = V + static_cast<long>(S0 + t) * nov;
-        double d = 0.0;
-        for (long x = threadIdx.x; x < nov; x += 256) d += a[x] * w[x];
-        d = block_sum(d, red);
-        for (long x = threadIdx.x; x < nov; x += 256) w[x] -= d * a[x];
-        __syncthreads();
+    double d = 0.0;
+    for (long x = threadIdx.x; x < nov; x += kAppendThreads) d += w[x] * (acc > 0 ? V[x] : w[x]);
+    d = sum(d);
+    for (int i = 0; i < 2 * acc; ++i) {
+      const double* a = V + static_cast<long>(i % acc) * nov;
+      const double* next = i + 1 < 2 * acc ? V + static_cast<long>((i + 1) % acc) * nov : w;
+      double dn = 0.0;
+      for (long x = threadIdx.x; x < nov; x += kAppendThreads) {
+        const double wx = w[x] - d * a[x];
+        w[x] = wx;
+        dn += wx * next[x];
       }
-    double nw = 0.0;
-    for (long x = threadIdx.x; x < nov; x += 256) nw += w[x] * w[x];
-    nw = sqrt(block_sum(nw, red));
+      d = sum(dn);
+    }
+    const double nw = sqrt(d);
     double n02 = 0.0;
-    for (int c = 0; c < kXChunks; ++c) n02 += n0part[(static_cast<long>(m) * kXChunks + c) * kBatchMaxRoots + u];
+    for (int c = 0; c < nch; ++c) n02 += n0part[(static_cast<long>(m) * kXChunks + c) * kBatchMaxRoots + u];
     if (nw > 1e-8 * sqrt(n02) && nw > 1e-14) {
-      double* dst = V + static_cast<long>(S0 + acc) * nov;
+      double* dst = V + static_cast<long>(acc) * nov;
       const double inv = 1.0 / nw;
-      for (long x = threadIdx.x; x < nov; x += 256) dst[x] = w[x] * inv;
+      for (long x = threadIdx.x; x < nov; x += kAppendThreads) dst[x] = w[x] * inv;
       ++acc;
-      __syncthreads();
     }
   }
+  __syncthreads();  // S, knew and coll have been read by every wavefront
   if (threadIdx.x == 0) {
     S[m] = S0;
     coll[m] = 0;
@@ -811,7 +847,7 @@ BatchResult batched_cis(const std::vector<DeviceMolecule*>& mols, const BatchOpt
 
   // ---- molecule table, ordering and pools
   std::vector<MolDesc> h(nmol);
-  long vtot = 0, xtot = 0, ttot = 0, scr = 0;
+  long vtot = 0, xtot = 0, scr = 0;
   int maxnew = 2 * K;
   for (int m = 0; m < nmol; ++m) {
     const DeviceMolecule& d = *mols[m];
@@ -834,10 +870,8 @@ BatchResult batched_cis(const std::vector<DeviceMolecule*>& mols, const BatchOpt
     md.nov = nov;
     md.vbase = vtot;
     md.xbase = xtot;
-    md.tbase = ttot;
     vtot += static_cast<long>(Smax) * nov;
     xtot += static_cast<long>(K) * nov;
-    ttot += static_cast<long>(2 * K) * nov;
     md.C32 = d.C32.p;
     md.C64 = d.C.p;
     md.eps = d.eps.p;
@@ -877,8 +911,6 @@ BatchResult batched_cis(const std::vector<DeviceMolecule*>& mols, const BatchOpt
   w.AV.ensure(vtot);
   w.X.ensure(xtot);
   w.Wc.ensure(xtot);
-  w.TV.ensure(ttot);
-  w.TAV.ensure(ttot);
   w.Mp.ensure(static_cast<size_t>(nmol) * Smax * Smax);
   w.evec.ensure(static_cast<size_t>(nmol) * Smax * Smax);
   w.eval.ensure(static_cast<size_t>(nmol) * Smax);
@@ -990,30 +1022,38 @@ BatchResult batched_cis(const std::vector<DeviceMolecule*>& mols, const BatchOpt
       if (timed) hipLaunchKernelGGL(stamp_span_kernel, dim3(1), dim3(256), 0, st, G, w.stamps.p, w.nsig.p + 1);
       hipLaunchKernelGGL(project_part_kernel, dim3(nmol, kXChunks), dim3(256), 0, st, w.mols.p, w.V.p, w.AV.p,
                          w.S.p, w.knew.p, w.active.p, w.part.p);
-      hipLaunchKernelGGL(project_kernel, dim3(nmol), dim3(256), 0, st, Smax, w.part.p, w.Mp.p, w.S.p, w.knew.p,
+      hipLaunchKernelGGL(project_kernel, dim3(nmol), dim3(256), 0, st, w.mols.p, Smax, w.part.p, w.Mp.p, w.S.p, w.knew.p,
                          w.active.p);
       hipLaunchKernelGGL(advance_kernel, dim3(ceil_div(nmol, 256)), dim3(256), 0, st, nmol, w.S.p, w.knew.p,
                          w.active.p);
       launch_eig_batch(st, nmol, eig);
-      hipLaunchKernelGGL(ritz_kernel, dim3(nmol, kXChunks), dim3(256), 0, st, w.mols.p, K, Smax, w.V.p, w.AV.p,
-                         w.evec.p, w.eval.p, w.S.p, w.active.p, w.X.p, w.Wc.p, w.omega.p, w.rpart.p);
-      hipLaunchKernelGGL(select_kernel, dim3(1), dim3(256), 0, st, nmol, K, Smax, opt.tol, w.rpart.p, w.rnorm.p,
-                         w.S.p, w.knew.p, w.active.p, w.coll.p, w.qcol.p, w.unc.p, w.conv.p, w.counters.p);
-      hipLaunchKernelGGL(collapse_kernel, dim3(nmol, Q), dim3(256), 0, st, w.mols.p, Smax, w.V.p, w.AV.p, w.evec.p,
-                         w.S.p, w.coll.p, w.qcol.p, w.TV.p, w.TAV.p);
-      hipLaunchKernelGGL(collapse_copy_kernel, dim3(nmol, Q + 1), dim3(256), 0, st, w.mols.p, Smax, w.TV.p, w.TAV.p,
-                         w.eval.p, w.S.p, w.coll.p, w.qcol.p, w.V.p, w.AV.p, w.Mp.p);
-      const dim3 chunks(nmol, kXChunks);
-      hipLaunchKernelGGL(precond_kernel, chunks, dim3(256), 0, st, w.mols.p, K, w.Wc.p, w.knew.p, w.active.p,
-                         w.unc.p, w.omega.p, w.n0.p);
-      for (int pass = 0; pass < 2; ++pass) {
-        hipLaunchKernelGGL(gs_dots_kernel, chunks, dim3(256), 0, st, w.mols.p, K, w.V.p, w.Wc.p, w.S.p, w.knew.p,
-                           w.active.p, w.coll.p, w.qcol.p, w.unc.p, w.part.p);
-        hipLaunchKernelGGL(gs_update_kernel, chunks, dim3(256), 0, st, w.mols.p, K, w.V.p, w.Wc.p, w.S.p,
-                           w.knew.p, w.active.p, w.coll.p, w.qcol.p, w.unc.p, w.part.p);
-      }
-      hipLaunchKernelGGL(append_kernel, dim3(nmol), dim3(256), 0, st, w.mols.p, K, Smax, w.V.p, w.Wc.p, w.S.p,
-                         w.knew.p, w.active.p, w.coll.p, w.qcol.p, w.unc.p, w.conv.p, w.counters.p, w.n0.p);
+      // kernels for at least the K roots wanted (registers for each of them)
+      const auto rest = [&](auto nr) {
+        constexpr int NR = decltype(nr)::value;
+        const dim3 chunks(nmol, kXChunks);
+        hipLaunchKernelGGL(ritz_kernel<NR>, chunks, dim3(256), 0, st, w.mols.p, K, Smax, w.V.p, w.AV.p, w.evec.p,
+                           w.eval.p, w.S.p, w.active.p, w.X.p, w.Wc.p, w.omega.p, w.rpart.p);
+        hipLaunchKernelGGL(select_kernel, dim3(1), dim3(256), 0, st, nmol, w.mols.p, K, Smax, opt.tol, w.rpart.p,
+                           w.rnorm.p, w.S.p, w.knew.p, w.active.p, w.coll.p, w.qcol.p, w.unc.p, w.conv.p,
+                           w.counters.p);
+        hipLaunchKernelGGL(collapse_kernel<2 * NR>, chunks, dim3(256), 0, st, w.mols.p, Smax, w.V.p, w.AV.p, w.evec.p,
+                           w.eval.p, w.S.p, w.coll.p, w.qcol.p, w.Mp.p);
+        hipLaunchKernelGGL(precond_kernel, chunks, dim3(256), 0, st, w.mols.p, K, w.Wc.p, w.knew.p, w.active.p,
+                           w.unc.p, w.omega.p, w.n0.p);
+        for (int pass = 0; pass < 2; ++pass) {
+          hipLaunchKernelGGL(gs_dots_kernel, chunks, dim3(256), 0, st, w.mols.p, K, w.V.p, w.Wc.p, w.S.p, w.knew.p,
+                             w.active.p, w.coll.p, w.qcol.p, w.unc.p, w.part.p);
+          hipLaunchKernelGGL(gs_update_kernel<NR>, chunks, dim3(256), 0, st, w.mols.p, K, w.V.p, w.Wc.p, w.S.p,
+                             w.knew.p, w.active.p, w.coll.p, w.qcol.p, w.unc.p, w.part.p);
+        }
+      };
+      if (K <= 3) rest(std::integral_constant<int, 3>{});
+      else if (K <= 5) rest(std::integral_constant<int, 5>{});
+      else if (K <= 8) rest(std::integral_constant<int, 8>{});
+      else if (K <= 12) rest(std::integral_constant<int, 12>{});
+      else rest(std::integral_constant<int, 16>{});
+      hipLaunchKernelGGL(append_kernel, dim3(nmol), dim3(kAppendThreads), 0, st, w.mols.p, K, Smax, w.V.p, w.Wc.p,
+                         w.S.p, w.knew.p, w.active.p, w.coll.p, w.qcol.p, w.unc.p, w.conv.p, w.counters.p, w.n0.p);
       SEQX_LAUNCH_CHECK();
     };
     if (opt.graph) {

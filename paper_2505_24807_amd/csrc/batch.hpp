@@ -22,7 +22,6 @@ struct MolDesc {
   long nov;
   long vbase;    // offset (elements) of the molecule's S_max x nov block in the V / AV pools
   long xbase;    // offset of its K x nov block in the Ritz / correction pools
-  long tbase;    // offset of its 2K x nov block in the collapse pools
   const float* C32;
   const double* C64;
   const double* eps;
@@ -77,7 +76,7 @@ struct BatchWork {
   DBuf<int2> items;
   DBuf<long long> nsig;    // [0] sigma vectors, [1] wall-clock ticks inside sigma launches, [2] flops
   DBuf<long long> stamps;  // start / end tick of each workgroup of the last sigma launch
-  DBuf<double> V, AV, X, Wc, TV, TAV, Mp, evec, eval, omega, rnorm, rpart, part, n0;
+  DBuf<double> V, AV, X, Wc, Mp, evec, eval, omega, rnorm, rpart, part, n0;
   DBuf<float> scratch32;
   DBuf<double> scratch64;
   DBuf<double> fin;

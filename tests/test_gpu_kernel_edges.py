@@ -154,10 +154,13 @@ def test_ground_states_do_not_depend_on_the_batch(ctx):
     job.free()
 
 
-# subspaces from 1 row (H2: one pair) to the cap of 48, all pairs wanted (water, 8 of 8) and few of many
+# subspaces from 1 row (H2: one pair) to the cap of 48, all pairs wanted (water, 8 of 8) and few of many; pair counts
+# of one ragged chunk, three (676) and the largest number (2601, more entries a chunk than threads)
 @pytest.mark.parametrize("k, mols", [(1, [molecules.h2(), molecules.water_cluster(1, 1), molecules.ethylene()]),
                                      (8, [molecules.water_cluster(1, 1), molecules.ethylene(),
                                           _noisy(molecules.polyene(6), 6)]),
+                                     (5, [_noisy(molecules.polyene(10), 10), _noisy(molecules.polyene(20), 20)]),
+                                     (12, [_noisy(molecules.polyene(10), 11), _noisy(molecules.polyene(20), 22)]),
                                      (16, [molecules.ethylene(), molecules.water_cluster(3, 3),
                                            _noisy(molecules.polyene(6), 6)])])
 def test_subspace_sizes_of_a_batch(ctx, k, mols):
