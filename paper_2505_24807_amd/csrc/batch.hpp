@@ -35,6 +35,12 @@ struct MolDesc {
   const Elem* elems;
 };
 
+// Where one molecule's roots go (buffers of its DeviceMolecule), and its coordinates.
+struct RootOut {
+  double *X, *Y, *omega, *f, *mu;
+  const double* xyz;
+};
+
 constexpr int kBatchMaxSub = 48;    // subspace cap per molecule (Gram-Schmidt and the Ritz step hold its coefficients in LDS)
 constexpr int kBatchMaxNp = 1536;   // packed pair indices per molecule (Coulomb step holds them in LDS)
 constexpr int kBatchMaxRoots = 16;
@@ -72,6 +78,7 @@ struct BatchResult {
 
 struct BatchWork {
   DBuf<MolDesc> mols;
+  DBuf<RootOut> outs;
   DBuf<int> order, S, knew, active, coll, qcol, unc, conv, counters;
   DBuf<int2> items;
   DBuf<long long> nsig;    // [0] sigma vectors, [1] wall-clock ticks inside sigma launches, [2] flops
@@ -79,13 +86,12 @@ struct BatchWork {
   DBuf<double> V, AV, X, Wc, Mp, evec, eval, omega, rnorm, rpart, part, n0;
   DBuf<float> scratch32;
   DBuf<double> scratch64;
-  DBuf<double> fin;
   hipStream_t stream = nullptr;
   ~BatchWork();
 };
 
 // Lowest nroots CIS roots of every molecule; fills each molecule's omega, X, Y (= 0), f, mu.
 BatchResult batched_cis(const std::vector<DeviceMolecule*>& mols, const BatchOptions& opt, BatchWork& w,
-                        TileTuning& tune, SigmaWork& sig, hipStream_t user_stream);
+                        TileTuning& tune, hipStream_t user_stream);
 
 }  // namespace seqx

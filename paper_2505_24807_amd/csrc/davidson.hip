@@ -409,8 +409,10 @@ int orthonormalize_append(hipStream_t st, DenseSolver& ds, DavWork& w, long nov,
   return kept;
 }
 
-}  // namespace
-
+// Amplitudes and properties of K converged roots: X, Y from T = X+Y and
+// U = X-Y rows (TDHF; CIS passes X in Tv and ignores Uv), the sign convention,
+// AO transition densities and ZDO transition dipoles and oscillator strengths.
+// om: device omega [K] (hartree).  Fills m.omega, m.X, m.Y, m.f, m.mu.
 void finalize_roots(DeviceMolecule& m, int theory, int K, const double* om, const double* Tv, const double* Uv,
                     SigmaWork& sig, DBuf<double>& scratch, hipStream_t st) {
   const long nov = static_cast<long>(m.nocc) * m.nvirt;
@@ -440,6 +442,8 @@ void finalize_roots(DeviceMolecule& m, int theory, int K, const double* om, cons
   m.nroots = K;
   m.theory = theory;
 }
+
+}  // namespace
 
 bool davidson_f32_basis(long nov, int precision) {
   return precision != kPrecFP64 && nov % 4 == 0 && nov >= 4096;

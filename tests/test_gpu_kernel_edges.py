@@ -183,3 +183,23 @@ def test_subspace_sizes_of_a_batch(ctx, k, mols):
             ref = ref[near]
         assert np.abs(got - ref[:k]).max() <= 1e-8
     job.free()
+
+
+@pytest.mark.parametrize("precision", [seqx.FP32, seqx.FP64])
+def test_properties_of_a_batch(ctx, precision):
+    """Amplitudes, dipoles and strengths of a batch against those of each molecule's own solve: vectors converged to a
+    residual of 1e-8 over gaps of 0.005 hartree agree to 2e-6, dipoles of a few atomic units to 1e-5.  (FP32 products
+    leave a residual floor near 1e-6: 2e-4 and 1e-3.)"""
+    mols = [molecules.h2(), molecules.water_cluster(1, 1), molecules.ethylene(), _noisy(molecules.polyene(6), 6)]
+    print(f"[gpu] batch properties precision={precision}", flush=True)
+    tol, tx, tm = (1e-8, 2e-6, 1e-5) if precision == seqx.FP64 else (1e-6, 2e-4, 1e-3)
+    job = ctx.prepare(*molecules.concat(mols))
+    job.solve(theory=seqx.CIS, nroots=1, tol=tol, max_iter=300, precision=precision, batched=True)
+    for m, mol in enumerate(mols):
+        alone = ctx.prepare([mol.natoms], mol.Z, mol.xyz)
+        alone.solve(theory=seqx.CIS, nroots=1, tol=1e-9, max_iter=300)
+        a, b = job.results(m), alone.results()
+        assert np.abs(a.X - b.X).max() <= tx and not a.Y.any()
+        assert np.abs(a.mu - b.mu).max() <= tm and np.abs(a.f - b.f).max() <= tm
+        alone.free()
+    job.free()
