@@ -1,6 +1,7 @@
 // C ABI of libseqx (declared in include/seqx.h): context and job lifecycle,
 // host validation, argument marshalling and the error model.  No exception
 // crosses the boundary; every entry point returns a status code.
+#include <algorithm>
 #include <cctype>
 #include <chrono>
 #include <cstdio>
@@ -10,6 +11,7 @@
 #include <deque>
 #include <fstream>
 #include <map>
+#include <mutex>
 #include <atomic>
 #include <exception>
 #include <thread>
@@ -38,6 +40,23 @@ static_assert(SEQX_SIGMA_SCRATCH_BYTES == kSigmaScratchBytes, "workspace size of
 
 using namespace seqx;
 
+// Pinned host memory that kernels write small results to; without it (the
+// allocation failed) results are copied one by one.
+struct Staging {
+  static constexpr size_t kSize = size_t(1) << 17;  // doubles: 1 MB
+  double* p = nullptr;
+  std::mutex mutex;
+  void alloc() {
+    if (hipHostMalloc(reinterpret_cast<void**>(&p), kSize * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+      p = nullptr;
+      (void)hipGetLastError();
+    }
+  }
+  ~Staging() {
+    if (p) (void)hipHostFree(p);
+  }
+};
+
 struct seqx_ctx {
   // caller allocators, never modified once added (buffers keep a pointer to
   // theirs).  Declared first so that they are destroyed last, after every
@@ -55,6 +74,7 @@ struct seqx_ctx {
   TileTuning tune;
   Mlp mlp;
   MlpWork mw;
+  Staging staging;
 };
 
 struct seqx_job {
@@ -367,6 +387,7 @@ seqx_status seqx_create(int device, void* hip_stream, seqx_ctx** out) {
     ctx->ds.reset(new DenseSolver(ctx->stream));
     // device address of this GPU's fixed sigma workspace (no-allocation entry point)
     sigma_scratch_setup(device);
+    ctx->staging.alloc();
   });
   if (s != SEQX_OK) {
     g_noctx_err = ctx->err;
@@ -906,6 +927,27 @@ seqx_status seqx_results(const seqx_job* job, int32_t mol, double* omega_eV, dou
     hipStream_t st = job->ctx->stream;
     const int K = m.nroots;
     const size_t nx = static_cast<size_t>(K) * m.nocc * m.nvirt;
+    // Results up to the size of the context's pinned buffer (1 MB) come through it
+    // in one launch, as a copy to pageable memory costs 15 us however short it
+    // is: 57 kB of five roots 93 -> 27 us, 0.8 MB 150 -> 62.  Larger ones are
+    // bound by the link either way.
+    const bool with_y = Y && m.theory == 1;  // zero for CIS
+    const size_t total = 5 * static_cast<size_t>(K) + (X ? nx : 0) + (with_y ? nx : 0);
+    Staging& sg = job->ctx->staging;
+    if (sg.p && total <= Staging::kSize) {
+      std::lock_guard<std::mutex> lock(sg.mutex);
+      pack_roots(m, X != nullptr, with_y, sg.p, st);
+      SEQX_HIP(hipStreamSynchronize(st));
+      if (omega_eV)
+        for (int j = 0; j < K; ++j) omega_eV[j] = sg.p[j] * kHartreeEV;
+      if (f) std::copy_n(sg.p + K, K, f);
+      if (mu) std::copy_n(sg.p + 2 * K, 3 * static_cast<size_t>(K), mu);
+      const double* amp = sg.p + 5 * static_cast<size_t>(K);
+      if (X) std::copy_n(amp, nx, X);
+      if (with_y) std::copy_n(amp + (X ? nx : 0), nx, Y);
+      else if (Y) std::fill_n(Y, nx, 0.0);
+      return;
+    }
     std::vector<double> om(K);
     d2h(om.data(), m.omega.p, K, st);
     if (X) d2h(X, m.X.p, nx, st);

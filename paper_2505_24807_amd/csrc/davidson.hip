@@ -445,6 +445,24 @@ void finalize_roots(DeviceMolecule& m, int theory, int K, const double* om, cons
 
 }  // namespace
 
+// bound by the link to the host; consecutive lanes write consecutive elements
+__global__ void __launch_bounds__(256) pack_roots_kernel(int K, long nx, long ny, const double* __restrict__ omega,
+                                                         const double* __restrict__ f, const double* __restrict__ mu,
+                                                         const double* __restrict__ X, const double* __restrict__ Y,
+                                                         double* __restrict__ out) {
+  const long i = blockIdx.x * 256L + threadIdx.x;
+  const long x = i - 5 * K, y = x - nx;
+  if (y >= ny) return;
+  out[i] = i < K ? omega[i] : i < 2 * K ? f[i - K] : x < 0 ? mu[i - 2 * K] : y < 0 ? X[x] : Y[y];
+}
+
+void pack_roots(const DeviceMolecule& m, bool with_x, bool with_y, double* out, hipStream_t st) {
+  const long n = static_cast<long>(m.nroots) * m.nocc * m.nvirt, nx = with_x ? n : 0, ny = with_y ? n : 0;
+  hipLaunchKernelGGL(pack_roots_kernel, dim3(ceil_div(5 * m.nroots + nx + ny, 256)), dim3(256), 0, st, m.nroots, nx, ny,
+                     m.omega.p, m.f.p, m.mu.p, m.X.p, m.Y.p, out);
+  SEQX_LAUNCH_CHECK();
+}
+
 bool davidson_f32_basis(long nov, int precision) {
   return precision != kPrecFP64 && nov % 4 == 0 && nov >= 4096;
 }

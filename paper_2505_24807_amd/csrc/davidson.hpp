@@ -72,6 +72,10 @@ struct DavResult {
   std::vector<std::vector<double>> omega_iter;  // Ritz values (hartree) per iteration
 };
 
+// The roots of molecule m as one row of doubles at out (device-visible host
+// memory): omega, f [nroots], mu [nroots][3], then X if with_x and Y if with_y.
+void pack_roots(const DeviceMolecule& m, bool with_x, bool with_y, double* out, hipStream_t st);
+
 // Lowest roots of molecule m; fills m.omega, m.X, m.Y, m.f, m.mu.
 // Throws Error(kEDavNoConv) / Error(kEUnstable) on failure.
 DavResult davidson(DeviceMolecule& m, const DavOptions& opt, DenseSolver& ds, DavWork& w, hipStream_t st);

@@ -203,3 +203,25 @@ def test_properties_of_a_batch(ctx, precision):
         assert np.abs(a.mu - b.mu).max() <= tm and np.abs(a.f - b.f).max() <= tm
         alone.free()
     job.free()
+
+
+# 2 kB, and just below and above the 1 MB that go through pinned memory (C20H22: 2601 pairs, 50 roots are 1.04e6 B)
+@pytest.mark.parametrize("n_carbon, k", [(4, 2), (20, 50), (20, 51)])
+@pytest.mark.parametrize("theory", [seqx.CIS, seqx.TDHF])
+def test_parts_of_results(ctx, n_carbon, k, theory):
+    """Every choice of outputs gives the same values; X^2 - Y^2 = 1 to a residual of 1e-3 squared."""
+    mol = _noisy(molecules.polyene(n_carbon), n_carbon)
+    print(f"[gpu] results {mol.name} k={k} theory={theory}", flush=True)
+    job = ctx.prepare([mol.natoms], mol.Z, mol.xyz)
+    n, o, v = job.dims()
+    job.solve(theory=theory, nroots=k, tol=1e-3, max_iter=300)
+    full = job.results()
+    norm = (full.X ** 2 - full.Y ** 2).sum((1, 2))
+    assert np.abs(norm - 1.0).max() <= 1e-6 and (theory == seqx.TDHF) == full.Y.any()
+    for keep in range(32):
+        out = [np.full(a.shape, np.nan) if keep >> i & 1 else None
+               for i, a in enumerate((full.omega_eV, full.X, full.Y, full.f, full.mu))]
+        job._check(job.lib.seqx_results(job.h, 0, *[None if a is None else seqx._dptr(a) for a in out]))
+        for a, b in zip(out, (full.omega_eV, full.X, full.Y, full.f, full.mu)):
+            assert a is None or np.array_equal(a, b)
+    job.free()
