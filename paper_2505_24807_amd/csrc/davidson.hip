@@ -390,7 +390,7 @@ int orthonormalize_append(hipStream_t st, DenseSolver& ds, DavWork& w, long nov,
     if (!again) break;
   }
   if (S == 0) dts(st, nc, Wc, nov, nc, Wc, nov, nov, G, nc, w.ws.p);
-  ds.eigh(nc, G, nc, w.w2.p);
+  ds.eigh_lowest(nc, G, nc, nc, w.w2.p);
   std::vector<double> lam(nc);
   d2h(lam.data(), w.w2.p, nc, st);
   SEQX_HIP(hipStreamSynchronize(st));

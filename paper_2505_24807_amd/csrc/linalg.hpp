@@ -10,6 +10,11 @@ namespace seqx {
 
 constexpr int kSmallDense = 256;  // largest n of the one-workgroup Cholesky kernel
 constexpr int kEigMax = 512;      // largest n of the k-lowest eigensolver
+// smallest n of it in eigh_lowest, also where all pairs are wanted: its four
+// launches take 33 us at n = 11 (65 with one cluster of all eigenvalues), 43 (75)
+// at 16, 52 (91) at 20 and 110 (164) at 48, Jacobi sweeps 39 at 10, 70 at 16, 102 at
+// 20 and 472 at 48
+constexpr int kEigMin = 13;
 // largest n whose reduction stays in one workgroup: a step there costs 1.2 us at
 // n = 64, 2.0 at 128 and 3.5 at 192 (instructions of 8 wavefronts on one compute
 // unit) against 2.8-2.9 across compute units
@@ -49,8 +54,8 @@ class DenseSolver {
   // eigenvalues ascending into w[n]; eigenvectors overwrite A (columns)
   void eigh(int n, double* A, int lda, double* w);
   // the k lowest eigenpairs only: w[0..k), eigenvectors in columns 0..k-1 of A
-  // (the rest of A is overwritten).  n <= kEigMax runs on the kernels of
-  // eig_lowest.hip; larger n uses eigh.  Reads the lower triangle.
+  // (the rest of A is overwritten).  kEigMin <= n <= kEigMax runs on the
+  // kernels of eig_lowest.hip; other n use eigh.  Reads the lower triangle.
   void eigh_lowest(int n, double* A, int lda, int k, double* w);
   // lower Cholesky factor in place (upper triangle untouched); info reports
   // the first non-positive pivot.  n <= kSmallDense runs as one workgroup.
