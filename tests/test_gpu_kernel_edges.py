@@ -225,3 +225,22 @@ def test_parts_of_results(ctx, n_carbon, k, theory):
         for a, b in zip(out, (full.omega_eV, full.X, full.Y, full.f, full.mu)):
             assert a is None or np.array_equal(a, b)
     job.free()
+
+
+# TDHF subspaces whose Cholesky factorisation has one ragged panel (12 rows), whole ones (32) and a remainder (100)
+@pytest.mark.parametrize("cap, k", [(12, 2), (32, 4), (100, 5)])
+def test_subspace_sizes_of_tdhf(ctx, cap, k):
+    """TDHF roots from subspaces of up to `cap` vectors against dense diagonalisation (C8H10, 441 pairs)."""
+    mol = _noisy(molecules.polyene(8), 8)
+    print(f"[gpu] tdhf subspace cap {cap}", flush=True)
+    job = ctx.prepare([mol.natoms], mol.Z, mol.xyz)
+    n, o, v = job.dims()
+    job.solve(theory=seqx.TDHF, nroots=k, tol=1e-8, max_iter=300, max_subspace=cap)
+    sy = model.make_system(mol.Z, mol.xyz, PR)
+    ints = integrals.build(sy)
+    res = scf.run(sy, ints)
+    A, B = excited.build_AB(ints, res.eps, res.C, o)
+    ref = excited.tdhf_dense(A, B, k, o, v)
+    assert np.abs(job.results().omega_eV - ref.omega * model.HARTREE_EV).max() <= 1e-8
+    assert job.stats().max_subspace_used <= cap
+    job.free()
