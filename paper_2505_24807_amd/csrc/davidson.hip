@@ -41,22 +41,26 @@ __global__ void gap_kernel(int o, int v, const double* __restrict__ eps, double*
 
 // smallest ng gaps (ties: lowest flat index i*v + a).  Any of them has i among
 // the ng highest occupied and a among the ng lowest virtual orbitals.
-__global__ void gap_guess_kernel(int o, int v, int ng, const double* __restrict__ eps, int* __restrict__ idx) {
+// One wavefront a candidate counts those before it (a thread each, in one
+// workgroup, took 806 us for 40 of 10201 pairs: now 8).
+__global__ void __launch_bounds__(256) gap_guess_kernel(int o, int v, int ng, const double* __restrict__ eps,
+                                                        int* __restrict__ idx) {
   const int i0 = max(0, o - ng), ni = o - i0, na = min(v, ng);
-  const int N = ni * na;
-  for (int q = threadIdx.x; q < N; q += blockDim.x) {
-    const int i = i0 + q / na, a = q % na;
-    const double g = eps[o + a] - eps[i];
-    const int f = i * v + a;
-    int rank = 0;
-    for (int q2 = 0; q2 < N; ++q2) {
-      const int i2 = i0 + q2 / na, a2 = q2 % na;
-      const double g2 = eps[o + a2] - eps[i2];
-      const int f2 = i2 * v + a2;
-      if (g2 < g || (g2 == g && f2 < f)) ++rank;
-    }
-    if (rank < ng) idx[rank] = f;
+  const int N = ni * na, q = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (q >= N) return;
+  const int i = i0 + q / na, a = q % na;
+  const double g = eps[o + a] - eps[i];
+  const int f = i * v + a;
+  int rank = 0;
+  for (int q2 = lane; q2 < N; q2 += 64) {
+    const int i2 = i0 + q2 / na, a2 = q2 % na;
+    const double g2 = eps[o + a2] - eps[i2];
+    const int f2 = i2 * v + a2;
+    if (g2 < g || (g2 == g && f2 < f)) ++rank;
   }
+#pragma unroll
+  for (int h = 1; h < 64; h <<= 1) rank += __shfl_xor(rank, h);
+  if (lane == 0 && rank < ng) idx[rank] = f;
 }
 
 template <class TV>
@@ -554,7 +558,8 @@ DavResult davidson(DeviceMolecule& m, const DavOptions& opt, DenseSolver& ds, Da
     // with locked roots: unit vectors at the ng gaps that follow the nlock smallest
     const int skip = static_cast<int>(std::min<long>(opt.nlock, nov - ng));
     w.idx.ensure(skip + ng);
-    hipLaunchKernelGGL(gap_guess_kernel, dim3(1), dim3(1024), 0, st, o, v, skip + ng, m.eps.p, w.idx.p);
+    const long ncand = static_cast<long>(std::min(o, skip + ng)) * std::min(v, skip + ng);
+    hipLaunchKernelGGL(gap_guess_kernel, dim3(ceil_div(ncand, 4)), dim3(256), 0, st, o, v, skip + ng, m.eps.p, w.idx.p);
     if (lb)
       hipLaunchKernelGGL(unit_vectors_kernel<float>, dim3(ceil_div(nov, 256), ng), dim3(256), 0, st, ng, nov,
                          w.idx.p + skip, w.V32.p);
