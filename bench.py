@@ -31,8 +31,9 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 METRIC = "σ-vectors/s and time-to-10-roots at 1e-4 eV, learned/mixed vs plain FP64"
-# TFLOP/s, dense, MI355X; split bfloat16 takes three bfloat16 products per product
-PEAK = {"fp64": 78.6, "fp32": 157.3, "bf16": 2500.0, "bf16x3": 2500.0 / 3}
+# TFLOP/s, dense, MI355X.  The transforms of the molecules timed here run on bfloat16
+# planes: six bfloat16 products per FP32 product, three per split-bfloat16 product.
+PEAK = {"fp64": 78.6, "fp32_cores": 157.3, "fp32": 2500.0 / 6, "bf16x3": 2500.0 / 3}
 HBM_PEAK_GBS = 8000.0
 NROOTS, TOL = 10, 1e-5
 
@@ -157,15 +158,15 @@ def _traffic(kernel_tag, flops_per_launch):
     """HBM bytes per launch of the dominant kernel from the committed counter
     summary (FETCH_SIZE and WRITE_SIZE, calibrated against a copy kernel),
     scaled from its k = 32 launch to this run's average launch by flops; None
-    when the GEMM source has changed since the counters were taken."""
+    when the transforms' source has changed since the counters were taken."""
     import hashlib
     import re
     try:
         text = open(os.path.join(ROOT, "profiles", "water330_sigma_counters.md")).read()
-        src = open(os.path.join(ROOT, "paper_2505_24807_amd", "csrc", "gemm.hip"), "rb").read()
+        src = open(os.path.join(ROOT, "paper_2505_24807_amd", "csrc", "planes.hip"), "rb").read()
     except OSError:
         return None
-    m = re.search(r"TRAFFIC (\S+) k32_bytes=(\S+) flops_k32=(\S+) gemm_src_sha1=(\w+)", text)
+    m = re.search(r"TRAFFIC (\S+) k32_bytes=(\S+) flops_k32=(\S+) planes_src_sha1=(\w+)", text)
     if not m or m.group(1) != kernel_tag or hashlib.sha1(src).hexdigest()[:12] != m.group(4):
         return None
     return float(m.group(2)) * flops_per_launch / float(m.group(3))
@@ -179,12 +180,13 @@ def roofline_of(r, dtype):
     ms, launches, flops = phase[0, p], phase[1, p], phase[2, p]
     avg_s = ms * 1e-3 / launches
     achieved = flops / launches / avg_s / 1e12
-    ctype = {"fp64": "double", "fp32": "float", "bf16x3": "float, split bfloat16"}[dtype]
-    traffic = _traffic("gemm128_kernel<float>:G_C_virt", flops / launches) if (dtype == "fp32" and p == 3) else None
+    kernel = {"fp64": "gemm_tile_kernel<double>", "fp32": "plane_gemm_kernel<3 planes, 6 bfloat16 products>",
+              "bf16x3": "plane_gemm_kernel<2 planes, 3 bfloat16 products>"}[dtype]
+    traffic = _traffic("plane_gemm_kernel<3>:G_C_virt", flops / launches) if (dtype == "fp32" and p == 3) else None
     return {"bound": "mfma", "achieved": round(achieved, 3), "peak": PEAK[dtype], "unit": "TFLOP/s",
             "frac": round(achieved / PEAK[dtype], 4),
             "traffic": round(traffic / 1e9, 3) if traffic else None, "traffic_unit": "GB per launch",
-            "kernel": (f"gemm128x3_kernel<{ctype}>" if dtype == "bf16x3" else f"gemm128_kernel<{ctype}>") + f" ({seqx.Stats.PHASES[p]})",
+            "kernel": f"{kernel} ({seqx.Stats.PHASES[p]})",
             "flops_per_launch": flops / launches, "avg_launch_ms": ms / launches}
 
 
@@ -243,8 +245,8 @@ def batched_c4(ctx, steps, loop=True):
             "autotune_s": round(t_tune, 3),
             "fused_sigma_s": round(tsig, 4),
             "fused_sigma_roofline": {"bound": "mfma", "achieved": round(fl / tsig / 1e12, 3) if tsig > 0 else None,
-                                     "peak": PEAK["fp32"], "unit": "TFLOP/s",
-                                     "frac": round(fl / tsig / 1e12 / PEAK["fp32"], 4) if tsig > 0 else None,
+                                     "peak": PEAK["fp32_cores"], "unit": "TFLOP/s",
+                                     "frac": round(fl / tsig / 1e12 / PEAK["fp32_cores"], 4) if tsig > 0 else None,
                                      "kernel": "sigma_items_kernel<float>"},
             "batched_fp64_s": round(t_b64, 4),
             "per_molecule_fp64_loop_s": round(t_loop, 3) if loop else None, "per_molecule_fp64_loop_n_sigma": n_loop,
