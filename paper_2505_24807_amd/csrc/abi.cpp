@@ -331,7 +331,8 @@ void prepare_parallel(seqx_ctx* ctx, seqx_job* job, int nmol, const int32_t* nat
       if (!dm->scf_done) small.push_back(dm.get());
     if (small.empty()) break;
     const auto t0 = std::chrono::steady_clock::now();
-    run_scf_small(small, so, job->ssw, ctx->stream);
+    ScfSmallWork work;  // up to 1 GB for a large batch: not kept with the job
+    run_scf_small(small, so, work, ctx->stream);
     t_scf[0] += 1e3 * std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   }
   double ti = 0.0, ts = 0.0;
