@@ -50,12 +50,13 @@ PhaseTimer::~PhaseTimer() {
 
 void forward_transform(const DeviceMolecule& m, int k, const double* X, double* T, SigmaWork& w, hipStream_t st) {
   const int n = m.nao, o = m.nocc, v = m.nvirt;
-  w.T1.ensure(static_cast<size_t>(k) * n * v);
+  w.buf.ensure(static_cast<size_t>(k) * n * v * sizeof(double));
+  double* T1 = reinterpret_cast<double*>(w.buf.p);
   // T1_I (n x v) = C[:, :o] (n x o, ld n) * X_I (o x v)
-  dgemm(st, false, false, n, v, o, 1.0, m.C.p, n, 0, X, v, static_cast<long>(o) * v, 0.0, w.T1.p, v,
+  dgemm(st, false, false, n, v, o, 1.0, m.C.p, n, 0, X, v, static_cast<long>(o) * v, 0.0, T1, v,
         static_cast<long>(n) * v, k);
   // T_I (n x n) = T1_I * C[:, o:]^T, one GEMM over the stacked T1_I
-  dgemm(st, false, true, k * n, n, v, 1.0, w.T1.p, v, 0, m.C.p + o, n, 0, 0.0, T, n, 0, 1);
+  dgemm(st, false, true, k * n, n, v, 1.0, T1, v, 0, m.C.p + o, n, 0, 0.0, T, n, 0, 1);
 }
 
 namespace {
@@ -309,37 +310,18 @@ namespace {
 void sigma_build_any(const DeviceMolecule& m, int theory, int k, const double* V, double* out1, double* out2,
                      const float* Vf, float* out1f, float* out2f, SigmaWork& w, hipStream_t st, int chunk,
                      long out_stride, int precision) {
-  const int n = m.nao, o = m.nocc, v = m.nvirt;
-  const long nn = static_cast<long>(n) * n, nv = static_cast<long>(n) * v, ov = static_cast<long>(o) * v;
+  const long ov = static_cast<long>(m.nocc) * m.nvirt;
   const long os = out_stride > 0 ? out_stride : ov;
   const bool tdhf = theory == 1;
   const bool f32io = Vf != nullptr;
   check_sigma_args(m, precision);
   if (f32io && precision == kPrecFP64) throw Error(kEArg, "FP32 vectors need a low-precision transform mode");
+  const bool planes = has_planes(m, precision);
   for (int c0 = 0; c0 < k; c0 += chunk) {
     const int kc = std::min(chunk, k - c0);
-    const int nb = tdhf ? 2 * kc : kc;
     ChunkBufs b;
-    if (precision != kPrecFP64) {
-      const bool planes = has_planes(m, precision);
-      w.low.ensure(carve_chunk(m, theory, kc, precision, planes, nullptr, nullptr));
-      carve_chunk(m, theory, kc, precision, planes, w.low.p, &b);
-    } else {
-      w.R.ensure(static_cast<size_t>(kc) * nn);
-      w.F.ensure(static_cast<size_t>(nb) * nn);
-      w.Z.ensure(static_cast<size_t>(nb) * nv);
-      w.T1.ensure(static_cast<size_t>(kc) * nv);
-      b.R = w.R.p;
-      b.F = w.F.p;
-      b.Z = w.Z.p;
-      b.T1 = w.T1.p;
-      w.g.r.ensure(static_cast<size_t>(kc) * m.np);
-      w.g.J.ensure(static_cast<size_t>(kc) * m.np);
-      w.g.ws.ensure(dots_workspace(kc, m.np, m.np));
-      b.gr = w.g.r.p;
-      b.gJ = w.g.J.p;
-      b.gws = w.g.ws.p;
-    }
+    w.buf.ensure(carve_chunk(m, theory, kc, precision, planes, nullptr, nullptr));
+    carve_chunk(m, theory, kc, precision, planes, w.buf.p, &b);
     std::array<hipEvent_t, kNumPhases + 1> ev;
     for (auto& e : ev) SEQX_HIP(hipEventCreate(&e));
     bool merged;

@@ -30,9 +30,10 @@ struct PhaseTimer {
 enum SigmaPrecision { kPrecFP64 = 0, kPrecFP32 = 1, kPrecBF16 = 2, kPrecBF16x3 = 3 };
 
 struct SigmaWork {
-  DBuf<double> T1, R, F, Z;
-  DBuf<unsigned char> low;  // intermediates of the low-precision transforms
-  GWork g;
+  // intermediates of one chunk of vectors, in whichever precision it runs: one
+  // buffer, as a solve that changes precision uses one set at a time ((H2O)330,
+  // 32 vectors: 2.4 GB of planes, 4.0 GB of FP64 matrices)
+  DBuf<unsigned char> buf;
   PhaseTimer timer;
 };
 
