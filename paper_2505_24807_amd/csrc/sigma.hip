@@ -316,11 +316,24 @@ void sigma_build_any(const DeviceMolecule& m, int theory, int k, const double* V
   const bool f32io = Vf != nullptr;
   check_sigma_args(m, precision);
   if (f32io && precision == kPrecFP64) throw Error(kEArg, "FP32 vectors need a low-precision transform mode");
-  const bool planes = has_planes(m, precision);
-  for (int c0 = 0; c0 < k; c0 += chunk) {
-    const int kc = std::min(chunk, k - c0);
+  bool planes = has_planes(m, precision);
+  for (int c0 = 0, kc = 0; c0 < k; c0 += kc) {
+    kc = std::min(chunk, k - c0);
+    // Where memory is short, fewer vectors at a time, down to one, and then the
+    // FP32 matrices (two thirds of the planes): what 32 vectors as FP32 matrices
+    // need is always enough.
+    for (;;) {
+      try {
+        w.buf.ensure(carve_chunk(m, theory, kc, precision, planes, nullptr, nullptr));
+        break;
+      } catch (const Error& e) {
+        if (e.status != kENoMem || (kc == 1 && !planes)) throw;
+        (void)hipGetLastError();  // a failed hipMalloc would be reported by the next launch check
+        if (kc > 1) chunk = kc = (kc + 1) / 2;
+        else planes = false;
+      }
+    }
     ChunkBufs b;
-    w.buf.ensure(carve_chunk(m, theory, kc, precision, planes, nullptr, nullptr));
     carve_chunk(m, theory, kc, precision, planes, w.buf.p, &b);
     std::array<hipEvent_t, kNumPhases + 1> ev;
     for (auto& e : ev) SEQX_HIP(hipEventCreate(&e));

@@ -59,3 +59,34 @@ def test_both_precisions_share_one_workspace(pooled, low):
     larger = max(held[(seqx.FP64,)], held[(low,)])
     assert min(held.values()) > 8 * 32 * o * v
     assert held[(low, seqx.FP64)] <= larger and held[(seqx.FP64, low)] <= larger
+
+
+# 32 vectors: fewer at a time, the same values; 1 vector: FP32 matrices instead of planes
+@pytest.mark.parametrize("theory", [seqx.CIS, seqx.TDHF])
+@pytest.mark.parametrize("k", [32, 1])
+def test_products_in_the_memory_of_fp32_matrices(pooled, theory, k):
+    """FP32 products need no more memory than V, R, F, T and Z as FP32 matrices, though planes take half as much again.
+    Bar of the second form: 8 n u of the largest element, u = 2^-24 (four chained sums of at most n terms)."""
+    ctx, pool = pooled
+    mol = molecules.water_cluster(67, 67)
+    print(f"[gpu] products in little memory {mol.name} k={k} theory={theory}", flush=True)
+    job = ctx.prepare([mol.natoms], mol.Z, mol.xyz)
+    n, o, v = job.dims()
+    V = np.random.default_rng(4).normal(size=(k, o, v))
+    nb, npair = (2 if theory == seqx.TDHF else 1) * k, 12 * 67
+    matrices = 4 * (k * (o * v + n * v + n * n) + nb * (n * n + n * v))
+    contraction = 8 * (2 * k * npair + 16 * min(k, 48) * npair) + 16 * 256
+    vectors = 8 * k * o * v * (3 if theory == seqx.TDHF else 2)
+    pool.limit = pool.now + matrices + contraction + vectors
+    little = job.sigma(V, theory=theory, precision=seqx.FP32)
+    pool.limit = None
+    full = job.sigma(V, theory=theory, precision=seqx.FP32)
+    for a, b in zip(little, full):
+        if a is None:
+            continue
+        if k > 1:
+            assert np.array_equal(a, b)
+        else:
+            assert np.abs(a - b).max() <= 8 * n * 2.0 ** -24 * np.abs(b).max()
+            assert not np.array_equal(a, b)
+    job.free()
