@@ -149,6 +149,27 @@ __global__ void check_words_kernel(const double* __restrict__ w2, const int* __r
   }
 }
 
+// largest |element| of T - [0 I], T the nr x (S + nr) overlaps of the last nr
+// basis rows with all of them (NaN if one is)
+__global__ void __launch_bounds__(1024) overlap_error_kernel(int nr, int S, const double* __restrict__ T,
+                                                             double* __restrict__ out) {
+  __shared__ double red[1024];
+  const int ld = S + nr;
+  double m = 0.0;
+  for (long x = threadIdx.x; x < static_cast<long>(nr) * ld; x += 1024) {
+    const int r = static_cast<int>(x / ld), c = static_cast<int>(x % ld);
+    const double e = fabs(T[x] - (c == S + r ? 1.0 : 0.0));
+    if (!(e <= m)) m = e;
+  }
+  red[threadIdx.x] = m;
+  __syncthreads();
+  for (int h = 512; h > 0; h >>= 1) {
+    if (threadIdx.x < h && !(red[threadIdx.x + h] <= red[threadIdx.x])) red[threadIdx.x] = red[threadIdx.x + h];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) out[0] = red[0];
+}
+
 __global__ void reduce_rows_kernel(int K, int nb, const double* __restrict__ part, double* __restrict__ out) {
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= K) return;
@@ -370,46 +391,68 @@ void dts(hipStream_t st, int ns, const TX* X, long ldx, int nt, const TY* Y, lon
 
 // Orthonormalise the nc rows of Wc against V[0:S] and among themselves, append
 // the kept directions at V[S:]; returns how many were kept.  Wc: FP64 rows, or
-// FP32 rows beside an FP32 basis (inner products and sums in FP64 either way).
+// FP32 rows beside an FP32 basis (inner products and sums in FP64 either way);
+// overwritten.
+//
+// One pass is a projection against V and a Loewdin step among the rows.  It
+// leaves the new rows an overlap with V of about (|V^T V - I| + u) / sqrt(lam),
+// lam the smallest kept eigenvalue of their Gram matrix, which is far below one
+// for corrections that lie largely in the basis or nearly repeat each other: if
+// that stayed, the loss would grow by such a factor in every iteration, until
+// the basis is linearly dependent and the projected matrices have roots at zero.
+// So the overlaps of the new rows with the whole basis and each other are formed
+// (one read of V) and the pass is repeated on them while they are above the
+// rounding of the rows.  A direction that loses three quarters of its norm in a
+// repeated pass lies in the basis to working precision and is left out.
+constexpr double kOrthTol64 = 1e-13, kOrthTol32 = 5e-7;
+constexpr int kOrthPasses = 4;
 template <class TV, class TW>
 int orthonormalize_append(hipStream_t st, DenseSolver& ds, DavWork& w, long nov, int nc, TW* Wc, int S, TV* V,
                           int max_keep) {
   double* G = w.G.p;
-  double* Cc = w.Q.p;  // nc x S coefficients, reused below for the Loewdin vectors
+  double* Cc = w.Q.p;  // overlaps with the basis: nc x S, then kept x (S + kept)
+  TV* Vn = V + static_cast<long>(S) * nov;
+  // V[S + r] = sum_c Q(c, j0 + r) src_c / sqrt(lam) over the eigenpairs (lam, Q) of the Gram
+  // matrix of the m rows of src with lam > lmin; the number of them, at most max_keep
+  auto loewdin = [&](const auto* src, int m, double lmin) -> int {
+    dts(st, m, src, nov, m, src, nov, nov, G, m, w.ws.p);
+    ds.eigh_lowest(m, G, m, m, w.w2.p);
+    std::vector<double> lam(m);
+    d2h(lam.data(), w.w2.p, m, st);
+    SEQX_HIP(hipStreamSynchronize(st));
+    int j0 = 0;
+    while (j0 < m && !(lam[j0] > lmin)) ++j0;
+    j0 = std::max(j0, m - max_keep);
+    if (j0 >= m) return 0;
+    hipLaunchKernelGGL(invsqrt_cols_kernel, dim3(m - j0), dim3(64), 0, st, G, m, m, j0, w.w2.p);
+    SEQX_LAUNCH_CHECK();
+    comb(st, m - j0, nov, m, 1.0, G + static_cast<long>(j0) * m, m, src, nov, 0.0, Vn, nov);
+    return m - j0;
+  };
   dts(st, nc, Wc, nov, nc, Wc, nov, nov, G, nc, w.ws.p);
   hipLaunchKernelGGL(scale_rows_kernel<TW>, dim3(ceil_div(nov, 256), nc), dim3(256), 0, st, nov, Wc, G, nc);
   SEQX_LAUNCH_CHECK();
-  // classical Gram-Schmidt against V; a second pass only when a unit row lost
-  // more than three quarters of its norm ("twice is enough")
-  for (int pass = 0; pass < 2 && S > 0; ++pass) {
+  if (S > 0) {
     dts(st, nc, Wc, nov, S, V, nov, nov, Cc, S, w.ws.p);
     comb(st, nc, nov, S, -1.0, Cc, S, V, nov, 1.0, Wc, nov);
-    dts(st, nc, Wc, nov, nc, Wc, nov, nov, G, nc, w.ws.p);
-    if (pass == 1) break;
-    std::vector<double> g(static_cast<size_t>(nc) * nc);
-    d2h(g.data(), G, g.size(), st);
+  }
+  int kept = loewdin(Wc, nc, 1e-12);
+  const double tol = sizeof(TV) == 8 ? kOrthTol64 : kOrthTol32;
+  TV* rows = reinterpret_cast<TV*>(Wc);  // Wc's storage, for rows of V's type
+  static_assert(sizeof(TV) <= sizeof(TW), "rows of V fit the storage of Wc");
+  for (int pass = 1; pass < kOrthPasses && kept > 0; ++pass) {
+    const int S1 = S + kept;
+    dts(st, kept, Vn, nov, S1, V, nov, nov, Cc, S1, w.ws.p);
+    hipLaunchKernelGGL(overlap_error_kernel, dim3(1), dim3(1024), 0, st, kept, S, Cc, w.w2.p);
+    SEQX_LAUNCH_CHECK();
+    double err = 0.0;
+    d2h(&err, w.w2.p, 1, st);
     SEQX_HIP(hipStreamSynchronize(st));
-    bool again = false;
-    for (int r = 0; r < nc; ++r) again = again || g[static_cast<size_t>(r) * nc + r] < 0.25;
-    if (!again) break;
+    if (err <= tol) break;
+    if (S > 0) comb(st, kept, nov, S, -1.0, Cc, S1, V, nov, 1.0, Vn, nov);
+    SEQX_HIP(hipMemcpyAsync(rows, Vn, static_cast<size_t>(kept) * nov * sizeof(TV), hipMemcpyDeviceToDevice, st));
+    kept = loewdin(rows, kept, 0.25);
   }
-  if (S == 0) dts(st, nc, Wc, nov, nc, Wc, nov, nov, G, nc, w.ws.p);
-  ds.eigh_lowest(nc, G, nc, nc, w.w2.p);
-  std::vector<double> lam(nc);
-  d2h(lam.data(), w.w2.p, nc, st);
-  SEQX_HIP(hipStreamSynchronize(st));
-  int j0 = 0;
-  while (j0 < nc && !(lam[j0] > 1e-12)) ++j0;
-  int kept = nc - j0;
-  if (kept > max_keep) {
-    j0 = nc - max_keep;
-    kept = max_keep;
-  }
-  if (kept <= 0) return 0;
-  hipLaunchKernelGGL(invsqrt_cols_kernel, dim3(kept), dim3(64), 0, st, G, nc, nc, j0, w.w2.p);
-  SEQX_LAUNCH_CHECK();
-  // V[S + r] = sum_c Q(c, j0 + r) W_c
-  comb(st, kept, nov, nc, 1.0, G + static_cast<long>(j0) * nc, nc, Wc, nov, 0.0, V + static_cast<long>(S) * nov, nov);
   return kept;
 }
 
@@ -524,7 +567,7 @@ DavResult davidson(DeviceMolecule& m, const DavOptions& opt, DenseSolver& ds, Da
   w.W.ensure(static_cast<size_t>(std::max(ncand_max, opt.guess ? opt.nguess : 0)) * nov);
   w.scratch.ensure(static_cast<size_t>(ps) * q_max * nov);
   w.G.ensure(static_cast<size_t>(ps) * Smax * Smax);
-  w.Q.ensure(static_cast<size_t>(std::max(ncand_max, q_max)) * Smax);
+  w.Q.ensure(static_cast<size_t>(std::max(std::max(ncand_max, q_max), opt.guess ? opt.nguess : 0)) * Smax);
   // FP32 basis rows and products while the products are formed in low
   // precision (their own rounding is far coarser); FP64 after the switch
   bool lb = davidson_f32_basis(nov, opt.precision);
