@@ -149,17 +149,19 @@ __global__ void check_words_kernel(const double* __restrict__ w2, const int* __r
   }
 }
 
-// largest |element| of T - [0 I], T the nr x (S + nr) overlaps of the last nr
-// basis rows with all of them (NaN if one is)
-__global__ void __launch_bounds__(1024) overlap_error_kernel(int nr, int S, const double* __restrict__ T,
+// T: the nr x (S + nr) overlaps of the last nr basis rows with all of them.
+// out = largest |element| of T - [0 I] (NaN if one is); T becomes the
+// coefficients [-T_v, (3 I - T_q) / 2] that make the rows orthonormal to first order
+__global__ void __launch_bounds__(1024) overlap_error_kernel(int nr, int S, double* __restrict__ T,
                                                              double* __restrict__ out) {
   __shared__ double red[1024];
   const int ld = S + nr;
   double m = 0.0;
   for (long x = threadIdx.x; x < static_cast<long>(nr) * ld; x += 1024) {
     const int r = static_cast<int>(x / ld), c = static_cast<int>(x % ld);
-    const double e = fabs(T[x] - (c == S + r ? 1.0 : 0.0));
+    const double t = T[x], one = c == S + r ? 1.0 : 0.0, e = fabs(t - one);
     if (!(e <= m)) m = e;
+    T[x] = c < S ? -t : 1.5 * one - 0.5 * t;
   }
   red[threadIdx.x] = m;
   __syncthreads();
@@ -401,10 +403,13 @@ void dts(hipStream_t st, int ns, const TX* X, long ldx, int nt, const TY* Y, lon
 // that stayed, the loss would grow by such a factor in every iteration, until
 // the basis is linearly dependent and the projected matrices have roots at zero.
 // So the overlaps of the new rows with the whole basis and each other are formed
-// (one read of V) and the pass is repeated on them while they are above the
-// rounding of the rows.  A direction that loses three quarters of its norm in a
-// repeated pass lies in the basis to working precision and is left out.
-constexpr double kOrthTol64 = 1e-13, kOrthTol32 = 5e-7;
+// (one read of V).  Above the rounding of the rows a first-order step takes them
+// out, which leaves their square (one combination of the basis rows); where that
+// is not enough the whole pass is repeated.  A direction that loses three
+// quarters of its norm in a repeated pass lies in the basis to working precision
+// and is left out.
+constexpr double kOrthTol64 = 1e-13, kOrthFirst64 = 1e-7;
+constexpr double kOrthTol32 = 5e-7, kOrthFirst32 = 1e-4;
 constexpr int kOrthPasses = 4;
 template <class TV, class TW>
 int orthonormalize_append(hipStream_t st, DenseSolver& ds, DavWork& w, long nov, int nc, TW* Wc, int S, TV* V,
@@ -438,6 +443,7 @@ int orthonormalize_append(hipStream_t st, DenseSolver& ds, DavWork& w, long nov,
   }
   int kept = loewdin(Wc, nc, 1e-12);
   const double tol = sizeof(TV) == 8 ? kOrthTol64 : kOrthTol32;
+  const double first = sizeof(TV) == 8 ? kOrthFirst64 : kOrthFirst32;
   TV* rows = reinterpret_cast<TV*>(Wc);  // Wc's storage, for rows of V's type
   static_assert(sizeof(TV) <= sizeof(TW), "rows of V fit the storage of Wc");
   for (int pass = 1; pass < kOrthPasses && kept > 0; ++pass) {
@@ -449,7 +455,12 @@ int orthonormalize_append(hipStream_t st, DenseSolver& ds, DavWork& w, long nov,
     d2h(&err, w.w2.p, 1, st);
     SEQX_HIP(hipStreamSynchronize(st));
     if (err <= tol) break;
-    if (S > 0) comb(st, kept, nov, S, -1.0, Cc, S1, V, nov, 1.0, Vn, nov);
+    if (err <= first) {
+      comb(st, kept, nov, S1, 1.0, Cc, S1, V, nov, 0.0, rows, nov);
+      SEQX_HIP(hipMemcpyAsync(Vn, rows, static_cast<size_t>(kept) * nov * sizeof(TV), hipMemcpyDeviceToDevice, st));
+      break;
+    }
+    if (S > 0) comb(st, kept, nov, S, 1.0, Cc, S1, V, nov, 1.0, Vn, nov);
     SEQX_HIP(hipMemcpyAsync(rows, Vn, static_cast<size_t>(kept) * nov * sizeof(TV), hipMemcpyDeviceToDevice, st));
     kept = loewdin(rows, kept, 0.25);
   }
