@@ -421,10 +421,14 @@ int orthonormalize_append(hipStream_t st, DenseSolver& ds, DavWork& w, long nov,
   // matrix of the m rows of src with lam > lmin; the number of them, at most max_keep
   auto loewdin = [&](const auto* src, int m, double lmin) -> int {
     dts(st, m, src, nov, m, src, nov, nov, G, m, w.ws.p);
-    ds.eigh_lowest(m, G, m, m, w.w2.p);
-    std::vector<double> lam(m);
-    d2h(lam.data(), w.w2.p, m, st);
-    SEQX_HIP(hipStreamSynchronize(st));
+    std::vector<double> lam(m + 1);  // and the solver's info word
+    for (bool library : {false, true}) {
+      ds.eigh_lowest(m, G, m, m, w.w2.p, w.w2.p + m, library);
+      d2h(lam.data(), w.w2.p, m + 1, st);
+      SEQX_HIP(hipStreamSynchronize(st));
+      if (lam[m] != kEigGaveUp) break;
+    }
+    if (lam[m] != 0.0) throw Error(kEDevice, "eigensolver of the Gram matrix failed");
     int j0 = 0;
     while (j0 < m && !(lam[j0] > lmin)) ++j0;
     j0 = std::max(j0, m - max_keep);
@@ -553,7 +557,7 @@ DavResult davidson(DeviceMolecule& m, const DavOptions& opt, DenseSolver& ds, Da
   w.Lm.ensure(static_cast<size_t>(Smax) * Smax);
   w.Tmp.ensure(static_cast<size_t>(Smax) * Smax);
   w.Hs.ensure(static_cast<size_t>(Smax) * Smax);
-  w.w2.ensure(Smax);
+  w.w2.ensure(Smax + 1);  // eigenvalues and an info word
   // Restarts keep, beside the current Ritz coefficients, those of the
   // previous iteration (padded with zeros for the rows added since): the
   // basis after a collapse spans both, as in a locally optimal block
@@ -752,7 +756,7 @@ DavResult davidson(DeviceMolecule& m, const DavOptions& opt, DenseSolver& ds, Da
     if (!use_prev || it < 2 || last_collapse == it - 1) return nullptr;
     return w.coef.p + static_cast<long>((it - 1) & 1) * 2 * K * Smax;
   };
-  bool converged = false;
+  bool converged = false, library = false;
   int it = 0;
   try {
     for (it = 1; it <= opt.max_iter; ++it) {
@@ -791,67 +795,75 @@ DavResult davidson(DeviceMolecule& m, const DavOptions& opt, DenseSolver& ds, Da
       S = S1;
       res.max_subspace = std::max(res.max_subspace, S);
       // 3. subspace eigenproblem
-      itimer.mark(kDavSmallEig);
       // t (TDHF) or x (CIS): S x K, ld Smax; u (TDHF) next to it
       double* tco = w.coef.p + static_cast<long>(it & 1) * 2 * K * Smax;
       double* uco = tco + static_cast<long>(K) * Smax;
       s_at[it & 1] = S;
-      if (tdhf) {
-        copy(st, w.Lm.p, w.Mm.p, static_cast<long>(S) * Smax);
-        ds.potrf(S, w.Lm.p, Smax);
-        zero_upper_cm(st, S, w.Lm.p, Smax);
-        dgemm_cm(st, false, false, S, S, S, 1.0, w.Mp.p, Smax, w.Lm.p, Smax, 0.0, w.Tmp.p, Smax);  // M+ L
-        dgemm_cm(st, true, false, S, S, S, 1.0, w.Lm.p, Smax, w.Tmp.p, Smax, 0.0, w.Hs.p, Smax);    // L^T M+ L
-        ds.eigh_lowest(S, w.Hs.p, Smax, K, w.w2.p);  // only the K lowest pairs are used
-        hipLaunchKernelGGL(omega_kernel, dim3(ceil_div(K, 64)), dim3(64), 0, st, K, w.w2.p, om, 1);
-        dgemm_cm(st, false, false, S, K, S, 1.0, w.Lm.p, Smax, w.Hs.p, Smax, 0.0, tco, Smax);   // L z
-        dgemm_cm(st, false, false, S, K, S, 1.0, w.Tmp.p, Smax, w.Hs.p, Smax, 0.0, uco, Smax);  // M+ L z
-        hipLaunchKernelGGL(scale_cols_kernel, dim3(K), dim3(256), 0, st, tco, Smax, S, K, om, 0.5);
-        hipLaunchKernelGGL(scale_cols_kernel, dim3(K), dim3(256), 0, st, uco, Smax, S, K, om, 1.5);
-      } else {
-        copy(st, w.Hs.p, w.Mp.p, static_cast<long>(S) * Smax);
-        // K Ritz pairs; 2K where this iteration may end in a collapse (the
-        // basis would overflow, or the low-precision phase may step up)
-        const bool may_collapse = S + K > Smax || prec != kPrecFP64;
-        ds.eigh_lowest(S, w.Hs.p, Smax, may_collapse ? std::min(2 * K, S) : std::min(K, S), w.w2.p);
-        hipLaunchKernelGGL(omega_kernel, dim3(ceil_div(K, 64)), dim3(64), 0, st, K, w.w2.p, om, 0);
-        copy(st, tco, w.Hs.p, static_cast<long>(K) * Smax);
-      }
-      SEQX_LAUNCH_CHECK();
-      // 4. Ritz vectors and products: rows j of Tv = sum_s t(s, j) V_s, etc.
-      itimer.mark(kDavRitz);
-      // [T; U] in one pass over V (t and u are adjacent coefficient columns)
-      if (lb) {
-        comb(st, ps * K, nov, S, 1.0, tco, Smax, w.V32.p, nov, 0.0, Tv32, nov);
-        comb(st, K, nov, S, 1.0, tco, Smax, w.SP32.p, ldp, 0.0, PT32, nov);
-        if (tdhf) comb(st, K, nov, S, 1.0, uco, Smax, w.SP32.p + nov, ldp, 0.0, MU32, nov);
-      } else {
-        dgemm(st, false, false, ps * K, static_cast<int>(nov), S, 1.0, tco, Smax, 0, w.V.p, nov, 0, 0.0, w.Tv.p, nov,
-              0, 1, nullptr);
-        dgemm(st, false, false, K, static_cast<int>(nov), S, 1.0, tco, Smax, 0, w.SP.p, ldp, 0, 0.0, w.PT.p, nov, 0, 1,
-              nullptr);
-        if (tdhf)
-          dgemm(st, false, false, K, static_cast<int>(nov), S, 1.0, uco, Smax, 0, w.SP.p + nov, ldp, 0, 0.0, MU, nov,
+      auto subspace = [&] {
+        itimer.mark(kDavSmallEig);
+        if (tdhf) {
+          copy(st, w.Lm.p, w.Mm.p, static_cast<long>(S) * Smax);
+          ds.potrf(S, w.Lm.p, Smax);
+          zero_upper_cm(st, S, w.Lm.p, Smax);
+          dgemm_cm(st, false, false, S, S, S, 1.0, w.Mp.p, Smax, w.Lm.p, Smax, 0.0, w.Tmp.p, Smax);  // M+ L
+          dgemm_cm(st, true, false, S, S, S, 1.0, w.Lm.p, Smax, w.Tmp.p, Smax, 0.0, w.Hs.p, Smax);    // L^T M+ L
+          ds.eigh_lowest(S, w.Hs.p, Smax, K, w.w2.p, nullptr, library);  // only the K lowest pairs are used
+          hipLaunchKernelGGL(omega_kernel, dim3(ceil_div(K, 64)), dim3(64), 0, st, K, w.w2.p, om, 1);
+          dgemm_cm(st, false, false, S, K, S, 1.0, w.Lm.p, Smax, w.Hs.p, Smax, 0.0, tco, Smax);   // L z
+          dgemm_cm(st, false, false, S, K, S, 1.0, w.Tmp.p, Smax, w.Hs.p, Smax, 0.0, uco, Smax);  // M+ L z
+          hipLaunchKernelGGL(scale_cols_kernel, dim3(K), dim3(256), 0, st, tco, Smax, S, K, om, 0.5);
+          hipLaunchKernelGGL(scale_cols_kernel, dim3(K), dim3(256), 0, st, uco, Smax, S, K, om, 1.5);
+        } else {
+          copy(st, w.Hs.p, w.Mp.p, static_cast<long>(S) * Smax);
+          // K Ritz pairs; 2K where this iteration may end in a collapse (the
+          // basis would overflow, or the low-precision phase may step up)
+          const bool may_collapse = S + K > Smax || prec != kPrecFP64;
+          ds.eigh_lowest(S, w.Hs.p, Smax, may_collapse ? std::min(2 * K, S) : std::min(K, S), w.w2.p,
+                         nullptr, library);
+          hipLaunchKernelGGL(omega_kernel, dim3(ceil_div(K, 64)), dim3(64), 0, st, K, w.w2.p, om, 0);
+          copy(st, tco, w.Hs.p, static_cast<long>(K) * Smax);
+        }
+        SEQX_LAUNCH_CHECK();
+        // 4. Ritz vectors and products: rows j of Tv = sum_s t(s, j) V_s, etc.
+        itimer.mark(kDavRitz);
+        // [T; U] in one pass over V (t and u are adjacent coefficient columns)
+        if (lb) {
+          comb(st, ps * K, nov, S, 1.0, tco, Smax, w.V32.p, nov, 0.0, Tv32, nov);
+          comb(st, K, nov, S, 1.0, tco, Smax, w.SP32.p, ldp, 0.0, PT32, nov);
+          if (tdhf) comb(st, K, nov, S, 1.0, uco, Smax, w.SP32.p + nov, ldp, 0.0, MU32, nov);
+        } else {
+          dgemm(st, false, false, ps * K, static_cast<int>(nov), S, 1.0, tco, Smax, 0, w.V.p, nov, 0, 0.0, w.Tv.p, nov,
                 0, 1, nullptr);
+          dgemm(st, false, false, K, static_cast<int>(nov), S, 1.0, tco, Smax, 0, w.SP.p, ldp, 0, 0.0, w.PT.p, nov, 0, 1,
+                nullptr);
+          if (tdhf)
+            dgemm(st, false, false, K, static_cast<int>(nov), S, 1.0, uco, Smax, 0, w.SP.p + nov, ldp, 0, 0.0, MU, nov,
+                  0, 1, nullptr);
+        }
+        // 5. residual norms
+        if (lb)
+          hipLaunchKernelGGL(residual_norm_kernel<float>, dim3(nbres, K), dim3(256), 0, st, nov, tdhf ? 1 : 0, om, Tv32,
+                             Uv32, PT32, MU32, w.part.p);
+        else
+          hipLaunchKernelGGL(residual_norm_kernel<double>, dim3(nbres, K), dim3(256), 0, st, nov, tdhf ? 1 : 0, om,
+                             w.Tv.p, Uv, w.PT.p, MU, w.part.p);
+        hipLaunchKernelGGL(reduce_rows_kernel, dim3(ceil_div(K, 64)), dim3(64), 0, st, K, nbres, w.part.p, w.rn.p);
+        SEQX_LAUNCH_CHECK();
+        itimer.mark(kDavCheck);
+        // one copy to the host: residual norms, omega, the lowest eigenvalue of
+        // the projected problem (TDHF: omega^2) and the eigh / potrf info words
+        hipLaunchKernelGGL(check_words_kernel, dim3(1), dim3(64), 0, st, w.w2.p, ds.info_device(), w.rn.p + 2 * K);
+        SEQX_LAUNCH_CHECK();
+        d2h(h_chk.data(), w.rn.p, 2 * K + 3, st);
+        SEQX_HIP(hipStreamSynchronize(st));
+        std::copy(h_chk.begin(), h_chk.begin() + K, h_rn.begin());
+        std::copy(h_chk.begin() + K, h_chk.begin() + 2 * K, h_om.begin());
+      };
+      subspace();
+      if (h_chk[2 * K + 1] == kEigGaveUp) {  // the GPU was busy elsewhere: by the library, here and from now on
+        library = true;
+        subspace();
       }
-      // 5. residual norms
-      if (lb)
-        hipLaunchKernelGGL(residual_norm_kernel<float>, dim3(nbres, K), dim3(256), 0, st, nov, tdhf ? 1 : 0, om, Tv32,
-                           Uv32, PT32, MU32, w.part.p);
-      else
-        hipLaunchKernelGGL(residual_norm_kernel<double>, dim3(nbres, K), dim3(256), 0, st, nov, tdhf ? 1 : 0, om,
-                           w.Tv.p, Uv, w.PT.p, MU, w.part.p);
-      hipLaunchKernelGGL(reduce_rows_kernel, dim3(ceil_div(K, 64)), dim3(64), 0, st, K, nbres, w.part.p, w.rn.p);
-      SEQX_LAUNCH_CHECK();
-      itimer.mark(kDavCheck);
-      // one copy to the host: residual norms, omega, the lowest eigenvalue of
-      // the projected problem (TDHF: omega^2) and the eigh / potrf info words
-      hipLaunchKernelGGL(check_words_kernel, dim3(1), dim3(64), 0, st, w.w2.p, ds.info_device(), w.rn.p + 2 * K);
-      SEQX_LAUNCH_CHECK();
-      d2h(h_chk.data(), w.rn.p, 2 * K + 3, st);
-      SEQX_HIP(hipStreamSynchronize(st));
-      std::copy(h_chk.begin(), h_chk.begin() + K, h_rn.begin());
-      std::copy(h_chk.begin() + K, h_chk.begin() + 2 * K, h_om.begin());
       const double h_w2min = h_chk[2 * K];
       const int h_info[2] = {static_cast<int>(h_chk[2 * K + 1]), static_cast<int>(h_chk[2 * K + 2])};
       float ms = 0.f;

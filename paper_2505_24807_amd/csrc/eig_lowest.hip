@@ -67,10 +67,6 @@ __device__ __forceinline__ double rcp_nr(double x) {
 
 // A value not yet published in the exchange area: a NaN that no arithmetic makes.
 constexpr unsigned long long kEmpty = ~0ull;
-// Rounds of polling before a wavefront gives up (about a second): reached only
-// if the other wavefronts of the launch cannot run.
-constexpr int kPollLimit = 1 << 20;
-
 __global__ void __launch_bounds__(256) exchange_fill_kernel(long n, unsigned long long* __restrict__ x, int* failed) {
   const long i = blockIdx.x * 256L + threadIdx.x;
   if (i < n) x[i] = kEmpty;
@@ -98,11 +94,15 @@ __device__ __forceinline__ unsigned long long peek(const double* p) {
 // LDS copies in turn).  GRID = true: wavefronts on different compute units,
 // exchange through memory: every value has a place of its own that holds kEmpty
 // until it is stored, so a reader simply polls the values it needs (device
-// scope; no counter, no ordering between values).  The grid is at most 128
-// single-wavefront workgroups, which are resident together.
+// scope; no counter, no ordering between values).  The grid is at most 64
+// single-wavefront workgroups, which are resident together unless other work
+// holds the GPU: a wavefront that has polled poll_limit rounds (about a second at
+// kEigPollLimit) gives up, so every wait ends.  The matrix is then left as it
+// was and the caller told (kEigGaveUp).
 template <int NC, int NR, int NW, bool GRID>
 __device__ __forceinline__ void tridiagonalise(int n, const double* __restrict__ A, int lda, double* __restrict__ W,
-                                               double* __restrict__ dte, double* xch, int* failed) {
+                                               double* __restrict__ dte, double* xch, int* failed,
+                                                int poll_limit) {
   static_assert(NW * NR >= 64 * NC, "rows must be covered");
   __shared__ double sp[2][GRID ? 1 : 64 * NC], sy[2][GRID ? 1 : 64 * NC];
   const int lane = threadIdx.x & 63;
@@ -220,7 +220,7 @@ __device__ __forceinline__ void tridiagonalise(int n, const double* __restrict__
           y[c] = __longlong_as_double(static_cast<long long>(by));
         }
         if (__all(ready)) break;
-        if (round >= kPollLimit) {
+        if (round >= poll_limit) {
           if (lane == 0) *failed = 1;
           return;
         }
@@ -282,8 +282,8 @@ template <int NC, int NR, int NW, bool GRID>
 __global__ void __launch_bounds__(GRID ? 64 : 64 * NW) tridiag_kernel(int n, const double* __restrict__ A, int lda,
                                                                       double* __restrict__ W,
                                                                       double* __restrict__ dte, double* xch,
-                                                                      int* failed) {
-  tridiagonalise<NC, NR, NW, GRID>(n, A, lda, W, dte, xch, failed);
+                                                                      int* failed, int poll_limit) {
+  tridiagonalise<NC, NR, NW, GRID>(n, A, lda, W, dte, xch, failed, poll_limit);
 }
 
 // ---------------------------------------------------------------- 2. eigenpairs of T
@@ -617,12 +617,16 @@ __global__ void __launch_bounds__(64) reflect_kernel(int n, int lda, const doubl
                                                      const double* __restrict__ tau,
                                                      const double* __restrict__ lam, const double* __restrict__ Z,
                                                      double* __restrict__ A, double* __restrict__ w,
-                                                     const int* __restrict__ failed, int* __restrict__ info) {
-  const int tt = blockIdx.x;
-  reflect<NC>(tt, n, lda, W, tau, Z, A);
-  if (threadIdx.x == 0) {
-    w[tt] = lam[tt];
-    if (tt == 0) info[0] = failed ? *failed : 0;
+                                                     const int* __restrict__ failed, int* __restrict__ info,
+                                                     double* __restrict__ status) {
+  const int tt = blockIdx.x, word = failed && *failed ? kEigGaveUp : 0;
+  if (word == 0) {
+    reflect<NC>(tt, n, lda, W, tau, Z, A);
+    if (threadIdx.x == 0) w[tt] = lam[tt];
+  }
+  if (tt == 0 && threadIdx.x == 0) {
+    info[0] = word;
+    if (status) *status = word;
   }
 }
 
@@ -648,7 +652,7 @@ __global__ void __launch_bounds__(512) batch_tridiag_kernel(EigBatch b) {
   const int m = blockIdx.x;
   if (!b.active[m]) return;
   const BatchScratch s(b, m);
-  tridiagonalise<1, 8, 8, false>(b.n[m], b.A + static_cast<long>(m) * b.ld * b.ld, b.ld, s.W, s.dte, nullptr, nullptr);
+  tridiagonalise<1, 8, 8, false>(b.n[m], b.A + static_cast<long>(m) * b.ld * b.ld, b.ld, s.W, s.dte, nullptr, nullptr, 0);
 }
 
 __global__ void __launch_bounds__(kPairThreads) batch_pair_kernel(EigBatch b) {
@@ -688,7 +692,7 @@ struct EigScratch {
 
 template <int NC>
 void launch_tail(hipStream_t st, int n, double* A, int lda, int k, double* w, const EigScratch& s, const int* failed,
-                 int* info) {
+                 int* info, double* status) {
   hipLaunchKernelGGL(tridiag_pair_kernel<NC>, dim3(k), dim3(kPairThreads), 0, st, n, s.dte, s.lam, s.Z, s.norm);
   if (k > 1) {
     if (static_cast<long>(k) * n <= kClusterLds)
@@ -697,21 +701,21 @@ void launch_tail(hipStream_t st, int n, double* A, int lda, int k, double* w, co
       hipLaunchKernelGGL(cluster_kernel<false>, dim3(1), dim3(kClusterThreads), 0, st, n, k, s.lam, s.norm, s.Z);
   }
   hipLaunchKernelGGL(reflect_kernel<NC>, dim3(k), dim3(64), 0, st, n, lda, s.W, s.dte + 2 * n, s.lam, s.Z, A, w,
-                     failed, info);
+                     failed, info, status);
 }
 
 template <int NC, int NR, int NW, bool GRID>
-void launch_tridiag(hipStream_t st, int n, const double* A, int lda, const EigScratch& s) {
+void launch_tridiag(hipStream_t st, int n, const double* A, int lda, const EigScratch& s, int poll_limit) {
   int* failed = reinterpret_cast<int*>(s.failed);
   if constexpr (GRID) {
     const long nx = 2L * n * n;
     hipLaunchKernelGGL(exchange_fill_kernel, dim3(ceil_div(nx, 256)), dim3(256), 0, st, nx,
                        reinterpret_cast<unsigned long long*>(s.xch), failed);
     hipLaunchKernelGGL((tridiag_kernel<NC, NR, NW, true>), dim3(NW), dim3(64), 0, st, n, A, lda, s.W, s.dte, s.xch,
-                       failed);
+                       failed, poll_limit);
   } else {
     hipLaunchKernelGGL((tridiag_kernel<NC, NR, NW, false>), dim3(1), dim3(64 * NW), 0, st, n, A, lda, s.W, s.dte,
-                       s.xch, failed);
+                       s.xch, failed, 0);
   }
 }
 
@@ -736,19 +740,20 @@ size_t eig_lowest_scratch(int n, int k) {
          (n > kEigOneGroup ? 2 * static_cast<size_t>(n) * n : 0);
 }
 
-void launch_eig_lowest(hipStream_t st, int n, double* A, int lda, int k, double* w, double* scratch, int* info) {
+void launch_eig_lowest(hipStream_t st, int n, double* A, int lda, int k, double* w, double* scratch, int* info,
+                       double* status, int poll_limit) {
   const EigScratch s(scratch, n, k);
-  if (n <= 64) launch_tridiag<1, 8, 8, false>(st, n, A, lda, s);
-  else if (n <= 128) launch_tridiag<2, 16, 8, false>(st, n, A, lda, s);
-  else if (n <= 192) launch_tridiag<3, 8, 24, true>(st, n, A, lda, s);
-  else if (n <= 256) launch_tridiag<4, 8, 32, true>(st, n, A, lda, s);
-  else if (n <= 384) launch_tridiag<6, 8, 48, true>(st, n, A, lda, s);
-  else launch_tridiag<8, 8, 64, true>(st, n, A, lda, s);
+  if (n <= 64) launch_tridiag<1, 8, 8, false>(st, n, A, lda, s, poll_limit);
+  else if (n <= 128) launch_tridiag<2, 16, 8, false>(st, n, A, lda, s, poll_limit);
+  else if (n <= 192) launch_tridiag<3, 8, 24, true>(st, n, A, lda, s, poll_limit);
+  else if (n <= 256) launch_tridiag<4, 8, 32, true>(st, n, A, lda, s, poll_limit);
+  else if (n <= 384) launch_tridiag<6, 8, 48, true>(st, n, A, lda, s, poll_limit);
+  else launch_tridiag<8, 8, 64, true>(st, n, A, lda, s, poll_limit);
   const int* failed = n > kEigOneGroup ? reinterpret_cast<const int*>(s.failed) : nullptr;
-  if (n <= 64) launch_tail<1>(st, n, A, lda, k, w, s, failed, info);
-  else if (n <= 128) launch_tail<2>(st, n, A, lda, k, w, s, failed, info);
-  else if (n <= 256) launch_tail<4>(st, n, A, lda, k, w, s, failed, info);
-  else launch_tail<8>(st, n, A, lda, k, w, s, failed, info);
+  if (n <= 64) launch_tail<1>(st, n, A, lda, k, w, s, failed, info, status);
+  else if (n <= 128) launch_tail<2>(st, n, A, lda, k, w, s, failed, info, status);
+  else if (n <= 256) launch_tail<4>(st, n, A, lda, k, w, s, failed, info, status);
+  else launch_tail<8>(st, n, A, lda, k, w, s, failed, info, status);
   SEQX_LAUNCH_CHECK();
 }
 

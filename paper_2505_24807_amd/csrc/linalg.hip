@@ -1,5 +1,6 @@
 // Small device kernels and the rocSOLVER wrapper.
 #include <algorithm>
+#include <cstdlib>
 #include <rocsolver/rocsolver.h>
 
 #include "jacobi.hpp"
@@ -18,6 +19,7 @@ DenseSolver::DenseSolver(hipStream_t st) : st_(st) {
   SEQX_RB(rocblas_create_handle(&h_));
   SEQX_RB(rocblas_set_stream(h_, st_));
   info_.alloc(2);
+  if (const char* e = std::getenv("SEQX_EIG_POLL_LIMIT")) poll_limit_ = std::max(0, std::atoi(e));
 }
 
 DenseSolver::~DenseSolver() {
@@ -28,7 +30,8 @@ namespace {
 // n <= NMAX: one workgroup of NT threads, Jacobi in LDS on the lower
 // triangle (no failure mode; info = 0).
 template <int NT, int NMAX>
-__global__ void __launch_bounds__(NT) small_eigh_kernel(int n, double* A, int lda, double* w, int* info) {
+__global__ void __launch_bounds__(NT) small_eigh_kernel(int n, double* A, int lda, double* w, int* info,
+                                                         double* status) {
   __shared__ JacobiLds L;
   for (int idx = threadIdx.x; idx < n * n; idx += NT) {
     const int i = idx / n, j = idx % n;
@@ -41,35 +44,46 @@ __global__ void __launch_bounds__(NT) small_eigh_kernel(int n, double* A, int ld
     A[i + static_cast<long>(r) * lda] = L.Q[i][L.perm[r]];
   }
   for (int r = threadIdx.x; r < n; r += NT) w[r] = L.A[L.perm[r]][L.perm[r]];
-  if (threadIdx.x == 0) info[0] = 0;
+  if (threadIdx.x == 0) {
+    info[0] = 0;
+    if (status) *status = 0.0;
+  }
 }
+
+__global__ void word_kernel(const int* __restrict__ info, double* __restrict__ status) { *status = *info; }
 }  // namespace
 
-void DenseSolver::eigh(int n, double* A, int lda, double* w) {
+void DenseSolver::eigh(int n, double* A, int lda, double* w, double* status) {
   if (n <= 0) return;
   if (n <= kJacobiMax) {
     // one wavefront where it holds a round at one 2 x 2 block a lane: n = 10 39 us
     // against 43 with four; n = 20 157 against 102
     if (n <= 16)
-      hipLaunchKernelGGL((small_eigh_kernel<64, 16>), dim3(1), dim3(64), 0, st_, n, A, lda, w, info_.p);
+      hipLaunchKernelGGL((small_eigh_kernel<64, 16>), dim3(1), dim3(64), 0, st_, n, A, lda, w, info_.p,
+                         status);
     else
-      hipLaunchKernelGGL((small_eigh_kernel<256, kJacobiMax>), dim3(1), dim3(256), 0, st_, n, A, lda, w, info_.p);
+      hipLaunchKernelGGL((small_eigh_kernel<256, kJacobiMax>), dim3(1), dim3(256), 0, st_, n, A, lda, w, info_.p,
+                         status);
     SEQX_LAUNCH_CHECK();
     return;
   }
   work_.ensure(static_cast<size_t>(n));
   SEQX_RB(rocsolver_dsyevd(h_, rocblas_evect_original, rocblas_fill_lower, n, A, lda, w, work_.p, info_.p));
+  if (status) {
+    hipLaunchKernelGGL(word_kernel, dim3(1), dim3(1), 0, st_, info_.p, status);
+    SEQX_LAUNCH_CHECK();
+  }
 }
 
-void DenseSolver::eigh_lowest(int n, double* A, int lda, int k, double* w) {
+void DenseSolver::eigh_lowest(int n, double* A, int lda, int k, double* w, double* status, bool library) {
   if (n <= 0 || k <= 0) return;
   k = std::min(k, n);
-  if (n < kEigMin || n > kEigMax) {
-    eigh(n, A, lda, w);
+  if (library || n < kEigMin || n > kEigMax) {
+    eigh(n, A, lda, w, status);
     return;
   }
   small_.ensure(eig_lowest_scratch(n, k));
-  launch_eig_lowest(st_, n, A, lda, k, w, small_.p, info_.p);
+  launch_eig_lowest(st_, n, A, lda, k, w, small_.p, info_.p, status, poll_limit_);
 }
 
 void DenseSolver::potrf(int n, double* A, int lda) {

@@ -22,8 +22,15 @@ constexpr int kEigOneGroup = 128;
 
 // k lowest eigenpairs, 2 <= n <= kEigMax (eig_lowest.hip): A's columns 0..k-1
 // and w; reads the lower triangle.  scratch holds eig_lowest_scratch(n, k) doubles.
+// Above kEigOneGroup rows wavefronts of different compute units wait for each
+// other's values, at most poll_limit rounds of polling; if that is not enough
+// (other work holds the GPU), A is left as it was and info and status (optional,
+// the same word as a double) are kEigGaveUp, else 0.
+constexpr int kEigGaveUp = -1;
+constexpr int kEigPollLimit = 1 << 20;  // about a second
 size_t eig_lowest_scratch(int n, int k);
-void launch_eig_lowest(hipStream_t st, int n, double* A, int lda, int k, double* w, double* scratch, int* info);
+void launch_eig_lowest(hipStream_t st, int n, double* A, int lda, int k, double* w, double* scratch, int* info,
+                       double* status, int poll_limit);
 // The lowest eigenpairs of many small problems (eig_lowest.hip), one workgroup
 // each for the reduction and one for every pair: problem m (of order n[m] <= ld
 // <= 64, where active[m]) reads the lower triangle of A + m ld^2 and writes its
@@ -51,12 +58,15 @@ class DenseSolver {
   ~DenseSolver();
   DenseSolver(const DenseSolver&) = delete;
   DenseSolver& operator=(const DenseSolver&) = delete;
-  // eigenvalues ascending into w[n]; eigenvectors overwrite A (columns)
-  void eigh(int n, double* A, int lda, double* w);
+  // eigenvalues ascending into w[n]; eigenvectors overwrite A (columns); status
+  // (device, optional): the info word as a double
+  void eigh(int n, double* A, int lda, double* w, double* status = nullptr);
   // the k lowest eigenpairs only: w[0..k), eigenvectors in columns 0..k-1 of A
   // (the rest of A is overwritten).  kEigMin <= n <= kEigMax runs on the
   // kernels of eig_lowest.hip; other n use eigh.  Reads the lower triangle.
-  void eigh_lowest(int n, double* A, int lda, int k, double* w);
+  // The info word (also at status) must be checked: on kEigGaveUp A is as before the call, and the caller repeats it
+  // with library = true (eigh, whose kernels do not wait for each other).
+  void eigh_lowest(int n, double* A, int lda, int k, double* w, double* status = nullptr, bool library = false);
   // lower Cholesky factor in place (upper triangle untouched); info reports
   // the first non-positive pivot.  n <= kSmallDense runs as one workgroup.
   void potrf(int n, double* A, int lda);
@@ -74,6 +84,9 @@ class DenseSolver {
   hipStream_t st_;
   DBuf<double> work_, small_;
   DBuf<int> info_;
+  // rounds of polling of eigh_lowest; SEQX_EIG_POLL_LIMIT at construction, for
+  // tests of a reduction that gives up
+  int poll_limit_ = kEigPollLimit;
 };
 
 // elementwise / reduction helpers (all ordered on `st`)
