@@ -65,7 +65,9 @@ __device__ __forceinline__ double rcp_nr(double x) {
 
 // ---------------------------------------------------------------- 1. tridiagonal form
 
-// A value not yet published in the exchange area: a NaN that no arithmetic makes.
+// A value not yet published in the exchange area: a NaN that no arithmetic makes
+// of numbers.  (One that came with the input keeps its bits through arithmetic:
+// it is published as another NaN.)
 constexpr unsigned long long kEmpty = ~0ull;
 __global__ void __launch_bounds__(256) exchange_fill_kernel(long n, unsigned long long* __restrict__ x, int* failed) {
   const long i = blockIdx.x * 256L + threadIdx.x;
@@ -74,8 +76,9 @@ __global__ void __launch_bounds__(256) exchange_fill_kernel(long n, unsigned lon
 }
 
 __device__ __forceinline__ void publish(double* p, double v) {
-  __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), static_cast<unsigned long long>(__double_as_longlong(v)),
-                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const unsigned long long b = static_cast<unsigned long long>(__double_as_longlong(v));
+  __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), b == kEmpty ? kEmpty >> 1 : b, __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ unsigned long long peek(const double* p) {
   return __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

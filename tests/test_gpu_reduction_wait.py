@@ -37,3 +37,31 @@ def test_solve_without_the_reduction(monkeypatch, theory, k):
     assert np.abs(got.omega_eV - ref.omega * model.HARTREE_EV).max() <= 1e-4
     job.free()
     ctx.close()
+
+
+@pytest.mark.parametrize("bits", [0x7FF8000000000000, 0xFFF8000000000000, 0xFFFFFFFFFFFFFFFF])
+def test_guess_with_a_nan(bits):
+    """A guess of more than 128 vectors with a NaN of any kind is refused, and at once: the reduction does not take the
+    NaN for a value still to come (a wait of seconds)."""
+    import time
+
+    mol = molecules.add_noise(molecules.polyene(20), 0.02, np.random.default_rng(20))
+    print(f"[gpu] guess with a NaN {bits:x}", flush=True)
+    ctx = seqx.Context(0)
+    ctx.set_params(*seqx.params_table(PR))
+    job = ctx.prepare([mol.natoms], mol.Z, mol.xyz)
+    n, o, v = job.dims()
+    guess = np.random.default_rng(1).normal(size=(140, o, v))
+    t0 = time.perf_counter()
+    job.solve(theory=seqx.CIS, nroots=4, tol=1e-3, max_iter=300, guess=seqx.GUESS_USER, user_guess=guess,
+              max_subspace=300)
+    usual = time.perf_counter() - t0
+    guess[5] = np.full((o, v), bits, dtype=np.uint64).view(np.float64)
+    t0 = time.perf_counter()
+    with pytest.raises(seqx.SeqxError) as ei:
+        job.solve(theory=seqx.CIS, nroots=4, tol=1e-3, max_iter=300, guess=seqx.GUESS_USER, user_guess=guess,
+                  max_subspace=300)
+    assert ei.value.status == 1  # E_ARG: no direction left
+    assert time.perf_counter() - t0 < usual + 0.3
+    job.free()
+    ctx.close()
