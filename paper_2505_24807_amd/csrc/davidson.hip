@@ -557,7 +557,6 @@ DavResult davidson(DeviceMolecule& m, const DavOptions& opt, DenseSolver& ds, Da
   w.Lm.ensure(static_cast<size_t>(Smax) * Smax);
   w.Tmp.ensure(static_cast<size_t>(Smax) * Smax);
   w.Hs.ensure(static_cast<size_t>(Smax) * Smax);
-  w.w2.ensure(Smax + 1);  // eigenvalues and an info word
   // Restarts keep, beside the current Ritz coefficients, those of the
   // previous iteration (padded with zeros for the rows added since): the
   // basis after a collapse spans both, as in a locally optimal block
@@ -567,6 +566,10 @@ DavResult davidson(DeviceMolecule& m, const DavOptions& opt, DenseSolver& ds, Da
   const int q_prev = opt.keep_prev ? (tdhf ? 2 * K : K) : 0;
   const bool use_prev = q_prev > 0 && q_ritz + q_prev + ncand_max <= Smax;
   const int q_max = q_ritz + (use_prev ? q_prev : 0);
+  // Gram matrices: of the basis, the corrections, the vectors of a collapse (in
+  // TDHF 2K of either, also where the whole space has fewer pairs) or a guess
+  const int ngram = std::max(Smax, std::max(ncand_max, q_max));
+  w.w2.ensure(ngram + 1);  // eigenvalues and an info word
   w.coef.ensure(static_cast<size_t>(Smax) * 4 * K);
   // Ritz rows: Tv holds [T; U] (U only for TDHF), PT holds [(A+B)T; (A-B)U] (CIS: A X)
   w.Tv.ensure(static_cast<size_t>(ps) * K * nov);
@@ -581,7 +584,7 @@ DavResult davidson(DeviceMolecule& m, const DavOptions& opt, DenseSolver& ds, Da
   float* MU32 = PT32 + static_cast<long>(K) * nov;
   w.W.ensure(static_cast<size_t>(std::max(ncand_max, opt.guess ? opt.nguess : 0)) * nov);
   w.scratch.ensure(static_cast<size_t>(ps) * q_max * nov);
-  w.G.ensure(static_cast<size_t>(ps) * Smax * Smax);
+  w.G.ensure(std::max(static_cast<size_t>(ps) * Smax * Smax, static_cast<size_t>(ngram) * ngram));
   w.Q.ensure(static_cast<size_t>(std::max(std::max(ncand_max, q_max), opt.guess ? opt.nguess : 0)) * Smax);
   // FP32 basis rows and products while the products are formed in low
   // precision (their own rounding is far coarser); FP64 after the switch
@@ -591,7 +594,7 @@ DavResult davidson(DeviceMolecule& m, const DavOptions& opt, DenseSolver& ds, Da
     w.SP32.ensure(static_cast<size_t>(ps) * Smax * nov);
     w.scr32.ensure(static_cast<size_t>(ps) * q_max * nov);
   }
-  w.ws.ensure(std::max<size_t>(dots_workspace(2 * Smax, std::max(Smax, opt.nlock), nov), 4096));
+  w.ws.ensure(std::max<size_t>(dots_workspace(2 * ngram, std::max(ngram, opt.nlock), nov), 4096));
   w.d.ensure(nov);
   w.rn.ensure(2 * K + 3);  // residual norms, omega, then the check words (lowest eigenvalue, eigh / potrf info)
   const int nbres = static_cast<int>(std::min<long>(256, ceil_div(nov, 256)));

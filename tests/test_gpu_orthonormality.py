@@ -77,3 +77,26 @@ def test_guess_of_nearly_dependent_vectors(ctx):
     # the span itself is known to 2^-52 / 1e-5 of a vector
     assert np.abs(first - np.linalg.eigvalsh((M + M.T) / 2)[:4] * seqx.HARTREE_EV).max() <= 1e-8
     job.free()
+
+
+@pytest.mark.parametrize("theory, k", [(seqx.TDHF, 8), (seqx.TDHF, 5), (seqx.CIS, 8)])
+def test_whole_space(ctx, theory, k):
+    """Water has 8 pairs: more corrections (2 k) than the space has dimensions.  No tolerance of 1e-300 is reached and
+    no direction is left (E_DAV_NOCONV); the next solve finds all roots."""
+    mol = molecules.water_cluster(1, 1)
+    print(f"[gpu] whole space theory={theory} k={k}", flush=True)
+    job = ctx.prepare([mol.natoms], mol.Z, mol.xyz)
+    n, o, v = job.dims()
+    assert o * v == 8
+    with pytest.raises(seqx.SeqxError) as ei:
+        job.solve(theory=theory, nroots=k, tol=1e-300, max_iter=5)
+    assert ei.value.status == 8
+    job.solve(theory=theory, nroots=k, tol=1e-8)
+    P, M = job.sigma(np.eye(8).reshape(8, o, v), theory=theory)
+    if theory == seqx.CIS:
+        ref = np.linalg.eigvalsh(P.reshape(8, 8))
+    else:
+        L = np.linalg.cholesky(M.reshape(8, 8))
+        ref = np.sqrt(np.linalg.eigvalsh(L.T @ P.reshape(8, 8) @ L))
+    assert np.abs(job.results().omega_eV - ref[:k] * seqx.HARTREE_EV).max() <= 1e-10
+    job.free()
