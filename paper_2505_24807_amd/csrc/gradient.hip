@@ -172,12 +172,31 @@ GradientResult param_gradient(DeviceMolecule& m, int theory, const Elem* elems_h
   // Tables at theta + h and theta - h of as many parameters at a time as keep
   // them below about 2 GB: the builders take a thread per atom pair, a few
   // hundred of a small molecule, so one parameter's tables leave the GPU
-  // nearly empty.  One launch over all of them: C20H22 15.2 -> 4.5 ms.
+  // nearly empty.  One launch over all of them: C20H22 15.2 -> 4.5 ms.  They are
+  // allocated after everything else and for fewer parameters where memory is
+  // short, down to the one that is always needed.
   const long per_param = 2 * (npp + nn);
   const int pg_max = static_cast<int>(std::max<long>(1, std::min<long>(params.size(), (2L << 30) / 8 / per_param)));
-  std::vector<Elem> tab(static_cast<size_t>(2) * kNumSlots * pg_max);
-  DBuf<Elem> dtab(tab.size());
-  DBuf<double> Wp(static_cast<size_t>(2) * npp * pg_max), Hp(static_cast<size_t>(2) * nn * pg_max);
+  int pg_tab = 0;  // parameters the tables hold
+  DBuf<Elem> dtab;
+  DBuf<double> Wp, Hp, contr, wst;
+  auto alloc_tables = [&](int kg) {
+    for (int pg = pg_max; pg_tab == 0; pg /= 2) {
+      try {
+        dtab.ensure(static_cast<size_t>(2) * kNumSlots * pg);
+        Hp.ensure(static_cast<size_t>(2) * nn * pg);
+        contr.ensure(static_cast<size_t>(2) * kg * pg);
+        wst.ensure(dots_workspace(kg, pg, std::max(npp, nn)));
+        Wp.ensure(static_cast<size_t>(2) * npp * pg);
+        pg_tab = pg;
+      } catch (const Error& e) {
+        if (e.status != kENoMem || pg == 1) throw;
+        (void)hipGetLastError();  // a failed hipMalloc would be reported by the next launch check
+        for (DBuf<double>* b : {&Wp, &Hp, &contr, &wst}) b->release();
+        dtab.release();
+      }
+    }
+  };
   for (int k0 = 0; k0 < K; k0 += kg_max) {
     const int kg = std::min(kg_max, K - k0);
     DBuf<double> T(kg * nov), U(kg * nov), L(kg * nov), Z(kg * nov), R(kg * nov), Pz(kg * nov), Q(kg * nov),
@@ -186,7 +205,7 @@ GradientResult param_gradient(DeviceMolecule& m, int theory, const Elem* elems_h
     DBuf<double> Mvv(static_cast<size_t>(kg) * v * v), Moo(static_cast<size_t>(kg) * o * o), Tnv(kg * nv),
         Tno(kg * no);
     DBuf<double> kk(static_cast<size_t>(kg) * kg), coef(2 * kg), ws;
-    ws.alloc(std::max<size_t>(std::max(dots_workspace(kg, kg, nov), dots_workspace(kg, pg_max, std::max(npp, nn))), 1024));
+    ws.alloc(std::max<size_t>(dots_workspace(kg, kg, nov), 1024));
     const double* X = m.X.p + k0 * nov;
     const double* Y = m.Y.p + k0 * nov;
     const dim3 rows(ceil_div(nov, 256), kg);
@@ -274,8 +293,10 @@ GradientResult param_gradient(DeviceMolecule& m, int theory, const Elem* elems_h
                        m.pi_nu.p, Dm.p, m.P.p, Ts, Ua, Gam.p);
     SEQX_LAUNCH_CHECK();
     // derivative tables by central differences of the integral builder, contracted with Gamma and D
-    for (size_t p0 = 0; p0 < params.size(); p0 += pg_max) {
-      const int pg = static_cast<int>(std::min<size_t>(pg_max, params.size() - p0));
+    alloc_tables(kg);  // the first group is the largest
+    std::vector<Elem> tab(static_cast<size_t>(2) * kNumSlots * pg_tab);
+    for (size_t p0 = 0; p0 < params.size(); p0 += pg_tab) {
+      const int pg = static_cast<int>(std::min<size_t>(pg_tab, params.size() - p0));
       for (int q = 0; q < pg; ++q) {
         const Param& pr = params[p0 + q];
         for (int sg = 0; sg < 2; ++sg) {
@@ -292,10 +313,9 @@ GradientResult param_gradient(DeviceMolecule& m, int theory, const Elem* elems_h
       hipLaunchKernelGGL(pair_difference_kernel, dim3(ceil_div(npp, 256), pg), dim3(256), 0, st, npp, Wp.p);
       hipLaunchKernelGGL(pair_difference_kernel, dim3(ceil_div(nn, 256), pg), dim3(256), 0, st, nn, Hp.p);
       SEQX_LAUNCH_CHECK();
-      DBuf<double> contr(static_cast<size_t>(2) * kg * pg);
-      dots(st, kg, Gam.p, npp, pg, Wp.p, 2 * npp, npp, contr.p, pg, ws.p);
-      dots(st, kg, Dm.p, nn, pg, Hp.p, 2 * nn, nn, contr.p + static_cast<size_t>(kg) * pg, pg, ws.p);
-      std::vector<double> hc2(contr.n);
+      dots(st, kg, Gam.p, npp, pg, Wp.p, 2 * npp, npp, contr.p, pg, wst.p);
+      dots(st, kg, Dm.p, nn, pg, Hp.p, 2 * nn, nn, contr.p + static_cast<size_t>(kg) * pg, pg, wst.p);
+      std::vector<double> hc2(static_cast<size_t>(2) * kg * pg);
       SEQX_HIP(hipMemcpyAsync(hc2.data(), contr.p, hc2.size() * sizeof(double), hipMemcpyDeviceToHost, st));
       SEQX_HIP(hipStreamSynchronize(st));  // also keeps `tab` as it is until its copy is done
       for (int j = 0; j < kg; ++j)

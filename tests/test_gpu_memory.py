@@ -90,3 +90,23 @@ def test_products_in_the_memory_of_fp32_matrices(pooled, theory, k):
             assert np.abs(a - b).max() <= 8 * n * 2.0 ** -24 * np.abs(b).max()
             assert not np.array_equal(a, b)
     job.free()
+
+
+def test_derivatives_in_the_memory_of_one_parameter(pooled):
+    """The derivatives need the tables of one parameter at a time, and take more where there is room: with room for one
+    only, the same values (sums in the same order, differences of tables: 1e-12 of the largest)."""
+    ctx, pool = pooled
+    mol = molecules.add_noise(molecules.polyene(20), 0.02, np.random.default_rng(20))
+    print(f"[gpu] derivatives in little memory {mol.name}", flush=True)
+    job = ctx.prepare([mol.natoms], mol.Z, mol.xyz)
+    n, o, v = job.dims()
+    job.solve(theory=seqx.CIS, nroots=2, tol=1e-6, max_iter=300)
+    pool.peak = pool.now
+    full, _ = job.param_gradient()
+    npair, nparam = 10 * 20 + 22, 11 + 4  # carbon's and hydrogen's parameters
+    tables = 8 * 2 * (npair * npair + n * n)
+    assert pool.peak - pool.now > nparam * tables
+    pool.limit = pool.peak - (nparam - 1) * tables
+    little, _ = job.param_gradient()
+    assert np.abs(little - full).max() <= 1e-12 * np.abs(full).max()
+    job.free()
