@@ -272,30 +272,36 @@ size_t carve_chunk(const DeviceMolecule& m, int theory, int kc, int precision, b
   return off;
 }
 
-// Algorithmic work of one chunk (flops, bytes, launches per phase); d = bytes
-// per stored element of the transforms.
-void chunk_work(const DeviceMolecule& m, int theory, int kc, int precision, bool merged,
+// Algorithmic work of one chunk (flops, bytes, launches per phase).  planes: the
+// operands C, V, T1, F and Z are rows of that many bfloat16 planes (0: matrices);
+// io32: FP32 vectors in and out.
+void chunk_work(const DeviceMolecule& m, int theory, int kc, int precision, int planes, bool io32, bool merged,
                 std::array<double, kNumPhases>& fl, std::array<double, kNumPhases>& by,
                 std::array<long, kNumPhases>& la) {
   const int n = m.nao, o = m.nocc, v = m.nvirt;
-  const long nn = static_cast<long>(n) * n, nv = static_cast<long>(n) * v, ov = static_cast<long>(o) * v;
-  const bool tdhf = theory == 1, f32 = precision != kPrecFP64;
-  const int nb = tdhf ? 2 * kc : kc;
-  const double d = f32 ? 4.0 : 8.0;
+  const double nn = static_cast<double>(n) * n, ov = static_cast<double>(o) * v;
+  const bool tdhf = theory == 1, low = precision != kPrecFP64;
+  const double k = kc, nb = tdhf ? 2.0 * kc : kc;
+  const double d = low ? 4.0 : 8.0;  // bytes of an element of a matrix, and of R in any form
+  // bytes of an operand of `rows` rows of `len` elements
+  auto operand = [&](double rows, int len) { return rows * (planes ? 2.0 * plane_row(len, planes) : d * len); };
+  const double T1 = k * operand(n, v), F = nb * operand(n, n), Z = nb * operand(v, n);
+  // orbital coefficients always have three planes
+  auto orbitals = [&](double rows, int len) { return rows * (planes ? 2.0 * plane_row(len, 3) : d * len); };
   fl = {};
   by = {};
   la = {};
-  fl[kPhaseFwd1] = 2.0 * n * o * v * kc;
-  by[kPhaseFwd1] = d * (static_cast<double>(n) * o + (ov + nv) * static_cast<double>(kc));
-  fl[kPhaseFwd2] = 2.0 * n * static_cast<double>(n) * v * kc;
-  by[kPhaseFwd2] = d * (static_cast<double>(n) * v + (nv + nn) * static_cast<double>(kc));
+  fl[kPhaseFwd1] = 2.0 * n * ov * k;
+  by[kPhaseFwd1] = orbitals(n, o) + k * operand(v, o) + T1;
+  fl[kPhaseFwd2] = 2.0 * nn * v * k;
+  by[kPhaseFwd2] = orbitals(n, v) + T1 + d * k * nn;
   // contraction: read R, write every F, read the packed ERIs (FP64) once
-  by[kPhaseG] = d * (static_cast<double>(kc) * nn + static_cast<double>(nb) * nn) + 8.0 * static_cast<double>(m.np) * m.np;
-  fl[kPhaseBwd1] = 2.0 * n * static_cast<double>(n) * v * nb;
-  by[kPhaseBwd1] = d * (static_cast<double>(n) * v + (nn + nv) * static_cast<double>(nb));
-  fl[kPhaseBwd2] = 2.0 * o * static_cast<double>(n) * v * nb;
-  by[kPhaseBwd2] = d * (static_cast<double>(n) * o + nv * static_cast<double>(nb)) + 8.0 * 2.0 * ov * nb;
-  la[kPhaseFwd1] = f32 ? 2 : 1;
+  by[kPhaseG] = d * k * nn + F + 8.0 * static_cast<double>(m.np) * m.np;
+  fl[kPhaseBwd1] = 2.0 * nn * v * nb;
+  by[kPhaseBwd1] = orbitals(v, n) + F + Z;
+  fl[kPhaseBwd2] = 2.0 * n * ov * nb;
+  by[kPhaseBwd2] = orbitals(o, n) + Z + (io32 ? 4.0 : 8.0) * 2.0 * ov * nb;
+  la[kPhaseFwd1] = planes || (low && !io32) ? 2 : 1;  // the vectors are split or rounded first
   la[kPhaseFwd2] = 1;
   la[kPhaseG] = 1;
   la[kPhaseBwd1] = 1;
@@ -353,7 +359,7 @@ void sigma_build_any(const DeviceMolecule& m, int theory, int k, const double* V
     }
     std::array<double, kNumPhases> fl, by;
     std::array<long, kNumPhases> la;
-    chunk_work(m, theory, kc, precision, merged, fl, by, la);
+    chunk_work(m, theory, kc, precision, planes ? plane_count(m, precision) : 0, f32io, merged, fl, by, la);
     w.timer.pending.push_back(ev);
     w.timer.pending_flops.push_back(fl);
     w.timer.pending_bytes.push_back(by);
