@@ -52,8 +52,7 @@ __device__ __forceinline__ void store_elem(To* __restrict__ C, long ldc, long b,
   if (beta != 0.0) v += beta * static_cast<double>(*cp);
   if (EPI) {
     const long vo = ((b / ep.vdiv) % ep.kv) * ep.strideV + static_cast<long>(row) * ldc + col;
-    const double vv = ep.Vf ? static_cast<double>(ep.Vf[vo]) : ep.V[vo];
-    v += (ep.eps[ep.nocc + col] - ep.eps[row]) * vv;
+    v += (ep.eps[ep.nocc + col] - ep.eps[row]) * ep.V[vo];
   }
   *cp = static_cast<To>(v);
 }
@@ -536,14 +535,20 @@ void gemm_any(hipStream_t st, bool ta, bool tb, int M, int N, int K, double alph
   const long ldmax = lda > ldb ? lda : ldb;
   const bool small_offsets = (ldmax * (static_cast<long>(K > 128 ? K : 128) + 128) + K) * static_cast<long>(sizeof(T)) <
                              (1L << 31);
-  if (small_offsets && M >= 32 && N >= 32 && K >= 32) {
-    if (epi)
-      launch_tiles<T, To, true>(st, ta, tb, M, N, K, alpha, A, lda, sA, B, ldb, sB, beta, C, ldc, sC, batch, ep);
-    else
-      launch_tiles<T, To, false>(st, ta, tb, M, N, K, alpha, A, lda, sA, B, ldb, sB, beta, C, ldc, sC, batch, ep);
-  } else if (epi) {
-    launch_cfg<T, To, 2, 2, 2, 2, true>(st, ta, tb, M, N, K, alpha, A, lda, sA, B, ldb, sB, beta, C, ldc, sC, batch,
-                                        ep);
+  const bool tiles = small_offsets && M >= 32 && N >= 32 && K >= 32;
+  if constexpr (sizeof(To) == 8) {  // the epilogue's products are FP64
+    if (epi) {
+      if (tiles)
+        launch_tiles<T, To, true>(st, ta, tb, M, N, K, alpha, A, lda, sA, B, ldb, sB, beta, C, ldc, sC, batch, ep);
+      else
+        launch_cfg<T, To, 2, 2, 2, 2, true>(st, ta, tb, M, N, K, alpha, A, lda, sA, B, ldb, sB, beta, C, ldc, sC,
+                                            batch, ep);
+      SEQX_LAUNCH_CHECK();
+      return;
+    }
+  }
+  if (tiles) {
+    launch_tiles<T, To, false>(st, ta, tb, M, N, K, alpha, A, lda, sA, B, ldb, sB, beta, C, ldc, sC, batch, ep);
   } else if (!skinny && M <= 32) {
     launch_cfg<T, To, 1, 4, 2, 1, false>(st, ta, tb, M, N, K, alpha, A, lda, sA, B, ldb, sB, beta, C, ldc, sC, batch,
                                          ep);
@@ -566,9 +571,8 @@ void dgemm(hipStream_t st, bool ta, bool tb, int M, int N, int K, double alpha, 
 }
 
 void sgemm(hipStream_t st, bool ta, bool tb, int M, int N, int K, double alpha, const float* A, long lda, long sA,
-           const float* B, long ldb, long sB, double beta, float* C, long ldc, long sC, int batch,
-           const SigmaEpilogue* epi) {
-  gemm_any<float, float>(st, ta, tb, M, N, K, alpha, A, lda, sA, B, ldb, sB, beta, C, ldc, sC, batch, epi);
+           const float* B, long ldb, long sB, double beta, float* C, long ldc, long sC, int batch) {
+  gemm_any<float, float>(st, ta, tb, M, N, K, alpha, A, lda, sA, B, ldb, sB, beta, C, ldc, sC, batch, nullptr);
 }
 
 void sgemm_out64(hipStream_t st, bool ta, bool tb, int M, int N, int K, double alpha, const float* A, long lda,

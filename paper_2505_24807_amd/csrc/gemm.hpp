@@ -10,7 +10,7 @@ struct SigmaEpilogue {
   const double* eps = nullptr;
   int nocc = 0;
   const double* V = nullptr;
-  const float* Vf = nullptr;  // FP32 trial vectors instead of V (read when set)
+  const float* Vf = nullptr;  // FP32 trial vectors instead of V (plane products only)
   long strideV = 0;
   int kv = 1;
   int vdiv = 1;  // batch b adds the diagonal term of V[(b / vdiv) % kv]
@@ -29,8 +29,7 @@ void dgemm(hipStream_t st, bool ta, bool tb, int M, int N, int K, double alpha, 
 // FP32 inputs on the FP32 matrix cores, FP32 accumulation; alpha, beta and the
 // epilogue are applied in FP64.  sgemm writes FP32, sgemm_out64 writes FP64.
 void sgemm(hipStream_t st, bool ta, bool tb, int M, int N, int K, double alpha, const float* A, long lda, long sA,
-           const float* B, long ldb, long sB, double beta, float* C, long ldc, long sC, int batch = 1,
-           const SigmaEpilogue* epi = nullptr);
+           const float* B, long ldb, long sB, double beta, float* C, long ldc, long sC, int batch = 1);
 void sgemm_out64(hipStream_t st, bool ta, bool tb, int M, int N, int K, double alpha, const float* A, long lda,
                  long sA, const float* B, long ldb, long sB, double beta, double* C, long ldc, long sC, int batch = 1,
                  const SigmaEpilogue* epi = nullptr);

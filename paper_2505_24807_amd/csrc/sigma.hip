@@ -71,8 +71,8 @@ struct ChunkBufs {
   double *gr = nullptr, *gJ = nullptr, *gws = nullptr;
 };
 
-// FP32 trial vectors in and FP32 products out (low-precision modes only), in
-// place of the FP64 ones
+// FP32 trial vectors in and FP32 products out (plane transforms only), in place
+// of the FP64 ones
 struct F32Io {
   const float* V = nullptr;
   float* out1 = nullptr;
@@ -185,33 +185,19 @@ void sigma_chunk(const DeviceMolecule& m, int theory, int kc, const double* Vc, 
   } else {
     // FP32 storage, products on the FP32 matrix cores
     const float* C32 = m.C32.p;
-    const float* Vs = b.V32;
-    if (io) {
-      Vs = io->V;
-      ep.V = nullptr;
-      ep.Vf = io->V;
-    } else {
-      to_float(st, kc * ov, Vc, b.V32);
-    }
-    sgemm(st, false, false, n, v, o, 1.0, C32, n, 0, Vs, v, ov, 0.0, b.T1s, v, nv, kc, nullptr);
+    to_float(st, kc * ov, Vc, b.V32);
+    sgemm(st, false, false, n, v, o, 1.0, C32, n, 0, b.V32, v, ov, 0.0, b.T1s, v, nv, kc);
     mark(1);
-    sgemm(st, false, true, kc * n, n, v, 1.0, b.T1s, v, 0, C32 + o, n, 0, 0.0, b.Rs, n, 0, 1, nullptr);
+    sgemm(st, false, true, kc * n, n, v, 1.0, b.T1s, v, 0, C32 + o, n, 0, 0.0, b.Rs, n, 0, 1);
     mark(2);
     if (tdhf)
       build_G(m, kc, b.Rs, nn, b.Fs, b.Fs + f2off, sF, kTwo, 4.0, -2.0, -2.0, b.gr, b.gJ, b.gws, st);
     else
       build_G(m, kc, b.Rs, nn, b.Fs, static_cast<float*>(nullptr), nn, kSum, 2.0, -1.0, -1.0, b.gr, b.gJ, b.gws, st);
     mark(3);
-    sgemm(st, false, false, nb * n, v, n, 1.0, b.Fs, n, 0, C32 + o, n, 0, 0.0, b.Zs, v, 0, 1, nullptr);
+    sgemm(st, false, false, nb * n, v, n, 1.0, b.Fs, n, 0, C32 + o, n, 0, 0.0, b.Zs, v, 0, 1);
     mark(4);
-    if (io) {
-      if (merged) {
-        sgemm(st, true, false, o, v, n, 1.0, C32, n, 0, b.Zs, v, nv, 0.0, io->out1, v, os / 2, nb, &ep);
-      } else {
-        sgemm(st, true, false, o, v, n, 1.0, C32, n, 0, b.Zs, v, nv, 0.0, io->out1, v, os, kc, &ep);
-        if (tdhf) sgemm(st, true, false, o, v, n, 1.0, C32, n, 0, b.Zs + kc * nv, v, nv, 0.0, io->out2, v, os, kc, &ep);
-      }
-    } else if (merged) {
+    if (merged) {
       sgemm_out64(st, true, false, o, v, n, 1.0, C32, n, 0, b.Zs, v, nv, 0.0, out1c, v, os / 2, nb, &ep);
     } else {
       sgemm_out64(st, true, false, o, v, n, 1.0, C32, n, 0, b.Zs, v, nv, 0.0, out1c, v, os, kc, &ep);
@@ -301,7 +287,7 @@ void chunk_work(const DeviceMolecule& m, int theory, int kc, int precision, int 
   by[kPhaseBwd1] = orbitals(v, n) + F + Z;
   fl[kPhaseBwd2] = 2.0 * n * ov * nb;
   by[kPhaseBwd2] = orbitals(o, n) + Z + (io32 ? 4.0 : 8.0) * 2.0 * ov * nb;
-  la[kPhaseFwd1] = planes || (low && !io32) ? 2 : 1;  // the vectors are split or rounded first
+  la[kPhaseFwd1] = low ? 2 : 1;  // the vectors are split or rounded first
   la[kPhaseFwd2] = 1;
   la[kPhaseG] = 1;
   la[kPhaseBwd1] = 1;
@@ -321,19 +307,20 @@ void sigma_build_any(const DeviceMolecule& m, int theory, int k, const double* V
   const bool tdhf = theory == 1;
   const bool f32io = Vf != nullptr;
   check_sigma_args(m, precision);
-  if (f32io && precision == kPrecFP64) throw Error(kEArg, "FP32 vectors need a low-precision transform mode");
   bool planes = has_planes(m, precision);
+  if (f32io && !planes) throw Error(kEArg, "FP32 vectors need plane transforms");
   for (int c0 = 0, kc = 0; c0 < k; c0 += kc) {
     kc = std::min(chunk, k - c0);
     // Where memory is short, fewer vectors at a time, down to one, and then the
     // FP32 matrices (two thirds of the planes): what 32 vectors as FP32 matrices
-    // need is always enough.
+    // need is always enough.  (Solves over FP32 vectors stop at one: their FP64
+    // phase needs more than that vector's planes.)
     for (;;) {
       try {
         w.buf.ensure(carve_chunk(m, theory, kc, precision, planes, nullptr, nullptr));
         break;
       } catch (const Error& e) {
-        if (e.status != kENoMem || (kc == 1 && !planes)) throw;
+        if (e.status != kENoMem || (kc == 1 && (!planes || f32io))) throw;
         (void)hipGetLastError();  // a failed hipMalloc would be reported by the next launch check
         if (kc > 1) chunk = kc = (kc + 1) / 2;
         else planes = false;

@@ -3,6 +3,7 @@
 // of the vector length, partial sums reduced in a fixed order) and
 // combinations of a basis into a few vectors.
 #include <algorithm>
+#include <type_traits>
 
 #include "gemm.hpp"
 
@@ -372,15 +373,14 @@ void dots_pass(hipStream_t st, int ns, const TX* X, long ldx, int nt, const TY* 
   const long chunk = ROWS == kRowsOne ? len : skinny_chunk(nt, len);
   const int nchunks = static_cast<int>((len + chunk - 1) / chunk);
   const dim3 grid(ceil_div(nt, ROWS == kRowsOne ? 64 : 128), nchunks);
-  if (ns <= 16)
-    hipLaunchKernelGGL((skinny_dots_kernel<1, TX, TY, ROWS>), grid, dim3(256), 0, st, ns, nt, X, ldx, Y, ldy, len,
-                       chunk, ws);
-  else if (ns <= 32)
-    hipLaunchKernelGGL((skinny_dots_kernel<2, TX, TY, ROWS>), grid, dim3(256), 0, st, ns, nt, X, ldx, Y, ldy, len,
-                       chunk, ws);
-  else
-    hipLaunchKernelGGL((skinny_dots_kernel<3, TX, TY, ROWS>), grid, dim3(256), 0, st, ns, nt, X, ldx, Y, ldy, len,
-                       chunk, ws);
+  const auto launch = [&](auto nx) {
+    hipLaunchKernelGGL((skinny_dots_kernel<decltype(nx)::value, TX, TY, ROWS>), grid, dim3(256), 0, st, ns, nt, X, ldx,
+                       Y, ldy, len, chunk, ws);
+  };
+  if constexpr (ROWS == kRowsOne) launch(std::integral_constant<int, 1>{});
+  else if (ns <= 16) launch(std::integral_constant<int, 1>{});
+  else if (ns <= 32) launch(std::integral_constant<int, 2>{});
+  else launch(std::integral_constant<int, 3>{});
   if (ns * nt < 1024 && nchunks >= 64)
     hipLaunchKernelGGL(reduce_partials_wide_kernel, dim3(ns * nt), dim3(256), 0, st, nchunks, ns, nt, ws, out, ldo);
   else
