@@ -12,6 +12,7 @@
 // and two traces per purification step.
 #include <algorithm>
 
+#include "diis.hpp"
 #include "gemm.hpp"
 #include "planes.hpp"
 #include "scf.hpp"
@@ -283,7 +284,7 @@ void sp2_density(hipStream_t st, int n, int nocc, const double* F, double* P, Sc
 void run_scf(DeviceMolecule& m, const ScfOptions& opt, DenseSolver& ds, GWork& gw, ScfWork& w, hipStream_t st) {
   const int n = m.nao, o = m.nocc;
   const long nn = static_cast<long>(n) * n;
-  const int nd = std::max(1, std::min(opt.ndiis, 16));
+  const int nd = std::max(1, std::min(opt.ndiis, kDiisMax));
   w.G.ensure(nn);
   w.F.ensure(nn);
   w.FP.ensure(nn);

@@ -13,6 +13,7 @@
 #include <algorithm>
 #include <cmath>
 
+#include "diis.hpp"
 #include "fock_blocks.hpp"
 #include "scf.hpp"
 #include "wave.hpp"
@@ -44,9 +45,9 @@ struct ScfDesc {
 struct ScfLds {
   double X[kScfSmallMax][kSLd];  // purification; packed densities and Coulomb values in between
   double red[2 * kSW];
-  double B[16][17], a[17][19], c[16];
-  double lo[kSW], hi[kSW], sc;
-  int piv;
+  double B[kDiisMax][kDiisMax + 1], c[kDiisMax];
+  double lo[kSW], hi[kSW];
+  DiisLds diis;
 };
 
 // sums of two values over the workgroup in a fixed order (every thread gets them)
@@ -246,60 +247,6 @@ __device__ void small_product(int n, const double* __restrict__ A, const double*
   __syncthreads();
 }
 
-// Pulay coefficients L.c[0 .. m) of the error overlaps L.B: Gauss-Jordan with
-// partial pivoting on the bordered system, one row per thread
-__device__ void small_diis(int m, ScfLds& L) {
-  const int t = threadIdx.x, n = m + 1;
-  if (t < m) {
-    for (int j = 0; j < m; ++j) L.a[t][j] = L.B[t][j];
-    L.a[t][m] = -1.0;
-    L.a[t][n] = 0.0;
-  } else if (t == m) {
-    for (int j = 0; j < m; ++j) L.a[m][j] = -1.0;
-    L.a[m][m] = 0.0;
-    L.a[m][n] = -1.0;
-  }
-  __syncthreads();
-  if (t == 0) {  // scale the error block for conditioning
-    double sc = 0.0;
-    for (int i = 0; i < m; ++i) sc = fmax(sc, fabs(L.a[i][i]));
-    L.sc = sc;
-  }
-  __syncthreads();
-  if (L.sc > 0 && t < m)
-    for (int j = 0; j < m; ++j) L.a[t][j] /= L.sc;
-  __syncthreads();
-  bool singular = false;
-  for (int col = 0; col < n; ++col) {
-    if (t == 0) {
-      int piv = col;
-      for (int r = col + 1; r < n; ++r)
-        if (fabs(L.a[r][col]) > fabs(L.a[piv][col])) piv = r;
-      L.piv = piv;
-    }
-    __syncthreads();
-    const int piv = L.piv;
-    if (piv != col && t <= n) {  // column t of the two rows
-      const double tmp = L.a[col][t];
-      L.a[col][t] = L.a[piv][t];
-      L.a[piv][t] = tmp;
-    }
-    __syncthreads();
-    const double d = L.a[col][col];
-    if (d == 0.0) {  // the same in every thread
-      singular = true;
-      break;
-    }
-    if (t < n && t != col) {
-      const double f = L.a[t][col] / d;
-      for (int j = col; j <= n; ++j) L.a[t][j] -= f * L.a[col][j];
-    }
-    __syncthreads();
-  }
-  if (t < m) L.c[t] = singular ? (t == m - 1 ? 1.0 : 0.0) : L.a[t][n] / L.a[t][t];
-  __syncthreads();
-}
-
 __global__ void __launch_bounds__(kST) scf_small_kernel(const ScfDesc* __restrict__ mols, double tol, int max_iter,
                                                         int nd) {
   __shared__ ScfLds L;
@@ -372,7 +319,7 @@ __global__ void __launch_bounds__(kST) scf_small_kernel(const ScfDesc* __restric
       }
       __syncthreads();
       if (mh >= 2) {
-        small_diis(mh, L);
+        diis_solve(mh, &L.B[0][0], kDiisMax + 1, L.c, L.diis);
         for (int x = tid; x < nn; x += kST) {
           double v = 0.0;
           for (int s = 0; s < mh; ++s) v += L.c[s] * m.Fh[static_cast<long>(s) * nn + x];
@@ -394,7 +341,7 @@ __global__ void __launch_bounds__(kST) scf_small_kernel(const ScfDesc* __restric
 }  // namespace
 
 void run_scf_small(const std::vector<DeviceMolecule*>& ms, const ScfOptions& opt, ScfSmallWork& w, hipStream_t st) {
-  const int nd = std::max(1, std::min(opt.ndiis, 16));
+  const int nd = std::max(1, std::min(opt.ndiis, kDiisMax));
   // molecules per launch: one per compute unit, and histories below about 1 GB
   constexpr size_t kPerLaunch = 256;
   constexpr size_t kMaxWork = (size_t(1) << 30) / sizeof(double);
