@@ -90,6 +90,19 @@ int plane_count(const DeviceMolecule& m, int precision) {
   return two ? 2 : 3;
 }
 
+// Where a chunk is formed from FP32 matrices although the molecule has planes:
+// TDHF products of many vectors below 150 AOs.  The exchange kernel has a
+// handful of workgroups there, each walking all vectors, and writing planes costs
+// it 6.3 us a vector.  Planes are the closer to FP64 (3.8e-8 against 6.7e-8 of the
+// product), so they give way only where they are slower than FP32 products have
+// been without them: at 96 AOs from 16 vectors on (32 vectors: 262 us against
+// 219), at 120 from 24 (279 against 253), at 144 from 28 (276 against 269); at 156
+// AOs 279 against 285.  In those cases matrices now take 153, 169 and 166 us.
+// CIS forms one matrix a vector and gained throughout.
+bool prefers_matrices(const DeviceMolecule& m, int theory, int kc) {
+  return theory == 1 && m.nao < 150 && 11 * kc > 2 * m.nao;
+}
+
 // One chunk of the product: kc vectors Vc -> out1c (and out2c), outputs os
 // elements apart.  ev (optional) receives the phase boundaries.
 void sigma_chunk(const DeviceMolecule& m, int theory, int kc, const double* Vc, double* out1c, double* out2c, long os,
@@ -307,15 +320,17 @@ void sigma_build_any(const DeviceMolecule& m, int theory, int k, const double* V
   const bool tdhf = theory == 1;
   const bool f32io = Vf != nullptr;
   check_sigma_args(m, precision);
-  bool planes = has_planes(m, precision);
-  if (f32io && !planes) throw Error(kEArg, "FP32 vectors need plane transforms");
+  bool has = has_planes(m, precision);
+  if (f32io && !has) throw Error(kEArg, "FP32 vectors need plane transforms");
   for (int c0 = 0, kc = 0; c0 < k; c0 += kc) {
     kc = std::min(chunk, k - c0);
     // Where memory is short, fewer vectors at a time, down to one, and then the
     // FP32 matrices (two thirds of the planes): what 32 vectors as FP32 matrices
     // need is always enough.  (Solves over FP32 vectors stop at one: their FP64
     // phase needs more than that vector's planes.)
+    bool planes;
     for (;;) {
+      planes = has && (f32io || !prefers_matrices(m, theory, kc));
       try {
         w.buf.ensure(carve_chunk(m, theory, kc, precision, planes, nullptr, nullptr));
         break;
@@ -323,7 +338,7 @@ void sigma_build_any(const DeviceMolecule& m, int theory, int k, const double* V
         if (e.status != kENoMem || (kc == 1 && (!planes || f32io))) throw;
         (void)hipGetLastError();  // a failed hipMalloc would be reported by the next launch check
         if (kc > 1) chunk = kc = (kc + 1) / 2;
-        else planes = false;
+        else has = false;
       }
     }
     ChunkBufs b;
@@ -431,7 +446,8 @@ void sigma_build_noalloc(const DeviceMolecule& m, int theory, int k, const doubl
   for (int c0 = 0; c0 < k; c0 += chunk) {
     const int kc = std::min(chunk, k - c0);
     ChunkBufs b;
-    carve_chunk(m, theory, kc, precision, planes, static_cast<unsigned char*>(base), &b);
+    carve_chunk(m, theory, kc, precision, planes && !prefers_matrices(m, theory, kc), static_cast<unsigned char*>(base),
+                &b);
     sigma_chunk(m, theory, kc, V + c0 * ov, out1 + c0 * ov, out2 ? out2 + c0 * ov : nullptr, ov, precision, b, st,
                 nullptr);
   }

@@ -44,3 +44,27 @@ def test_plane_products(mol, k, split_planes, theory):
             assert np.linalg.norm(a - b) <= bar * np.linalg.norm(b - diag)
     job.free()
     ctx.close()
+
+
+# the last and first number of vectors on either side of the rule (2 n / 11 vectors, 150 AOs), and a pass of 32 after 8
+@pytest.mark.parametrize("mol, k", [(molecules.water_cluster(16, 16), 17), (molecules.water_cluster(16, 16), 18),
+                                    (molecules.water_cluster(24, 24), 26), (molecules.water_cluster(24, 24), 27),
+                                    (molecules.water_cluster(25, 25), 32), (molecules.water_cluster(16, 16), 40)],
+                         ids=lambda x: getattr(x, "name", str(x)))
+def test_many_vectors_of_small_molecules(mol, k):
+    """TDHF products of many vectors below 150 AOs take FP32 matrices: four chained sums of at most n rounded terms,
+    sqrt(n) 2^-24 each."""
+    print(f"[gpu] many vectors {mol.name} k={k}", flush=True)
+    ctx = seqx.Context(0)
+    ctx.set_params(*seqx.params_table(PR))
+    job = ctx.prepare([mol.natoms], mol.Z, mol.xyz)
+    n, o, v = job.dims()
+    eps = job.scf_results()[0] / model.HARTREE_EV
+    V = np.random.default_rng(5).normal(size=(k, o, v))
+    diag = (eps[None, o:] - eps[:o, None]) * V
+    ref = job.sigma(V, theory=seqx.TDHF)
+    for precision in (seqx.FP32, seqx.BF16X3):
+        for a, b in zip(job.sigma(V, theory=seqx.TDHF, precision=precision), ref):
+            assert np.linalg.norm(a - b) <= 4 * np.sqrt(n) * 2.0 ** -24 * np.linalg.norm(b - diag)
+    job.free()
+    ctx.close()
