@@ -126,9 +126,13 @@ constexpr int kFlush = 4;  // panels
 // lanes of one LDS cycle (8 rows, one chunk each) touch all banks once.
 // SP, SQ: planes stored in P and Q (the first NP are used).
 //
-// Bound by the matrix cores: six products a value, 145-165 TFLOP/s of FP32
-// work or 0.9-1.0 PFLOP/s in bfloat16 (a large library bfloat16 product
-// reaches 1.1 on this card; the FP32 matrix cores gave 93-115).  (H2O)330, 20
+// Six products a value: 145-165 TFLOP/s of FP32 work or 0.9-1.0 PFLOP/s in
+// bfloat16 (a large library bfloat16 product reaches 1.1 on this card; the FP32
+// matrix cores gave 93-115).  Counters of the four products of (H2O)330, 32
+// vectors: matrix cores busy 50-58 % of the cycles, LDS 39-43 % (a quarter of it
+// bank conflicts), memory at most 3.6 TB/s, and a clock of 1.7 GHz where the FP64
+// products run at 2.3: no unit is full, the clock and the staging of a panel that
+// two workgroups overlap only in part set the time.  (H2O)330, 20
 // vectors, TDHF: C_o V 0.62 -> 0.43 ms, T1 C_v^T 0.97 -> 0.60, F C_v 1.80 ->
 // 1.29, C_o^T Z 1.49 -> 1.10; the whole products 5.23 -> 3.87 ms, with the
 // error against FP64 9.3e-8 -> 3.3e-8.  Two planes, (H2O)200, 32 vectors:
