@@ -63,9 +63,9 @@ typedef enum { SEQX_CIS = 0, SEQX_TDHF = 1 } seqx_theory;
  * projection, Gram-Schmidt, the small eigensolves and the SCF stay FP64.
  * SEQX_FP32: C, V and the AO matrices hold FP32 values, transforms with FP32
  * accumulation (on the FP32 matrix cores, or, from 96 AOs on, as products of
- * exact three-way bfloat16 splits of the FP32 values); the NDDO contraction sums in FP64 and
- * the (eps_a - eps_i) V term is added in FP64 (mixed-precision mode of the
- * paper's outlook).  A seqx_solve in FP32 restarts from its Ritz vectors with
+ * exact three-way bfloat16 splits of the FP32 values, but for many TDHF vectors
+ * below 150 AOs); the NDDO contraction sums in FP64 and the (eps_a - eps_i) V
+ * term is added in FP64 (mixed-precision mode of the paper's outlook).  A seqx_solve in FP32 restarts from its Ritz vectors with
  * FP64 products once its residuals reach max(tol, the FP32 rounding floor) or
  * stop improving, and converges to tol in FP64, so its roots carry FP64
  * accuracy.  SEQX_BF16X3: the same FP32 storage, each transform as three
@@ -106,7 +106,9 @@ typedef struct {
   double tol;           /* residual norm in hartree; <= 0 selects 1e-6 */
   int32_t max_iter;     /* <= 0 selects 100 */
   int32_t max_subspace; /* <= 0: derived from mem_budget_bytes, capped at 20 * nroots + 40 */
-  size_t mem_budget_bytes; /* 0: 40 % of free device memory (subspace + sigma scratch) */
+  size_t mem_budget_bytes; /* bounds max_subspace: bytes of the basis rows and their products; 0: 40 % of
+                              free device memory.  The workspace of the products (up to 32 vectors at a
+                              time; fewer where memory is short) comes on top. */
   int32_t precision;    /* seqx_precision of the transforms */
   int32_t guess;        /* seqx_guess */
   int32_t n_user_guess; /* SEQX_GUESS_USER: number of host vectors in user_guess */
@@ -147,7 +149,8 @@ typedef struct {
   /* Sigma-build phases since the last seqx_solve started (device time from HIP
    * events on the context stream): 0 C_occ V, 1 (C_occ V) C_virt^T,
    * 2 NDDO contraction G(R), 3 G C_virt, 4 C_occ^T (G C_virt) + de V.
-   * Flops and bytes are algorithmic (what the operation must do), not counters. */
+   * Flops and bytes are algorithmic (what the operation must do), not counters;
+   * operands count as they are stored (bfloat16 planes: 2 bytes a plane). */
   double phase_ms[5];
   int64_t phase_launches[5];
   double phase_flops[5];
@@ -267,8 +270,8 @@ seqx_status seqx_integrals(const seqx_job* job, int32_t mol, double* out, size_t
 /* Matrix-free products (Eqs. 8-9) for k host vectors V[k][nocc][nvirt]:
  *   theory CIS : out1 = A V            (out2 unused, may be NULL)
  *   theory TDHF: out1 = (A+B) V, out2 = (A-B) V
- * in hartree, with the transforms in `precision` (SEQX_FP64 or SEQX_FP32; the
- * others return SEQX_E_ARG).  Blocking host copy. */
+ * in hartree, with the transforms in `precision` (SEQX_BF16 returns
+ * SEQX_E_ARG).  Blocking host copy. */
 seqx_status seqx_sigma(seqx_job* job, int32_t mol, int32_t theory, int32_t k, const double* V,
                        double* out1, double* out2, int32_t precision);
 /* Same on device buffers (ordered on the context stream, no host sync). */

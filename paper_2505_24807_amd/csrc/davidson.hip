@@ -407,7 +407,9 @@ void dts(hipStream_t st, int ns, const TX* X, long ldx, int nt, const TY* Y, lon
 // out, which leaves their square (one combination of the basis rows); where that
 // is not enough the whole pass is repeated.  A direction that loses three
 // quarters of its norm in a repeated pass lies in the basis to working precision
-// and is left out.
+// and is left out.  8 CIS roots of 40 waters over FP32 products: 82 iterations,
+// where a single projection lost the basis at the 60th.  It costs 1.5 % of the
+// time of 20 roots of C40H42 and 3 % of the (H2O)330 TDHF step.
 constexpr double kOrthTol64 = 1e-13, kOrthFirst64 = 1e-7;
 constexpr double kOrthTol32 = 5e-7, kOrthFirst32 = 1e-4;
 constexpr int kOrthPasses = 4;

@@ -13,7 +13,9 @@ constexpr int kEigMax = 512;      // largest n of the k-lowest eigensolver
 // smallest n of it in eigh_lowest, also where all pairs are wanted: its four
 // launches take 33 us at n = 11 (65 with one cluster of all eigenvalues), 43 (75)
 // at 16, 52 (91) at 20 and 110 (164) at 48, Jacobi sweeps 39 at 10, 70 at 16, 102 at
-// 20 and 472 at 48
+// 20 and 472 at 48.  All pairs of a Gram matrix near the identity (one cluster) stay
+// ahead of the library's divide and conquer up to kEigMax: 166 us against 974 at 49,
+// 588 / 2152 at 128, 827 / 2124 at 129, 1886 / 6035 at 256, 5717 / 11305 at 512
 constexpr int kEigMin = 13;
 // largest n whose reduction stays in one workgroup: a step there costs 1.2 us at
 // n = 64, 2.0 at 128 and 3.5 at 192 (instructions of 8 wavefronts on one compute

@@ -48,9 +48,10 @@ struct SigmaWork {
 // values.  From kPlaneMinAo AOs on they are kept as three bfloat16 planes
 // (planes.hpp), which represent them exactly, and the four transforms are
 // products of the planes with FP32 accumulation, at least as accurate as the
-// FP32 matrix cores; smaller molecules use those.  kPrecBF16x3: two planes
-// (split bfloat16).  Either way the NDDO contraction multiplies and adds in
-// FP64 and the (eps_a - eps_i) V term is added in FP64.
+// FP32 matrix cores; smaller molecules, and many TDHF vectors below 150 AOs,
+// use those.  kPrecBF16x3: two planes (split bfloat16).  Either way the NDDO
+// contraction multiplies and adds in FP64 and the (eps_a - eps_i) V term is
+// added in FP64.
 void sigma_build(const DeviceMolecule& m, int theory, int k, const double* V, double* out1, double* out2,
                  SigmaWork& w, hipStream_t st, int chunk = 32, long out_stride = 0, int precision = kPrecFP64);
 
